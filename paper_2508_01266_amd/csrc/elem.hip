@@ -112,16 +112,61 @@ hipError_t tau_like(const void *x1, const void *x2, const void *t1, void *out, K
     return hipGetLastError();
 }
 
-// y2[r][ki,kj,ka][i][j][a][b] = scale * (P_ij P_ab Z)[ki,kj,ka][r][i][j][a][b] - omega_r * x2[r][...]
-// The four rows (ki,kj,ka,i,j), (kj,ki,ka,j,i), (ki,kj,kb,i,j), (kj,ki,kb,j,i) of one orbit of the
-// antisymmetriser read the same four rows of Z: with P, Q, R, S those rows and A = P - Q - R^T + S^T
-// (transposes in (a, b)) they are A, -A, -A^T and A^T.  The workgroup of the orbit's first row
-// ((ki, i) <= (kj, j), ka <= kb) writes all of its distinct rows, so Z is read about once per output
-// (the transposed reads of a row hit the cache lines its direct reads brought in); the other
-// workgroups return at once.
-template <typename T>
-__global__ void k_pp_out(const typename Cx<T>::type *Z, const double2 *x2, double2 *y2, const double *omega,
-                         KMesh km, int R, int o, int v, double scale) {
+// One orbit of the antisymmetriser P(ij)P(ab): the four rows 0: (ki,kj,ka,i,j), 1: (kj,ki,ka,j,i),
+// 2: (ki,kj,kb,i,j), 3: (kj,ki,kb,j,i) of an array read by ld(row, e) become A, -A, -A^T and A^T with
+// A = row0 - row1 - (row2 - row3)^T (transposes in (a, b)), handed to st(row, e, value).  The workgroup
+// takes the rows tile by tile: the differences row0 - row1 of tile (a, b) and row2 - row3 of tile (b, a)
+// go through LDS, so every element is read once, along its unit-stride index, and both A and -A^T are
+// written along theirs.  Bound by HBM.  (Reading the transposed elements from memory instead, twice,
+// ran at 3.6 TB/s on the batched complex64 output, v = 40, and below 1 TB/s at v = 60 with two summands,
+// whose rows do not stay in the L1 cache.)
+constexpr int kOrbTile = 32;
+struct OrbitLds {
+    double2 d[kOrbTile * (kOrbTile + 1)], e[kOrbTile * (kOrbTile + 1)];
+};
+template <typename Ld, typename St>
+__device__ __forceinline__ void orbit_rows(OrbitLds &lds, int v, bool two_pairs, bool two_blocks, Ld ld, St st) {
+    const int nt = (v + kOrbTile - 1) / kOrbTile, ts = (v + nt - 1) / nt;
+    for (int a0 = 0; a0 < v; a0 += ts)
+        for (int b0 = 0; b0 < v; b0 += ts) {
+            const int na = min(ts, v - a0), nb = min(ts, v - b0), n = na * nb;
+            for (int e = threadIdx.x; e < n; e += blockDim.x) {
+                const int a = e / nb, b = e - a * nb, at = (a0 + a) * v + b0 + b;
+                const double2 p = ld(0, at), q = ld(1, at);
+                lds.d[a * (kOrbTile + 1) + b] = make_double2(p.x - q.x, p.y - q.y);
+            }
+            for (int e = threadIdx.x; e < n; e += blockDim.x) {
+                const int b = e / na, a = e - b * na, at = (b0 + b) * v + a0 + a;
+                const double2 p = ld(2, at), q = ld(3, at);
+                lds.e[b * (kOrbTile + 1) + a] = make_double2(p.x - q.x, p.y - q.y);
+            }
+            __syncthreads();
+            for (int e = threadIdx.x; e < n; e += blockDim.x) {
+                const int a = e / nb, b = e - a * nb, at = (a0 + a) * v + b0 + b;
+                const double2 x = lds.d[a * (kOrbTile + 1) + b], y = lds.e[b * (kOrbTile + 1) + a];
+                const double2 z = make_double2(x.x - y.x, x.y - y.y);
+                st(0, at, z);
+                if (two_pairs) st(1, at, make_double2(-z.x, -z.y));
+            }
+            if (two_blocks)
+                for (int e = threadIdx.x; e < n; e += blockDim.x) {
+                    const int b = e / na, a = e - b * na, at = (b0 + b) * v + a0 + a;
+                    const double2 x = lds.d[a * (kOrbTile + 1) + b], y = lds.e[b * (kOrbTile + 1) + a];
+                    const double2 z = make_double2(x.x - y.x, x.y - y.y);
+                    st(2, at, make_double2(-z.x, -z.y));
+                    if (two_pairs) st(3, at, z);
+                }
+            __syncthreads();
+        }
+}
+
+// y2[r][ki,kj,ka][i][j][a][b] = scale * (P_ij P_ab Z)[ki,kj,ka][r][i][j][a][b] - omega_r * x2[r][...],
+// Z the sum of zs.n arrays (NS of them, or any number for NS = 0).  The workgroup of an orbit's first
+// row ((ki, i) <= (kj, j), ka <= kb) writes all of its distinct rows; the others return at once.
+template <typename T, int NS>
+__global__ void k_pp_out(SlabList zs, const double2 *x2, double2 *y2, const double *omega, KMesh km, int R, int o,
+                         int v, double scale) {
+    __shared__ OrbitLds lds;
     const int nk = km.size(), vv = v * v;
     const i64 B = (i64)nk * nk * nk;
     const i64 rows = B * R * o * o;
@@ -136,59 +181,72 @@ __global__ void k_pp_out(const typename Cx<T>::type *Z, const double2 *x2, doubl
         const int kb = km.comb(ki, kj, ka);
         const int pi = ki * o + i, pj = kj * o + j;
         if (pi > pj || ka > kb) continue;
-        const bool two_pairs = pi != pj, two_blocks = ka != kb;
         auto zrow = [&](int k0, int k1, int k2, int p, int q3) {
-            return Z + ((((i64)(k0 * nk + k1) * nk + k2) * R + r) * o + p) * o * vv + (i64)q3 * vv;
+            return ((((i64)(k0 * nk + k1) * nk + k2) * R + r) * o + p) * o * vv + (i64)q3 * vv;
         };
         auto yrow = [&](int k0, int k1, int k2, int p, int q3) {
             return (((i64)r * B + ((i64)k0 * nk + k1) * nk + k2) * o + p) * o * vv + (i64)q3 * vv;
         };
-        const typename Cx<T>::type *P = zrow(ki, kj, ka, i, j), *Q = zrow(kj, ki, ka, j, i);
-        const typename Cx<T>::type *Rz = zrow(ki, kj, kb, i, j), *S = zrow(kj, ki, kb, j, i);
-        const i64 o0 = row * vv, o1 = yrow(kj, ki, ka, j, i), o2 = yrow(ki, kj, kb, i, j), o3 = yrow(kj, ki, kb, j, i);
+        const i64 zr[4] = {zrow(ki, kj, ka, i, j), zrow(kj, ki, ka, j, i), zrow(ki, kj, kb, i, j), zrow(kj, ki, kb, j, i)};
+        const i64 yr[4] = {row * vv, yrow(kj, ki, ka, j, i), yrow(ki, kj, kb, i, j), yrow(kj, ki, kb, j, i)};
         const double w = omega ? omega[r] : 0.0;
-        auto put = [&](i64 off, int e, double zr, double zi) {
-            double2 out;
-            out.x = scale * zr;
-            out.y = scale * zi;
-            if (omega) {
-                const double2 xv = x2[off + e];
-                out.x -= w * xv.x;
-                out.y -= w * xv.y;
-            }
-            y2[off + e] = out;
-        };
-        for (int e = threadIdx.x; e < vv; e += blockDim.x) {
-            const int a = e / v, b = e - a * v, et = b * v + a;
-            const auto p = P[e], qd = Q[e], rt = Rz[et], st = S[et];
-            const double ar = (double)p.x - (double)qd.x - (double)rt.x + (double)st.x;
-            const double ai = (double)p.y - (double)qd.y - (double)rt.y + (double)st.y;
-            put(o0, e, ar, ai);
-            if (two_pairs) put(o1, e, -ar, -ai);
-            if (two_blocks) {
-                const auto pt = P[et], qt = Q[et], rd = Rz[e], sd = S[e];
-                const double tr = (double)pt.x - (double)qt.x - (double)rd.x + (double)sd.x;
-                const double ti = (double)pt.y - (double)qt.y - (double)rd.y + (double)sd.y;
-                put(o2, e, -tr, -ti);
-                if (two_pairs) put(o3, e, tr, ti);
-            }
-        }
+        orbit_rows(lds, v, pi != pj, ka != kb,
+            [&](int rw, int e) {
+                const i64 at = zr[rw] + e;
+                auto z = reinterpret_cast<const typename Cx<T>::type *>(zs.p[0])[at];
+                if constexpr (NS == 0) {
+                    for (int s = 1; s < zs.n; ++s) {
+                        const auto t = reinterpret_cast<const typename Cx<T>::type *>(zs.p[s])[at];
+                        z.x += t.x;
+                        z.y += t.y;
+                    }
+                } else {
+#pragma unroll
+                    for (int s = 1; s < NS; ++s) {
+                        const auto t = reinterpret_cast<const typename Cx<T>::type *>(zs.p[s])[at];
+                        z.x += t.x;
+                        z.y += t.y;
+                    }
+                }
+                return make_double2((double)z.x, (double)z.y);
+            },
+            [&](int rw, int e, double2 z) {
+                const i64 at = yr[rw] + e;
+                double2 out = make_double2(scale * z.x, scale * z.y);
+                if (omega) {
+                    const double2 xv = x2[at];
+                    out.x -= w * xv.x;
+                    out.y -= w * xv.y;
+                }
+                y2[at] = out;
+            });
     }
 }
 
 template <typename T>
-hipError_t pp_out(const void *Z, const void *x2, void *y2, const double *omega, KMesh km, int R, int o, int v,
+hipError_t pp_out(const SlabList &Z, const void *x2, void *y2, const double *omega, KMesh km, int R, int o, int v,
                   double scale, hipStream_t s) {
     const int nk = km.size();
     const i64 rows = (i64)nk * nk * nk * R * o * o;
-    hipLaunchKernelGGL(k_pp_out<T>, dim3(rows_grid(rows)), dim3(256), 0, s, (const typename Cx<T>::type *)Z,
-                       (const double2 *)x2, (double2 *)y2, omega, km, R, o, v, scale);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(rows_grid(rows)), dim3(256), 0, s, Z, (const double2 *)x2, (double2 *)y2, omega,
+                           km, R, o, v, scale);
+    };
+    switch (Z.n) {
+    case 1: go(k_pp_out<T, 1>); break;
+    case 2: go(k_pp_out<T, 2>); break;
+    case 3: go(k_pp_out<T, 3>); break;
+    case 4: go(k_pp_out<T, 4>); break;
+    case 5: go(k_pp_out<T, 5>); break;
+    case 6: go(k_pp_out<T, 6>); break;
+    default: go(k_pp_out<T, 0>); break;
+    }
     return hipGetLastError();
 }
 
-// y1[r][k][i][a] = s1[k][r][i][a] - omega_r x1[r][k][i][a]
+// y1[r][k][i][a] = s1[k][r][i][a] - omega_r x1[r][k][i][a], s1 the sum of s1.n arrays
 template <typename T>
-__global__ void k_s1_out(const typename Cx<T>::type *s1, const double2 *x1, double2 *y1, const double *omega,
+__global__ void k_s1_out(SlabList s1, const double2 *x1, double2 *y1, const double *omega,
                          int nk, int R, int o, int v) {
     const i64 E = (i64)o * v;
     const i64 n = (i64)R * nk * E;
@@ -196,7 +254,13 @@ __global__ void k_s1_out(const typename Cx<T>::type *s1, const double2 *x1, doub
         const i64 e = t % E;
         const int k = (int)((t / E) % nk);
         const int r = (int)(t / (E * nk));
-        auto sv = s1[((i64)k * R + r) * E + e];
+        const i64 at = ((i64)k * R + r) * E + e;
+        auto sv = reinterpret_cast<const typename Cx<T>::type *>(s1.p[0])[at];
+        for (int q = 1; q < s1.n; ++q) {
+            const auto w = reinterpret_cast<const typename Cx<T>::type *>(s1.p[q])[at];
+            sv.x += w.x;
+            sv.y += w.y;
+        }
         double2 out;
         out.x = (double)sv.x;
         out.y = (double)sv.y;
@@ -211,10 +275,9 @@ __global__ void k_s1_out(const typename Cx<T>::type *s1, const double2 *x1, doub
 }
 
 template <typename T>
-hipError_t s1_out(const void *s1, const void *x1, void *y1, const double *omega, int nk, int R, int o, int v,
+hipError_t s1_out(const SlabList &s1, const void *x1, void *y1, const double *omega, int nk, int R, int o, int v,
                   hipStream_t s) {
-    hipLaunchKernelGGL(k_s1_out<T>, dim3(grid_for((i64)R * nk * o * v)), dim3(256), 0, s,
-                       (const typename Cx<T>::type *)s1, (const double2 *)x1, (double2 *)y1, omega, nk, R, o, v);
+    hipLaunchKernelGGL(k_s1_out<T>, dim3(grid_for((i64)R * nk * o * v)), dim3(256), 0, s, s1, (const double2 *)x1, (double2 *)y1, omega, nk, R, o, v);
     return hipGetLastError();
 }
 
@@ -381,6 +444,7 @@ hipError_t conj_scale(void *y, const void *x, double s, i64 n, hipStream_t st) {
 // out = scale * c(y - y(ij swapped) - y(ab swapped) + y(both swapped)) on caller-layout doubles
 // [R][ki][kj][ka][i][j][a][b] (kb implied), c = complex conjugation when conj != 0.  Out of place.
 __global__ void k_antisym(const double2 *y, double2 *out, int R, KMesh km, int o, int v, double scale, int conj) {
+    __shared__ OrbitLds lds;
     const int nk = km.size(), vv = v * v;
     const i64 B = (i64)nk * nk * nk;
     const i64 rows = (i64)R * B * o * o;
@@ -394,18 +458,16 @@ __global__ void k_antisym(const double2 *y, double2 *out, int R, KMesh km, int o
         const int ki = (int)(q % nk);
         const i64 r = q / nk;
         const int kb = km.comb(ki, kj, ka);
+        const int pi = ki * o + i, pj = kj * o + j;
+        if (pi > pj || ka > kb) continue;
         auto rowp = [&](int k0, int k1, int k2, int p, int q3) {
-            return y + ((r * B + ((i64)k0 * nk + k1) * nk + k2) * o + p) * o * vv + (i64)q3 * vv;
+            return ((r * B + ((i64)k0 * nk + k1) * nk + k2) * o + p) * o * vv + (i64)q3 * vv;
         };
-        const double2 *Y1 = rowp(ki, kj, ka, i, j), *Y2 = rowp(kj, ki, ka, j, i);
-        const double2 *Y3 = rowp(ki, kj, kb, i, j), *Y4 = rowp(kj, ki, kb, j, i);
-        double2 *dst = out + row * vv;
-        for (int e = threadIdx.x; e < vv; e += blockDim.x) {
-            const int a = e / v, b = e - a * v, et = b * v + a;
-            const double2 z1 = Y1[e], z2 = Y2[e], z3 = Y3[et], z4 = Y4[et];
-            const double re = scale * (z1.x - z2.x - z3.x + z4.x), im = scale * (z1.y - z2.y - z3.y + z4.y);
-            dst[e] = make_double2(re, conj ? -im : im);
-        }
+        const i64 yr[4] = {row * vv, rowp(kj, ki, ka, j, i), rowp(ki, kj, kb, i, j), rowp(kj, ki, kb, j, i)};
+        orbit_rows(lds, v, pi != pj, ka != kb, [&](int rw, int e) { return y[yr[rw] + e]; },
+                   [&](int rw, int e, double2 z) {
+                       out[yr[rw] + e] = make_double2(scale * z.x, conj ? -scale * z.y : scale * z.y);
+                   });
     }
 }
 
@@ -432,6 +494,7 @@ hipError_t convert_f64_f32(const void *in, void *out, i64 n, hipStream_t s) {
 // Z[ki,kj,ka][r][i][j][a][b] = scale * (P_ij P_ab y)[r][ki,kj,ka][i][j][a][b]  (caller layout in, block layout out)
 template <typename T>
 __global__ void k_pp_in(const double2 *y, typename Cx<T>::type *Z, KMesh km, int R, int o, int v, double scale) {
+    __shared__ OrbitLds lds;
     const int nk = km.size(), vv = v * v;
     const i64 B = (i64)nk * nk * nk;
     const i64 rows = B * R * o * o;
@@ -444,17 +507,18 @@ __global__ void k_pp_in(const double2 *y, typename Cx<T>::type *Z, KMesh km, int
         const i64 blk = q / R;
         const int ka = (int)(blk % nk), kj = (int)((blk / nk) % nk), ki = (int)(blk / (nk * nk));
         const int kb = km.comb(ki, kj, ka);
-        auto rowp = [&](int k0, int k1, int k2, int p, int q3) {
-            return y + (((i64)r * B + ((i64)k0 * nk + k1) * nk + k2) * o + p) * o * vv + (i64)q3 * vv;
+        const int pi = ki * o + i, pj = kj * o + j;
+        if (pi > pj || ka > kb) continue;
+        auto yrow = [&](int k0, int k1, int k2, int p, int q3) {
+            return (((i64)r * B + ((i64)k0 * nk + k1) * nk + k2) * o + p) * o * vv + (i64)q3 * vv;
         };
-        const double2 *Y1 = rowp(ki, kj, ka, i, j), *Y2 = rowp(kj, ki, ka, j, i);
-        const double2 *Y3 = rowp(ki, kj, kb, i, j), *Y4 = rowp(kj, ki, kb, j, i);
-        typename Cx<T>::type *dst = Z + row * vv;
-        for (int e = threadIdx.x; e < vv; e += blockDim.x) {
-            const int a = e / v, b = e - a * v, et = b * v + a;
-            const double2 z1 = Y1[e], z2 = Y2[e], z3 = Y3[et], z4 = Y4[et];
-            dst[e] = mk<T>((T)(scale * (z1.x - z2.x - z3.x + z4.x)), (T)(scale * (z1.y - z2.y - z3.y + z4.y)));
-        }
+        auto zrow = [&](int k0, int k1, int k2, int p, int q3) {
+            return ((((i64)(k0 * nk + k1) * nk + k2) * R + r) * o + p) * o * vv + (i64)q3 * vv;
+        };
+        const i64 yr[4] = {yrow(ki, kj, ka, i, j), yrow(kj, ki, ka, j, i), yrow(ki, kj, kb, i, j), yrow(kj, ki, kb, j, i)};
+        const i64 zr[4] = {row * vv, zrow(kj, ki, ka, j, i), zrow(ki, kj, kb, i, j), zrow(kj, ki, kb, j, i)};
+        orbit_rows(lds, v, pi != pj, ka != kb, [&](int rw, int e) { return y[yr[rw] + e]; },
+                   [&](int rw, int e, double2 z) { Z[zr[rw] + e] = mk<T>((T)(scale * z.x), (T)(scale * z.y)); });
     }
 }
 
@@ -467,12 +531,12 @@ hipError_t pp_in(const void *y, void *Z, KMesh km, int R, int o, int v, double s
     return hipGetLastError();
 }
 
-// out[blk][r][i][j][a][b] += scale * (in[blk][r][i][j][a][b] - in[blk'][r][i][j][b][a]), blk = (ki,kj,ka),
+// out[blk][r][i][j][a][b] (+)= scale * (in[blk][r][i][j][a][b] - in[blk'][r][i][j][b][a]), blk = (ki,kj,ka),
 // blk' = (ki,kj,kb): the (a,b)-antisymmetric completion of a block-layout doubles array that holds
 // only one block of each (ka, kb) pair
 template <typename T>
 __global__ void k_expand_ab(const typename Cx<T>::type *in, typename Cx<T>::type *out, KMesh km, int R, int o,
-                            int v, T scale) {
+                            int v, T scale, int add) {
     const int nk = km.size(), vv = v * v;
     const i64 inblk = (i64)R * o * o;
     const i64 rows = (i64)nk * nk * nk * inblk;
@@ -486,18 +550,20 @@ __global__ void k_expand_ab(const typename Cx<T>::type *in, typename Cx<T>::type
         typename Cx<T>::type *dst = out + row * vv;
         for (int e = threadIdx.x; e < vv; e += blockDim.x) {
             const int a = e / v, b = e - a * v;
-            const auto x1 = X1[e], x2 = X2[b * v + a], y = dst[e];
+            const auto x1 = X1[e], x2 = X2[b * v + a];
+            auto y = mk<T>(0, 0);
+            if (add) y = dst[e];
             dst[e] = mk<T>(y.x + scale * (x1.x - x2.x), y.y + scale * (x1.y - x2.y));
         }
     }
 }
 
 template <typename T>
-hipError_t expand_ab(const void *in, void *out, KMesh km, int R, int o, int v, double scale, hipStream_t s) {
+hipError_t expand_ab(const void *in, void *out, KMesh km, int R, int o, int v, double scale, int add, hipStream_t s) {
     const int nk = km.size();
     const i64 rows = (i64)nk * nk * nk * R * o * o;
     hipLaunchKernelGGL(k_expand_ab<T>, dim3(rows_grid(rows)), dim3(256), 0, s, (const typename Cx<T>::type *)in,
-                       (typename Cx<T>::type *)out, km, R, o, v, (T)scale);
+                       (typename Cx<T>::type *)out, km, R, o, v, (T)scale, add);
     return hipGetLastError();
 }
 
@@ -599,14 +665,14 @@ hipError_t outer_oovv(void *g, const void *x, const void *y, double c, int nk, i
 #define INST(T)                                                                                              \
     template hipError_t pp_in<T>(const void *, void *, KMesh, int, int, int, double, hipStream_t);             \
     template hipError_t add_inplace<T>(void *, const void *, i64, hipStream_t);                              \
-    template hipError_t expand_ab<T>(const void *, void *, KMesh, int, int, int, double, hipStream_t);        \
+    template hipError_t expand_ab<T>(const void *, void *, KMesh, int, int, int, double, int, hipStream_t);        \
     template hipError_t zero_fill<T>(void *, i64, hipStream_t);                                              \
     template hipError_t pair_transpose<T>(const void *, void *, int, int, int, hipStream_t);                                                                                              \
     template hipError_t tau_like<T>(const void *, const void *, const void *, void *, KMesh, int, int, int,  \
                                     double, int, hipStream_t);                                               \
-    template hipError_t pp_out<T>(const void *, const void *, void *, const double *, KMesh, int, int, int,  \
+    template hipError_t pp_out<T>(const SlabList &, const void *, void *, const double *, KMesh, int, int, int,  \
                                   double, hipStream_t);                                                      \
-    template hipError_t s1_out<T>(const void *, const void *, void *, const double *, int, int, int, int,    \
+    template hipError_t s1_out<T>(const SlabList &, const void *, void *, const double *, int, int, int, int,    \
                                   hipStream_t);                                                              \
     template hipError_t chol_slice<T>(const void *, void *, int, int, int, int, int, int, int, double, int,  \
                                       hipStream_t);                                                          \

@@ -1,6 +1,7 @@
 // Launchers of the streaming kernels (definitions in elem.hip).
 #pragma once
 #include "common.hpp"
+#include "group.hpp"
 
 namespace lrcc {
 template <typename Tin, typename Tout>
@@ -9,10 +10,10 @@ template <typename T>
 hipError_t tau_like(const void *x1, const void *x2, const void *t1, void *out, KMesh km, int R, int o, int v,
                     double c, int x1_has_rhs, hipStream_t s);
 template <typename T>
-hipError_t pp_out(const void *Z, const void *x2, void *y2, const double *omega, KMesh km, int R, int o, int v,
+hipError_t pp_out(const SlabList &Z, const void *x2, void *y2, const double *omega, KMesh km, int R, int o, int v,
                   double scale, hipStream_t s);
 template <typename T>
-hipError_t s1_out(const void *s1, const void *x1, void *y1, const double *omega, int nk, int R, int o, int v,
+hipError_t s1_out(const SlabList &s1, const void *x1, void *y1, const double *omega, int nk, int R, int o, int v,
                   hipStream_t s);
 template <typename Tout>
 hipError_t chol_slice(const void *L, void *out, int nk, int naux, int n, int p0, int np, int q0, int nq,
@@ -35,10 +36,10 @@ hipError_t permute4(const void *in, void *out, KMesh km, const int *ext_in, cons
                     hipStream_t s);
 template <typename T>
 hipError_t pp_in(const void *y, void *Z, KMesh km, int R, int o, int v, double scale, hipStream_t s);
-// out += scale * (in - in with (a,b) and ka/kb swapped): completes a doubles array that holds one
+// out (+)= scale * (in - in with (a,b) and ka/kb swapped), added where `add`: completes a doubles array that holds one
 // block of each (ka, kb) pair
 template <typename T>
-hipError_t expand_ab(const void *in, void *out, KMesh km, int R, int o, int v, double scale, hipStream_t s);
+hipError_t expand_ab(const void *in, void *out, KMesh km, int R, int o, int v, double scale, int add, hipStream_t s);
 template <typename T>
 hipError_t add_inplace(void *y, const void *x, i64 n, hipStream_t s);
 template <typename T>

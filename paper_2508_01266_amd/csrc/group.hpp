@@ -1,0 +1,50 @@
+// Grouped execution of a recorded program: independent products of one dependency level run as one
+// launch over a table of work items.
+#pragma once
+#include "common.hpp"
+
+namespace lrcc {
+
+// One output tile of one product: rows m0.., columns n0.. of op `op`, reduction steps [t0, t1) of its
+// (segment, k) range starting at segment sb, added to (beta) or stored at the block at C.
+struct GroupItem {
+    void *C;
+    int op, m0, n0, sb, t0, t1;
+    float js;          // the job's multiplier of alpha
+    int beta;
+    int tile;          // index into kGroupTiles
+};
+
+// out[e] = sum over nsrc arrays, `n` elements; src indexes the table of source pointers
+struct SumSeg {
+    void *dst;
+    i64 n;
+    int src0, nsrc;
+};
+
+constexpr int kGroupTK = 16;          // reduction elements per step of a grouped product
+struct GroupTile { int m, n, frags; };   // rows, columns, 16x16 fragments per wave
+constexpr GroupTile kGroupTiles[4] = {{32, 32, 1}, {64, 64, 4}, {16, 64, 1}, {64, 16, 1}};
+constexpr int kSumChunk = 1024;       // elements of a SumSeg per workgroup
+constexpr int kMaxSlabs = 16;         // arrays an output kernel can sum
+
+// Arrays whose elementwise sum is the value of a tensor.
+struct SlabList {
+    const void *p[kMaxSlabs];
+    int n;
+};
+inline SlabList one_slab(const void *p) {
+    SlabList s{};
+    s.p[0] = p;
+    s.n = 1;
+    return s;
+}
+
+// items [0, n) of the device table; large: 64x64 tiles, else the tiles of one fragment per wave
+template <typename T>
+hipError_t launch_gemm_group(int large, const GemmArgs *ops, const GroupItem *items, int n, hipStream_t s);
+// work: one (segment, first element / kSumChunk) pair per workgroup
+template <typename T>
+hipError_t launch_sums(const SumSeg *segs, const void *const *src, const int2 *work, int n, hipStream_t s);
+
+}  // namespace lrcc

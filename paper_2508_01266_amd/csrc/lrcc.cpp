@@ -242,6 +242,7 @@ void kt_copy(Program &P, const KT &dst, const KT &src) {
     const void *s = src.p;
     size_t bytes = src.count() * 2 * sizeof(T);
     P.ops.push_back([=](hipStream_t st) { return hipMemcpyAsync(d, s, bytes, hipMemcpyDeviceToDevice, st); });
+    P.node(Node::COPY, {src.p}, dst.p, dst.count());
 }
 
 // Dressing of the virtual Cholesky slice for the ladder (t1-transformed integrals):
@@ -665,7 +666,7 @@ void tune_store(const std::string &key, const std::vector<int> &choice);
 static void tune_pre(lrcc_ctx *c, Program *p, const char *which, hipStream_t st) {
     if (!c->autotune || p->tuned || p->tunables.empty() || g_dry_run) return;
     char b[160];
-    std::snprintf(b, sizeof b, "v9,%s,%d,%d,%d,%d,ladder%d,mesh%dx%dx%d", which, c->nk, c->no, c->nv, c->naux,
+    std::snprintf(b, sizeof b, "v10,%s,%d,%d,%d,%d,ladder%d,mesh%dx%dx%d", which, c->nk, c->no, c->nv, c->naux,
                   c->ladder_mode, c->km.n0, c->km.n1, c->km.n2);
     std::vector<int> choice;
     if (tune_lookup(b, choice)) {
@@ -1000,6 +1001,25 @@ void ladder_block_gemms(lrcc_ctx *c, Program &P, bool transpose, const void *A, 
             }
 }
 
+// Output steps of a product: y1 = s1 - omega x1, y2 = scale P(ij)P(ab) Z - omega x2 (caller layouts).
+template <typename T>
+void emit_outputs(lrcc_ctx *c, Program &P, const KT &s1, const KT &Z, int R, double scale) {
+    const int nk = c->nk, o = c->no, v = c->nv;
+    const void *sp = s1.p, *zp = Z.p;
+    P.ops.push_back([=](hipStream_t s) {
+        return s1_out<T>(one_slab(sp), c->io_x1, c->io_y1, c->io_omega, nk, R, o, v, s);
+    });
+    P.node(Node::OUT, {sp}, nullptr, s1.count()).from = [=](hipStream_t s, const SlabList &l) {
+        return s1_out<T>(l, c->io_x1, c->io_y1, c->io_omega, nk, R, o, v, s);
+    };
+    P.ops.push_back([=](hipStream_t s) {
+        return pp_out<T>(one_slab(zp), c->io_x2, c->io_y2, c->io_omega, c->km, R, o, v, scale, s);
+    });
+    P.node(Node::OUT, {zp}, nullptr, Z.count()).from = [=](hipStream_t s, const SlabList &l) {
+        return pp_out<T>(l, c->io_x2, c->io_y2, c->io_omega, c->km, R, o, v, scale, s);
+    };
+}
+
 template <typename T>
 Program *build_sigma(lrcc_ctx *c, State<T> &S, int R, DevMem &wm, bool full = true, int terms = TERMS_ALL) {
     const int nk = c->nk, o = c->no, v = c->nv;
@@ -1009,9 +1029,15 @@ Program *build_sigma(lrcc_ctx *c, State<T> &S, int R, DevMem &wm, bool full = tr
     KT x1 = G.x1, x2 = G.x2, Z = G.Z, s1 = G.s1;
     // caller layout -> internal (paper -> crystal normalisation for doubles)
     P->ops.push_back([=](hipStream_t s) { return rhs_to_block<double, T>(c->io_x1, x1.p, R, nk, (i64)o * v, 1.0, s); });
+    P->node(Node::WRITE, {}, x1.p, x1.count()).write_to = [=](hipStream_t s, void *d, bool) {
+        return rhs_to_block<double, T>(c->io_x1, d, R, nk, (i64)o * v, 1.0, s);
+    };
     P->ops.push_back([=](hipStream_t s) {
         return rhs_to_block<double, T>(c->io_x2, x2.p, R, nb3, (i64)o * o * v * v, 1.0 / nk, s);
     });
+    P->node(Node::WRITE, {}, x2.p, x2.count()).write_to = [=](hipStream_t s, void *d, bool) {
+        return rhs_to_block<double, T>(c->io_x2, d, R, nb3, (i64)o * o * v * v, 1.0 / nk, s);
+    };
     for (const SymOp &op : G.ops) {
         switch (op.kind) {
         case SymOp::CON:
@@ -1025,6 +1051,9 @@ Program *build_sigma(lrcc_ctx *c, State<T> &S, int R, DevMem &wm, bool full = tr
             void *t1p = S.t1.p, *xa = op.A.p, *xb = op.B.p, *out = op.C.p;
             const KMesh km = c->km;
             P->ops.push_back([=](hipStream_t s) { return tau_like<T>(xa, xb, t1p, out, km, R, o, v, 1.0, 1, s); });
+            P->node(Node::WRITE, {xa, xb}, out, op.C.count()).write_to = [=](hipStream_t s, void *d, bool) {
+                return tau_like<T>(xa, xb, t1p, d, km, R, o, v, 1.0, 1, s);
+            };
             break;
         }
         case SymOp::LADDER: {
@@ -1077,10 +1106,7 @@ Program *build_sigma(lrcc_ctx *c, State<T> &S, int R, DevMem &wm, bool full = tr
         }
     }
     // outputs in the caller layout: y = (A - omega) x, paper normalisation
-    P->ops.push_back([=](hipStream_t s) { return s1_out<T>(s1.p, c->io_x1, c->io_y1, c->io_omega, nk, R, o, v, s); });
-    P->ops.push_back([=](hipStream_t s) {
-        return pp_out<T>(Z.p, c->io_x2, c->io_y2, c->io_omega, c->km, R, o, v, (double)nk, s);
-    });
+    emit_outputs<T>(c, *P, s1, Z, R, (double)nk);
     return P;
 }
 
@@ -1097,16 +1123,13 @@ void emit_reverse_sweep(lrcc_ctx *c, State<T> &S, int R, const SigmaGraph &G, Pr
 template <typename T>
 Program *build_sigma_adjoint(lrcc_ctx *c, State<T> &S, int R, DevMem &wm, bool full = true,
                              int terms = TERMS_ALL) {
-    const int nk = c->nk, o = c->no, v = c->nv;
+    const int nk = c->nk;
     auto P = new Program();
     SigmaGraph G = record_sigma<T>(c, S, R, wm, full, terms);
     emit_reverse_sweep<T>(c, S, R, G, P, &c->io_x1, &c->io_x2);
     KT x1 = G.x1, x2 = G.x2;
     // y1 = x1bar - omega z1 ; y2 = P(ij)P(ab) x2bar / Nk - omega z2
-    P->ops.push_back([=](hipStream_t s) { return s1_out<T>(x1.p, c->io_x1, c->io_y1, c->io_omega, nk, R, o, v, s); });
-    P->ops.push_back([=](hipStream_t s) {
-        return pp_out<T>(x2.p, c->io_x2, c->io_y2, c->io_omega, c->km, R, o, v, 1.0 / nk, s);
-    });
+    emit_outputs<T>(c, *P, x1, x2, R, 1.0 / nk);
     return P;
 }
 
@@ -1119,11 +1142,18 @@ void emit_reverse_sweep(lrcc_ctx *c, State<T> &S, int R, const SigmaGraph &G, Pr
         void *p = a.p;
         i64 n = a.count();
         P->ops.push_back([=](hipStream_t s) { return zero_fill<T>(p, n, s); });
+        P->node(Node::ZERO, {}, p, n);
     }
     KT x1 = G.x1, x2 = G.x2, Z = G.Z, s1 = G.s1;
     // cotangent of the outputs: s1bar = z1, Zbar = (Nk/4) P(ij)P(ab) z2
     P->ops.push_back([=](hipStream_t s) { return rhs_to_block<double, T>(*z1src, s1.p, R, nk, (i64)o * v, 1.0, s); });
+    P->node(Node::WRITE, {}, s1.p, s1.count()).write_to = [=](hipStream_t s, void *d, bool) {
+        return rhs_to_block<double, T>(*z1src, d, R, nk, (i64)o * v, 1.0, s);
+    };
     P->ops.push_back([=](hipStream_t s) { return pp_in<T>(*z2src, Z.p, c->km, R, o, v, 0.25 * nk, s); });
+    P->node(Node::WRITE, {}, Z.p, Z.count()).write_to = [=](hipStream_t s, void *d, bool) {
+        return pp_in<T>(*z2src, d, c->km, R, o, v, 0.25 * nk, s);
+    };
     for (auto it = G.ops.rbegin(); it != G.ops.rend(); ++it) {
         const SymOp &op = *it;
         switch (op.kind) {
@@ -1137,6 +1167,7 @@ void emit_reverse_sweep(lrcc_ctx *c, State<T> &S, int R, const SigmaGraph &G, Pr
             void *a = op.A.p, *cc = op.C.p;
             i64 n = op.A.count();
             P->ops.push_back([=](hipStream_t s) { return add_inplace<T>(a, cc, n, s); });
+            P->node(Node::ADD, {cc}, a, n);
             break;
         }
         case SymOp::TAU: {
@@ -1144,6 +1175,7 @@ void emit_reverse_sweep(lrcc_ctx *c, State<T> &S, int R, const SigmaGraph &G, Pr
             void *a = op.B.p, *cc = op.C.p;
             i64 n = op.B.count();
             P->ops.push_back([=](hipStream_t s) { return add_inplace<T>(a, cc, n, s); });
+            P->node(Node::ADD, {cc}, a, n);
             const KT &dt = op.C, &xx1 = op.A, &t1 = S.t1;
             contract<T>(*P, xx1, "Ria", dt, "Rijab", t1, "jb", 1.0, true);
             contract<T>(*P, xx1, "Rjb", dt, "Rijab", t1, "ia", 1.0, true);
@@ -1168,6 +1200,7 @@ void emit_reverse_sweep(lrcc_ctx *c, State<T> &S, int R, const SigmaGraph &G, Pr
                 void *Wb = by_class ? P->alloc((size_t)wblocks * vv * vv * 2 * sizeof(T)) : S.Wst;
                 const KMesh km = c->km;
                 P->ops.push_back([tmp, n](hipStream_t s) { return zero_fill<T>(tmp, n, s); });
+                P->node(Node::ZERO, {}, tmp, n);
                 for (int K0 = by_class ? 0 : -1; K0 < (by_class ? nk : 0); K0 += by_class ? nb : 1) {
                     const int ncl = by_class ? std::min(nb, nk - K0) : 0;
                     if (by_class) build_wstore<T>(c, *P, S.La, S.Lb, Wb, K0, ncl, TAG_BUILD);
@@ -1176,8 +1209,11 @@ void emit_reverse_sweep(lrcc_ctx *c, State<T> &S, int R, const SigmaGraph &G, Pr
                                                    : "ladder (stored integrals, transposed)");
                 }
                 P->ops.push_back([tmp, dst, km, R, o, v](hipStream_t s) {
-                    return expand_ab<T>(tmp, dst, km, R, o, v, 1.0, s);
+                    return expand_ab<T>(tmp, dst, km, R, o, v, 1.0, 1, s);
                 });
+                P->node(Node::WRITE, {tmp}, dst, n, true).write_to = [=](hipStream_t s, void *d, bool add) {
+                    return expand_ab<T>(tmp, d, km, R, o, v, 1.0, add ? 1 : 0, s);
+                };
                 break;
             }
             LadderArgs la = ladder_args<T>(c, op.C.p, S.LaT, S.LbT, op.A.p, R, op.alpha.real());
@@ -1204,10 +1240,11 @@ void emit_reverse_sweep(lrcc_ctx *c, State<T> &S, int R, const SigmaGraph &G, Pr
 // file (the path in LRCC_TUNE_CACHE); the key is nk,o,v,naux,nrhs,precision,direction,ladder path.
 std::string tune_key(lrcc_ctx *c, int prec, int R, bool adj, int variant, int path) {
     char b[128];
-    // "v9": candidate semantics (GEMM: heuristic tile shape first, up to three, four in complex64;
-    // ladder: four kernel/order variants); the ladder path (1 rebuilt in LDS, 2 stored, 3 built by
+    // "v10": candidate semantics (GEMM: heuristic tile shape first, up to three, four in complex64;
+    // ladder: four kernel/order variants; where a program has a grouped form, last: 0 grouped, else
+    // op by op); the ladder path (1 rebuilt in LDS, 2 stored, 3 built by
     // momentum class) changes the program's launches, so it is part of the key
-    std::snprintf(b, sizeof b, "v9,%d,%d,%d,%d,%d,%s,%s%d,ladder%d", c->nk, c->no, c->nv, c->naux, R,
+    std::snprintf(b, sizeof b, "v10,%d,%d,%d,%d,%d,%s,%s%d,ladder%d", c->nk, c->no, c->nv, c->naux, R,
                   prec == LRCC_FP64 ? "f64" : "f32", adj ? "adjoint" : "forward", variant, path);
     if (!c->km.chain()) return std::string(b) + ",mesh" + std::to_string(c->km.n0) + "x" + std::to_string(c->km.n1) +
                                "x" + std::to_string(c->km.n2);
@@ -1275,6 +1312,9 @@ hipError_t run_sigma(lrcc_ctx *c, Program *p, hipStream_t st) {
 // kLeanSigma: the CCSD Jacobian (complex128) without the term -x_ie R_jabe, on the blocks of the
 // lean precompute; kRTermSigma: that term alone (complex128).
 constexpr int kLeanSigma = -1, kRTermSigma = -2;
+// most device memory of the extra arrays of a program's grouped form (six doubles arrays of 64 MB, the
+// largest that are split over several, with room for the smaller tensors)
+constexpr size_t kGroupBudget = (size_t)1 << 30;
 Program *sigma_program(lrcc_ctx *c, int prec, int R, bool adjoint = false, int variant = 0) {
     auto key = std::make_pair(variant * 4 + prec * 2 + (adjoint ? 1 : 0), R);
     auto it = c->progs.find(key);
@@ -1298,6 +1338,8 @@ Program *sigma_program(lrcc_ctx *c, int prec, int R, bool adjoint = false, int v
     p->tune_key = tune_key(c, prec, R, adjoint, variant, p->ladder_path);
     c->progs[key].reset(p);
     c->progmem[key] = std::move(mem);
+    if (prec == LRCC_FP64) (void)p->group<double>(kGroupBudget);
+    else (void)p->group<float>(kGroupBudget);
     return p;
 }
 
@@ -1879,9 +1921,9 @@ void ensure_alpha_programs(lrcc_ctx *c) {
         contract<double>(*P, Z, "Rijab", t2, "ijac", Fx, "Rbc", 0.5, false);
         contract<double>(*P, Z, "Rijab", t2, "ikab", Gx, "Rkj", -0.5);
         void *xi1 = c->xi1, *xi2 = c->xi2;
-        P->ops.push_back([=](hipStream_t s) { return s1_out<double>(s1.p, nullptr, xi1, nullptr, nk, R, o, v, s); });
+        P->ops.push_back([=](hipStream_t s) { return s1_out<double>(one_slab(s1.p), nullptr, xi1, nullptr, nk, R, o, v, s); });
         const KMesh km = c->km;
-        P->ops.push_back([=](hipStream_t s) { return pp_out<double>(Z.p, nullptr, xi2, nullptr, km, R, o, v, (double)nk, s); });
+        P->ops.push_back([=](hipStream_t s) { return pp_out<double>(one_slab(Z.p), nullptr, xi2, nullptr, km, R, o, v, (double)nk, s); });
         c->prog_xi = std::move(P);
     }
     // right-hand side of the lambda equations: -(S^-1 dE/dT) = -(f_ia + <ij||ab> t_jb, <ij||ab>/Nk)
@@ -4208,7 +4250,8 @@ static void group_apply(lrcc_group *g, const int *nrhs, const double *const *ome
     // everything before the ladder (whole programs for chains that do not join)
     for (int i = 0; i < n; ++i) {
         io(i);
-        HIPCHK(prog[i]->run_range(st, 0, joined[i] ? prog[i]->ladder_op : prog[i]->ops.size()));
+        if (joined[i]) HIPCHK(prog[i]->run_range(st, 0, prog[i]->ladder_op));
+        else HIPCHK(prog[i]->run(st));
     }
     if (!join.empty()) {
         auto it = g->tab.find(key);

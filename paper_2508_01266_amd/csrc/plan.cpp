@@ -129,7 +129,18 @@ hipError_t Program::run_range(hipStream_t s, size_t begin, size_t end) {
 
 hipError_t Program::run(hipStream_t s, Profiler *prof) {
     tags.resize(ops.size(), TAG_NONE);
+    const bool grp = use_grouped && !grouped.empty();
     const bool timed = prof && prof->on;
+    if (grp && !timed) {
+        for (const Launch &l : grouped) {
+            hipError_t e = l.fn(s);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
+    const size_t nops = grp ? grouped.size() : ops.size();
+    auto tag_of = [&](size_t i) { return grp ? grouped[i].tag : tags[i]; };
+    auto run_op = [&](size_t i) { return grp ? grouped[i].fn(s) : ops[i](s); };
     hipEvent_t p0 = nullptr, p1 = nullptr;
     if (timed) {
         p0 = prof->ev();
@@ -141,30 +152,30 @@ hipError_t Program::run(hipStream_t s, Profiler *prof) {
     static const bool per_op = std::getenv("LRCC_OP_TIMES") != nullptr;
     std::vector<std::pair<hipEvent_t, hipEvent_t>> opev;
     if (timed && per_op) names.resize(ops.size());
-    for (size_t i = 0; i < ops.size(); ++i) {
+    for (size_t i = 0; i < nops; ++i) {
         hipEvent_t a = nullptr, b = nullptr;
         if (timed && per_op) {
             hipEvent_t x = prof->ev(), y = prof->ev();
             opev.push_back({x, y});
             (void)hipEventRecord(x, s);
-            hipError_t e = ops[i](s);
+            hipError_t e = run_op(i);
             if (e != hipSuccess) return e;
             (void)hipEventRecord(y, s);
-            if (tags[i] != TAG_NONE) prof->record(tags[i], x, y);   // the profile owns these two
+            if (tag_of(i) != TAG_NONE) prof->record(tag_of(i), x, y);   // the profile owns these two
             continue;
         }
-        if (timed && tags[i] != TAG_NONE) {
+        if (timed && tag_of(i) != TAG_NONE) {
             a = prof->ev();
             b = prof->ev();
             hipError_t e = hipEventRecord(a, s);
             if (e != hipSuccess) return e;
         }
-        hipError_t e = ops[i](s);
+        hipError_t e = run_op(i);
         if (e != hipSuccess) return e;
         if (a) {
             e = hipEventRecord(b, s);
             if (e != hipSuccess) return e;
-            prof->record(tags[i], a, b);
+            prof->record(tag_of(i), a, b);
         }
     }
     if (timed) {
@@ -177,8 +188,8 @@ hipError_t Program::run(hipStream_t s, Profiler *prof) {
         for (size_t i = 0; i < opev.size(); ++i) {
             float ms = 0;
             (void)hipEventElapsedTime(&ms, opev[i].first, opev[i].second);
-            std::fprintf(stderr, "[lrcc-op] %4zu %10.3f ms  %s\n", i, ms, names[i].c_str());
-            if (tags[i] != TAG_NONE) continue;
+            std::fprintf(stderr, "[lrcc-op] %4zu %10.3f ms  %s\n", i, ms, (grp ? grouped[i].name : names[i]).c_str());
+            if (tag_of(i) != TAG_NONE) continue;
             prof->pool.push_back(opev[i].first);
             prof->pool.push_back(opev[i].second);
         }
@@ -189,6 +200,7 @@ hipError_t Program::run(hipStream_t s, Profiler *prof) {
 void Program::apply(const std::vector<int> &choice) {
     for (size_t i = 0; i < tunables.size() && i < choice.size(); ++i)
         tunables[i].set(std::min(choice[i], tunables[i].ncand - 1));
+    use_grouped = choice.size() <= tunables.size() || choice[tunables.size()] == 0;
     tuned = true;
 }
 
@@ -232,6 +244,25 @@ hipError_t Program::autotune(hipStream_t s, std::vector<int> &choice) {
             for (int cnd = 0; cnd < tunables[k].ncand; ++cnd) std::fprintf(stderr, " %.3f", t[cnd][k]);
             std::fprintf(stderr, " ms -> %d\n", choice[k]);
         }
+    if (err == hipSuccess && !grouped.empty()) {
+        // the tuned ops one by one against the grouped form, each warmed up once
+        apply(choice);
+        hipEvent_t b[2];
+        if (hipEventCreate(&b[0]) != hipSuccess || hipEventCreate(&b[1]) != hipSuccess) return hipErrorUnknown;
+        float ms[2] = {0, 0};
+        for (int form = 0; form < 2 && err == hipSuccess; ++form) {
+            use_grouped = form == 0;
+            err = run(s);
+            (void)hipEventRecord(b[0], s);
+            for (int rep = 0; rep < 3 && err == hipSuccess; ++rep) err = run(s);
+            (void)hipEventRecord(b[1], s);
+            if (err == hipSuccess) err = hipEventSynchronize(b[1]);
+            if (err == hipSuccess) err = hipEventElapsedTime(&ms[form], b[0], b[1]);
+        }
+        (void)hipEventDestroy(b[0]);
+        (void)hipEventDestroy(b[1]);
+        choice.push_back(ms[0] <= ms[1] ? 0 : 1);
+    }
     apply(choice);
     return err;
 }
@@ -470,7 +501,9 @@ void raw_gemm(Program &P, GemmArgs g, const std::vector<i64> &offC, const std::v
     P.flops += P.last_flops;
     auto gp = std::make_shared<GemmArgs>(g);
     P.ops.push_back([gp](hipStream_t s) { return launch_gemm<T>(*gp, s); });
-    P.gemm_ops[P.ops.size() - 1] = Program::GemmOp{gp, sizeof(T) == 8, P.last_flops};
+    P.gemm_ops[P.ops.size() - 1] = Program::GemmOp{gp, sizeof(T) == 8, P.last_flops, offC, segBeg, jscale, sizeC};
+    P.node(Node::GEMM, {g.A, g.B}, g.C, sizeC, g.beta != 0).full =
+        !g.sm.tri && !g.sn.tri && (i64)g.M * g.N * g.njobs == sizeC;
     // candidates: tile shapes, the heuristic one first
     const std::vector<int> cand = gemm_candidates(g, sizeof(T) == 8);
     P.tunables.push_back({P.ops.size() - 1, (int)cand.size(), [gp, cand](int c) { gp->shape = c == 0 ? -1 : cand[c]; }});
@@ -587,6 +620,7 @@ void contract_packed(Program &P, const KT &C, const std::string &cl, const KT &A
         void *cp = C.p;
         const i64 n = C.count();
         P.ops.push_back([cp, n](hipStream_t s) { return zero_fill<T>(cp, n, s); });
+        P.node(Node::ZERO, {}, cp, n);
     }
     for (int m = 0; m < (1 << np); ++m) {
         if (offC[m].empty()) continue;

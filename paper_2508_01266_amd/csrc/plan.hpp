@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "common.hpp"
+#include "group.hpp"
 
 namespace lrcc {
 
@@ -68,6 +69,21 @@ struct Tunable {
     std::function<void(int)> set;
 };
 
+// Data flow of one recorded op of a program that may run grouped (see Program::group).  Tensors are
+// identified by their base pointers; `acc`: adds to the tensor it writes; `full`: writes every element.
+struct Node {
+    enum Kind { GEMM, ZERO, COPY, ADD, WRITE, OUT } kind = GEMM;
+    size_t op = 0;                    // index into Program::ops
+    std::vector<const void *> reads;
+    void *write = nullptr;            // tensor written (null for OUT)
+    i64 count = 0;                    // its elements
+    bool acc = false, full = true;
+    // WRITE: the op writing to dst, or adding to it.  OUT: the op reading the sum of the arrays that
+    // make up reads[0]
+    std::function<hipError_t(hipStream_t, void *dst, bool acc)> write_to;
+    std::function<hipError_t(hipStream_t, const SlabList &)> from;
+};
+
 // A recorded sequence of device launches plus the device memory it owns.
 struct Program {
     std::vector<std::function<hipError_t(hipStream_t)>> ops;
@@ -77,6 +93,36 @@ struct Program {
         names.resize(ops.size());
         names.back() = n;
     }
+    // Grouped form: the ops' data flow (one node per op where every op has one) and the launches made
+    // from it by group(): the products of one dependency level as one launch over a table of work
+    // items, with separate arrays for contributions to one tensor that would have to wait for each
+    // other.  Empty: the program runs op by op.
+    std::vector<Node> nodes;
+    struct Launch {
+        std::function<hipError_t(hipStream_t)> fn;
+        int tag;
+        std::string name;
+    };
+    std::vector<Launch> grouped;
+    bool use_grouped = true;             // run the grouped form where there is one
+    // node of the op recorded last
+    Node &node(Node::Kind k, std::vector<const void *> reads, void *write, i64 count, bool acc = false) {
+        Node n;
+        n.kind = k;
+        n.op = ops.size() - 1;
+        n.reads = std::move(reads);
+        n.write = write;
+        n.count = count;
+        n.acc = acc;
+        nodes.push_back(std::move(n));
+        return nodes.back();
+    }
+    // make the grouped form if the data flow allows it and its extra arrays take at most `budget`
+    // bytes; returns whether it was made
+    template <typename T>
+    bool group(size_t budget);
+    template <typename T>
+    bool make_grouped(size_t budget);
     std::vector<Tunable> tunables;
     bool tuned = false;
     std::string tune_key;
@@ -100,6 +146,10 @@ struct Program {
         std::shared_ptr<GemmArgs> args;
         bool fp64;
         i64 flops;
+        std::vector<i64> offC;          // host copies of the job lists
+        std::vector<int> segBeg;
+        std::vector<float> jscale;
+        i64 sizeC;
     };
     std::map<size_t, GemmOp> gemm_ops;
     // real flops of the matrix-core instructions of the GEMM launches with tag t: 8 per complex
