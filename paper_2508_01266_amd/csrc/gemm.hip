@@ -3,8 +3,9 @@
 // A complex product is four real MFMA products on split real/imaginary
 // planes staged in LDS: Cre += Are*Bre - Aim*Bim, Cim += Are*Bim + Aim*Bre.
 // 256 threads = 4 waves; each wave owns a WTM x WTN sub-tile of 16x16x4 MFMA
-// blocks.  Tile shapes: 64x64 (default), 128x128 (complex64, large M and N)
-// and 128x64 (complex128, large M).  Operand addresses use the three-level
+// blocks.  Tile shapes: 64x64 (default), 16x256 (small M) and 128x64
+// (complex128, large M); the large complex64 products run on the bf16 matrix
+// cores instead (split.hip).  Operand addresses use the three-level
 // index splits of GemmArgs so that k-blocked tensors are read in place (no
 // permute passes); the thread->element map of each tile load runs along the
 // unit-stride index when one exists, for coalesced loads.
@@ -34,9 +35,7 @@ template <> struct Mfma<float> {
 
 constexpr int TK = 16, NT = 256;
 
-// G3: complex products from three real matrix-core products (Gauss' method:
-// k1 = br (ar + ai), k2 = ar (bi - br), k3 = ai (br + bi); re = k1 - k3, im = k1 + k2)
-template <typename T, int TM, int TN, int WTM, int WTN, int KIND, bool G3 = false>
+template <typename T, int TM, int TN, int WTM, int WTN, int KIND>
 __global__ void __launch_bounds__(NT) gemm_kernel(GemmArgs g) {
     typedef typename Cx<T>::type C2;
     typedef typename Mfma<T>::v4 v4;
@@ -86,17 +85,11 @@ __global__ void __launch_bounds__(NT) gemm_kernel(GemmArgs g) {
         bcol[q] = bok[q] ? split_off32(gn, g.sn, (int)g.Bn.s[0], (int)g.Bn.s[1], (int)g.Bn.s[2]) : 0;
     }
 
-    v4 accr[FM][FN], acci[FM][FN], acc3[G3 ? FM : 1][G3 ? FN : 1];
+    v4 accr[FM][FN], acci[FM][FN];
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < FN; ++j) { accr[i][j] = v4{0, 0, 0, 0}; acci[i][j] = v4{0, 0, 0, 0}; }
-    if constexpr (G3) {
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-            for (int j = 0; j < FN; ++j) acc3[i][j] = v4{0, 0, 0, 0};
-    }
 
     const int sb = g.segBeg[job], se = g.segBeg[job + 1];
     const int ksteps = (g.K + TK - 1) / TK;
@@ -142,30 +135,14 @@ __global__ void __launch_bounds__(NT) gemm_kernel(GemmArgs g) {
             for (int i = 0; i < FM; ++i)
 #pragma unroll
                 for (int j = 0; j < FN; ++j) {
-                    if constexpr (G3) {
-                        accr[i][j] = Mfma<T>::mma(ar[i] + ai[i], br[j], accr[i][j]);
-                        acci[i][j] = Mfma<T>::mma(ar[i], bi[j] - br[j], acci[i][j]);
-                        acc3[i][j] = Mfma<T>::mma(ai[i], br[j] + bi[j], acc3[i][j]);
-                    } else {
-                        accr[i][j] = Mfma<T>::mma(ar[i], br[j], accr[i][j]);
-                        accr[i][j] = Mfma<T>::mma(-ai[i], bi[j], accr[i][j]);
-                        acci[i][j] = Mfma<T>::mma(ar[i], bi[j], acci[i][j]);
-                        acci[i][j] = Mfma<T>::mma(ai[i], br[j], acci[i][j]);
-                    }
+                    accr[i][j] = Mfma<T>::mma(ar[i], br[j], accr[i][j]);
+                    accr[i][j] = Mfma<T>::mma(-ai[i], bi[j], accr[i][j]);
+                    acci[i][j] = Mfma<T>::mma(ar[i], bi[j], acci[i][j]);
+                    acci[i][j] = Mfma<T>::mma(ai[i], br[j], acci[i][j]);
                 }
         }
         __syncthreads();
     }
-    if constexpr (G3) {
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-            for (int j = 0; j < FN; ++j) {
-                acci[i][j] = accr[i][j] + acci[i][j];
-                accr[i][j] = accr[i][j] - acc3[i][j];
-            }
-    }
-
     if (g.ksplit > 1) {
         // raw partial sums, reduced by k_gemm_reduce
         C2 *Pj = reinterpret_cast<C2 *>(g.part) + ((i64)split * g.njobs_all + g.job0 + job) * g.M * g.N;
@@ -238,7 +215,7 @@ __global__ void __launch_bounds__(NT) gemm_kernel(GemmArgs g) {
     }
 }
 
-template <typename T, int TM, int TN, int WTM, int WTN, bool G3 = false>
+template <typename T, int TM, int TN, int WTM, int WTN>
 hipError_t launch_shape(const GemmArgs &g, hipStream_t s) {
     const int tilesM = (g.M + TM - 1) / TM, tilesN = (g.N + TN - 1) / TN;
     // grid.y is limited to 65535: launch the job list in chunks
@@ -251,10 +228,10 @@ hipError_t launch_shape(const GemmArgs &g, hipStream_t s) {
         dim3 grid(tilesM * tilesN, c.njobs, g.ksplit);
         // KIND 2 (generic) and 3 (ladder): the reduction index is a triangle split
         if (g.sk.tri && g.kind == 1)
-            hipLaunchKernelGGL((gemm_kernel<T, TM, TN, WTM, WTN, 3, G3>), grid, dim3(NT), 0, s, c);
-        else if (g.sk.tri) hipLaunchKernelGGL((gemm_kernel<T, TM, TN, WTM, WTN, 2, G3>), grid, dim3(NT), 0, s, c);
-        else if (g.kind == 1) hipLaunchKernelGGL((gemm_kernel<T, TM, TN, WTM, WTN, 1, G3>), grid, dim3(NT), 0, s, c);
-        else hipLaunchKernelGGL((gemm_kernel<T, TM, TN, WTM, WTN, 0, G3>), grid, dim3(NT), 0, s, c);
+            hipLaunchKernelGGL((gemm_kernel<T, TM, TN, WTM, WTN, 3>), grid, dim3(NT), 0, s, c);
+        else if (g.sk.tri) hipLaunchKernelGGL((gemm_kernel<T, TM, TN, WTM, WTN, 2>), grid, dim3(NT), 0, s, c);
+        else if (g.kind == 1) hipLaunchKernelGGL((gemm_kernel<T, TM, TN, WTM, WTN, 1>), grid, dim3(NT), 0, s, c);
+        else hipLaunchKernelGGL((gemm_kernel<T, TM, TN, WTM, WTN, 0>), grid, dim3(NT), 0, s, c);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -289,8 +266,12 @@ __global__ void k_gemm_reduce(GemmArgs g) {
 
 int gemm_shape(const GemmArgs &g, bool fp64) {
     if (g.shape >= 0) return g.shape;
+    // complex64: the bf16 products need a reduction that fills most of a 32-deep step and tiles that are
+    // not mostly edge (Nk=5, o=8, v=40, 48 right-hand sides: M=3072 N=1600 K=28 0.43 against 0.49 ms of
+    // 64x64, M=122880 N=40 K=40 3.4 against 4.6, M=3072 N=28 K=1600 0.44 against 0.52; but
+    // M=2560 N=1920 K=8 2.2 against 2.0, M=64 N=76800 K=64 1.17 against 1.13)
+    if (!fp64 && g.K >= 24 && g.M >= 96 && g.N >= 24) return 3;
     if (g.M <= 16 && g.N >= 128) return 2;
-    if (g.M >= 128 && g.N >= 128) return 1;
     if (fp64 && g.M >= 128 && g.N >= 64) return 1;
     return 0;
 }
@@ -299,15 +280,10 @@ std::vector<int> gemm_candidates(const GemmArgs &g, bool fp64) {
     GemmArgs h = g;
     h.shape = -1;
     std::vector<int> c{gemm_shape(h, fp64)};
-    // complex64 large tiles also come with three real products per complex one (4)
-    const int others[5] = {0, 1, 3, 4, 2};
-    const int cap = fp64 ? 3 : 4;
-    for (int s : others) {
-        if ((int)c.size() == cap) break;
-        if ((s == 3 || s == 4) && fp64) continue;   // complex128 large tile is already 128x64
-        if (s == 4 && (g.M < 128 || g.N < 128)) continue;
+    for (int s : {3, 0, 1, 2}) {
+        if (s == 1 && (!fp64 || g.M < 64)) continue;
+        if (s == 3 && (fp64 || g.M < 32 || g.N < 16)) continue;
         if (s == 2 && g.M > 32) continue;         // small-M tile only for short M
-        if (s != 0 && g.M < 64 && s != 2) continue;
         if (std::find(c.begin(), c.end(), s) == c.end()) c.push_back(s);
     }
     return c;
@@ -319,17 +295,11 @@ hipError_t launch_gemm(const GemmArgs &g, hipStream_t s) {
     constexpr bool f64 = sizeof(T) == 8;
     hipError_t e;
     switch (gemm_shape(g, f64)) {
-    case 1:
-        if constexpr (f64) e = launch_shape<T, 128, 64, 64, 32>(g, s);
-        else e = launch_shape<T, 128, 128, 64, 64>(g, s);
-        break;
+    case 1: e = launch_shape<T, 128, 64, 64, 32>(g, s); break;
     case 2: e = launch_shape<T, 16, 256, 16, 64>(g, s); break;
-    case 3:   // complex64 only: 128x64 tiles with three real products per complex one
-        e = launch_shape<T, 128, 64, 64, 32, !f64>(g, s);
-        break;
-    case 4:   // complex64 only: 128x128 tiles with three real products per complex one
-        if constexpr (f64) e = launch_shape<T, 128, 64, 64, 32>(g, s);
-        else e = launch_shape<T, 128, 128, 64, 64, true>(g, s);
+    case 3:   // complex64 only (split.hip)
+        if constexpr (f64) e = hipErrorInvalidValue;
+        else e = launch_gemm_split(g, s);
         break;
     default: e = launch_shape<T, 64, 64, 32, 32>(g, s); break;
     }

@@ -1240,7 +1240,7 @@ void emit_reverse_sweep(lrcc_ctx *c, State<T> &S, int R, const SigmaGraph &G, Pr
 // file (the path in LRCC_TUNE_CACHE); the key is nk,o,v,naux,nrhs,precision,direction,ladder path.
 std::string tune_key(lrcc_ctx *c, int prec, int R, bool adj, int variant, int path) {
     char b[128];
-    // "v10": candidate semantics (GEMM: heuristic tile shape first, up to three, four in complex64;
+    // "v10": candidate semantics (GEMM: heuristic tile shape first;
     // ladder: four kernel/order variants; where a program has a grouped form, last: 0 grouped, else
     // op by op); the ladder path (1 rebuilt in LDS, 2 stored, 3 built by
     // momentum class) changes the program's launches, so it is part of the key

@@ -49,8 +49,7 @@ double Program::tag_mfma_flops(int t) const {
     for (const auto &kv : gemm_ops) {
         if (kv.first >= tags.size() || tags[kv.first] != t) continue;
         const int sh = gemm_shape(*kv.second.args, kv.second.fp64);
-        const bool g3 = !kv.second.fp64 && (sh == 3 || sh == 4);
-        f += (double)kv.second.flops * (g3 ? 0.75 : 1.0);
+        f += (double)kv.second.flops * (!kv.second.fp64 && sh == 3 ? 6.0 : 1.0);   // six bf16 products per fp32 one
     }
     return f;
 }
@@ -254,7 +253,7 @@ hipError_t Program::autotune(hipStream_t s, std::vector<int> &choice) {
             use_grouped = form == 0;
             err = run(s);
             (void)hipEventRecord(b[0], s);
-            for (int rep = 0; rep < 3 && err == hipSuccess; ++rep) err = run(s);
+            if (err == hipSuccess) err = run(s);
             (void)hipEventRecord(b[1], s);
             if (err == hipSuccess) err = hipEventSynchronize(b[1]);
             if (err == hipSuccess) err = hipEventElapsedTime(&ms[form], b[0], b[1]);

@@ -153,7 +153,7 @@ struct Program {
     };
     std::map<size_t, GemmOp> gemm_ops;
     // real flops of the matrix-core instructions of the GEMM launches with tag t: 8 per complex
-    // multiply-add formed, 6 for the tiles that form complex products from three real ones
+    // multiply-add formed, 48 for the tiles that form a real product from six bf16 ones
     double tag_mfma_flops(int t) const;
     // ladder path of a sigma program: 1 integrals rebuilt in LDS, 2 stored blocks, 3 blocks built
     // one momentum class at a time (0: no ladder term)

@@ -1,0 +1,276 @@
+// complex64 products on the bf16 matrix cores.
+//
+// Every fp32 operand x is the sum of three bf16 numbers, x = h + m + l, up to 2^-25 |x| (h, m, l the
+// roundings of x and of what is left), and a product is formed from six bf16 products with fp32
+// accumulation, smallest first: h l + l h + m m + m h + h m + h h.  The terms left out (m l, l m, l l)
+// are below 2^-24 |a b|.  The matrix cores run bf16 16 times as fast as fp32, so six products leave a
+// factor of 2.7; a complex product takes 24 of them.  An infinite operand gives NaN (its remainder is
+// NaN), a finite one above the largest bf16 number, 3.39e38, too.
+#include "common.hpp"
+
+namespace lrcc {
+
+namespace {
+constexpr int NT = 256;
+typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+typedef float f2 __attribute__((ext_vector_type(2)));
+typedef float v4 __attribute__((ext_vector_type(4)));
+typedef unsigned u4 __attribute__((ext_vector_type(4)));
+struct __attribute__((aligned(8))) c64x2 { float2 a, b; };   // two elements, 8-byte aligned
+
+__device__ __forceinline__ v4 mma(bf8 a, bf8 b, v4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ unsigned bits(bf2 x) { return __builtin_bit_cast(unsigned, x); }
+
+// the three bf16 parts of eight values (pairs packed in order)
+__device__ __forceinline__ void split8(const float *x, u4 &h, u4 &m, u4 &l) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const f2 v = {x[2 * i], x[2 * i + 1]};
+        const bf2 a = __builtin_convertvector(v, bf2);
+        const f2 r = v - __builtin_convertvector(a, f2);
+        const bf2 b = __builtin_convertvector(r, bf2);
+        const f2 q = r - __builtin_convertvector(b, f2);
+        h[i] = bits(a);
+        m[i] = bits(b);
+        l[i] = bits(__builtin_convertvector(q, bf2));
+    }
+}
+}  // namespace
+
+// 128x64 tiles, 32-deep steps, four waves of 64x32; an LDS unit is eight consecutive reduction elements
+// of one row of one part (re/im x h/m/l), the operand of one 16x16x32 instruction per lane.  75 KB of LDS
+// and under 256 registers: two workgroups per compute unit, so that one converts while the other
+// multiplies.  Operands are loaded one step ahead, eight elements of a row per thread.
+// RUN: every unit lies in one run of the reduction index (its innermost extent is a multiple of 8).
+template <bool RUN>
+__global__ void __launch_bounds__(NT, 2) gemm_split_kernel(GemmArgs g) {
+    constexpr int TM = 128, TN = 64, TK = 32, KG = TK / 8;
+    constexpr int FM = 4, FN = 2, UA = TM * KG / NT, UB = TN * KG / NT;
+    // the k groups of a row start 8 banks apart
+    constexpr int SA = TM + 2, SB = TN + 2;
+    __shared__ u4 lA[6 * KG * SA], lB[6 * KG * SB];
+    const int job = blockIdx.y, split = blockIdx.z;
+    const int tilesM = (g.M + TM - 1) / TM;
+    const int m0 = (blockIdx.x % tilesM) * TM, n0 = (blockIdx.x / tilesM) * TN;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = (wave & 1) * 64, wn = (wave >> 1) * 32;
+    const float2 *A = reinterpret_cast<const float2 *>(g.A);
+    const float2 *B = reinterpret_cast<const float2 *>(g.B);
+    float2 *C = reinterpret_cast<float2 *>(g.C);
+    const int ak0 = (int)g.Ak.s[0], ak1 = (int)g.Ak.s[1], ak2 = (int)g.Ak.s[2];
+    const int bk0 = (int)g.Bk.s[0], bk1 = (int)g.Bk.s[1], bk2 = (int)g.Bk.s[2];
+    int arow[UA], akg[UA], am[UA], bcol[UB], bkg[UB], bn[UB];
+    bool aok[UA], bok[UB];
+#pragma unroll
+    for (int q = 0; q < UA; ++q) {
+        const int idx = tid + NT * q;
+        if (g.aMfast) { am[q] = idx % TM; akg[q] = idx / TM; } else { akg[q] = idx % KG; am[q] = idx / KG; }
+        const int gm = m0 + am[q];
+        aok[q] = gm < g.M;
+        arow[q] = aok[q] ? split_off32(gm, g.sm, (int)g.Am.s[0], (int)g.Am.s[1], (int)g.Am.s[2]) : 0;
+    }
+#pragma unroll
+    for (int q = 0; q < UB; ++q) {
+        const int idx = tid + NT * q;
+        if (g.bNfast) { bn[q] = idx % TN; bkg[q] = idx / TN; } else { bkg[q] = idx % KG; bn[q] = idx / KG; }
+        const int gn = n0 + bn[q];
+        bok[q] = gn < g.N;
+        bcol[q] = bok[q] ? split_off32(gn, g.sn, (int)g.Bn.s[0], (int)g.Bn.s[1], (int)g.Bn.s[2]) : 0;
+    }
+    v4 accr[FM][FN], acci[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) { accr[i][j] = v4{0, 0, 0, 0}; acci[i][j] = v4{0, 0, 0, 0}; }
+
+    const int sb = g.segBeg[job], se = g.segBeg[job + 1];
+    const int ksteps = (g.K + TK - 1) / TK;
+    const i64 nsteps = (i64)(se - sb) * ksteps;
+    const int tbeg = (int)(nsteps * split / g.ksplit), tend = (int)(nsteps * (split + 1) / g.ksplit);
+    float2 va[UA][8], vb[UB][8];
+    auto unit = [&](const float2 *P, int row, bool ok, int k, int s0, int s1, int s2, float2 *v) {
+        if (RUN) {
+            if (ok && k < g.K) {
+                const float2 *p = P + row + split_off32<false>(k, g.sk, s0, s1, s2);
+                if (s2 == 1) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const c64x2 w = *reinterpret_cast<const c64x2 *>(p + 2 * i);
+                        v[2 * i] = w.a;
+                        v[2 * i + 1] = w.b;
+                    }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) v[i] = p[i * s2];
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[i] = make_float2(0, 0);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                v[i] = ok && k + i < g.K ? P[row + split_off32<true>(k + i, g.sk, s0, s1, s2)] : make_float2(0, 0);
+        }
+    };
+    auto fetch = [&](int t) {
+        const int s = sb + t / ksteps, k0 = (t % ksteps) * TK;
+        const float2 *As = A + g.segA[s];
+        const float2 *Bs = B + g.segB[s];
+#pragma unroll
+        for (int q = 0; q < UA; ++q) unit(As, arow[q], aok[q], k0 + 8 * akg[q], ak0, ak1, ak2, va[q]);
+#pragma unroll
+        for (int q = 0; q < UB; ++q) unit(Bs, bcol[q], bok[q], k0 + 8 * bkg[q], bk0, bk1, bk2, vb[q]);
+    };
+    auto put = [&](const float2 *v, u4 *l, int stride, int at) {
+        float x[8], y[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) { x[i] = v[i].x; y[i] = v[i].y; }
+        u4 p[3];
+        split8(x, p[0], p[1], p[2]);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) l[c * KG * stride + at] = p[c];
+        split8(y, p[0], p[1], p[2]);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) l[(3 + c) * KG * stride + at] = p[c];
+    };
+    if (tbeg < tend) fetch(tbeg);
+    for (int t = tbeg; t < tend; ++t) {
+#pragma unroll
+        for (int q = 0; q < UA; ++q) put(va[q], lA, SA, akg[q] * SA + am[q]);
+#pragma unroll
+        for (int q = 0; q < UB; ++q) put(vb[q], lB, SB, bkg[q] * SB + bn[q]);
+        __syncthreads();
+        if (t + 1 < tend) fetch(t + 1);
+        const int kg = lane >> 4, c = lane & 15;
+        bf8 b[FN][6];
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int p = 0; p < 6; ++p)
+                b[j][p] = __builtin_bit_cast(bf8, lB[(p * KG + kg) * SB + wn + 16 * j + c]);
+#pragma unroll
+        for (int i = 0; i < FM; ++i) {
+            bf8 a[6], na[3];
+#pragma unroll
+            for (int p = 0; p < 6; ++p) {
+                const u4 w = lA[(p * KG + kg) * SA + wm + 16 * i + c];
+                a[p] = __builtin_bit_cast(bf8, w);
+                if (p >= 3) na[p - 3] = __builtin_bit_cast(bf8, w ^ u4{0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u});
+            }
+            // the five small products of a step are summed apart and added to the running sum once:
+            // an instruction rounds its accumulator every four elements, and at the size of the small
+            // sums those roundings do not count
+            constexpr int pa[5] = {0, 2, 1, 1, 0}, pb[5] = {2, 0, 1, 0, 1};
+            v4 lr[FN], li[FN];
+#pragma unroll
+            for (int j = 0; j < FN; ++j) { lr[j] = v4{0, 0, 0, 0}; li[j] = v4{0, 0, 0, 0}; }
+#pragma unroll
+            for (int q = 0; q < 5; ++q) {
+#pragma unroll
+                for (int j = 0; j < FN; ++j) {
+                    lr[j] = mma(a[pa[q]], b[j][pb[q]], lr[j]);
+                    li[j] = mma(a[pa[q]], b[j][3 + pb[q]], li[j]);
+                }
+#pragma unroll
+                for (int j = 0; j < FN; ++j) {
+                    lr[j] = mma(na[pa[q]], b[j][3 + pb[q]], lr[j]);
+                    li[j] = mma(a[3 + pa[q]], b[j][pb[q]], li[j]);
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+                accr[i][j] = mma(a[0], b[j][0], accr[i][j]);
+                acci[i][j] = mma(a[0], b[j][3], acci[i][j]);
+            }
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+                accr[i][j] = mma(na[0], b[j][3], accr[i][j]);
+                acci[i][j] = mma(a[3], b[j][0], acci[i][j]);
+            }
+#pragma unroll
+            for (int j = 0; j < FN; ++j) { accr[i][j] += lr[j]; acci[i][j] += li[j]; }
+        }
+        __syncthreads();
+    }
+    if (g.ksplit > 1) {
+        // raw partial sums, reduced by a second kernel
+        float2 *Pj = reinterpret_cast<float2 *>(g.part) + ((i64)split * g.njobs_all + g.job0 + job) * g.M * g.N;
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int gm = m0 + wm + 16 * i + 4 * (lane >> 4) + r;
+                    const int gn = n0 + wn + 16 * j + (lane & 15);
+                    if (gm < g.M && gn < g.N) Pj[(i64)gm * g.N + gn] = make_float2(accr[i][j][r], acci[i][j][r]);
+                }
+        return;
+    }
+    const float js = g.jscale ? g.jscale[g.job0 + job] : 1.0f;
+    const float alr = js * (float)g.alpha_re, ali = js * (float)g.alpha_im;
+    float2 *Cj = C + g.offC[job];
+    i64 coff[FN];
+    bool cok[FN];
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+        const int gn = n0 + wn + 16 * j + (lane & 15);
+        cok[j] = gn < g.N;
+        coff[j] = cok[j] ? split_off(gn, g.sn, g.Cn) : 0;
+    }
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+        i64 roff[4];
+        bool rok[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int gm = m0 + wm + 16 * i + 4 * (lane >> 4) + r;
+            rok[r] = gm < g.M;
+            roff[r] = rok[r] ? split_off(gm, g.sm, g.Cm) : 0;
+        }
+        float2 old[FN][4];
+        if (g.beta) {
+            // all reads before the first write; (0, 0) of the block stands in for outside elements
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) old[j][r] = Cj[rok[r] && cok[j] ? roff[r] + coff[j] : 0];
+        }
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if (!(rok[r] && cok[j])) continue;
+                const float xr = accr[i][j][r], xi = acci[i][j][r];
+                float2 w = make_float2(alr * xr - ali * xi, alr * xi + ali * xr);
+                if (g.beta) { w.x += old[j][r].x; w.y += old[j][r].y; }
+                Cj[roff[r] + coff[j]] = w;
+            }
+    }
+}
+
+hipError_t launch_gemm_split(const GemmArgs &g, hipStream_t s) {
+    const int tilesM = (g.M + 127) / 128, tilesN = (g.N + 63) / 64;
+    const bool run = !g.sk.tri && g.sk.d2 % 8 == 0;
+    // grid.y is limited to 65535: launch the job list in chunks
+    for (int j0 = 0; j0 < g.njobs; j0 += 65535) {
+        GemmArgs c = g;
+        c.njobs = (g.njobs - j0 < 65535) ? g.njobs - j0 : 65535;
+        c.offC = g.offC + j0;
+        c.segBeg = g.segBeg + j0;
+        c.job0 = j0;
+        const dim3 grid(tilesM * tilesN, c.njobs, g.ksplit);
+        if (run) hipLaunchKernelGGL(gemm_split_kernel<true>, grid, dim3(NT), 0, s, c);
+        else hipLaunchKernelGGL(gemm_split_kernel<false>, grid, dim3(NT), 0, s, c);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+}  // namespace lrcc
