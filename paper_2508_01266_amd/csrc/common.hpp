@@ -141,8 +141,7 @@ struct GemmArgs {
     Split sm, sn, sk;
     Strides Am, Ak, Bk, Bn, Cm, Cn;
     int aMfast, bNfast;  // tile-load thread maps: 1 = run along m (resp. n)
-    int shape;           // tile shape: -1 automatic, 0 = 64x64, 1 = 128x64 (complex128), 2 = 16x256
-                         // (small M), 3 = 128x64 on the bf16 matrix cores (complex64)
+    int shape;           // tile: -1 automatic, else an index into kGroupTiles, or kSplitTile
     int alt;             // unused (kept zero)
     double alpha_re, alpha_im;
     int beta;

@@ -25,6 +25,9 @@ struct SumSeg {
 constexpr int kGroupTK = 16;          // reduction elements per step of a grouped product
 struct GroupTile { int m, n, frags; };   // rows, columns, 16x16 fragments per wave
 constexpr GroupTile kGroupTiles[4] = {{32, 32, 1}, {64, 64, 4}, {16, 64, 1}, {64, 16, 1}};
+constexpr int kSplitTile = 4;            // 128x64 on the bf16 matrix cores, complex64 (split.hip)
+// index of the tile for M x N outputs of each of `jobs` blocks; fill: the launch has to fill the device
+int best_tile(int M, int N, i64 jobs, bool fill);
 constexpr int kSumChunk = 1024;       // elements of a SumSeg per workgroup
 constexpr int kMaxSlabs = 16;         // arrays an output kernel can sum
 

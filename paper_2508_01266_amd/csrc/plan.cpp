@@ -49,7 +49,7 @@ double Program::tag_mfma_flops(int t) const {
     for (const auto &kv : gemm_ops) {
         if (kv.first >= tags.size() || tags[kv.first] != t) continue;
         const int sh = gemm_shape(*kv.second.args, kv.second.fp64);
-        f += (double)kv.second.flops * (!kv.second.fp64 && sh == 3 ? 6.0 : 1.0);   // six bf16 products per fp32 one
+        f += (double)kv.second.flops * (!kv.second.fp64 && sh == kSplitTile ? 6.0 : 1.0);   // six bf16 products per fp32 one
     }
     return f;
 }
@@ -692,11 +692,18 @@ void contract(Program &P, const KT &C, const std::string &cl, const KT &A, const
         make_split(by_stride(chains(Nl, tb, tc), kext <= 64 && !tb.hasR ? tc : tb), tb, tc, g.sn, g.Bn, g.Cn, g.N, what);
     }
     {
-        // K: make the unit-stride group innermost for whichever operand has one (A first)
+        // K: the unit-stride group innermost for whichever operand has one; where both do, for the one
+        // that the tiles read more of (a tile of the other then uses 16 bytes of each line it touches
+        // until its later steps; Nk=5, o=8, v=40, one complex128 vector: x_ie <- Z_ijab H_abej, 1 GB of H)
         auto kc = chains(Kl, tb, ta);
-        bool a_unit = false;
-        for (auto &c : kc) a_unit = a_unit || ta.stride[pos(ta, c.back())] == 1;
-        make_split(a_unit ? by_stride(kc, ta) : by_stride(kc, tb), ta, tb, g.sk, g.Ak, g.Bk, g.K, what);
+        bool a_unit = false, b_unit = false;
+        for (auto &c : kc) {
+            a_unit = a_unit || ta.stride[pos(ta, c.back())] == 1;
+            b_unit = b_unit || tb.stride[pos(tb, c.back())] == 1;
+        }
+        const double ra = (double)A.count() * ((g.N + 63) / 64), rb = (double)B.count() * ((g.M + 63) / 64);
+        const bool by_a = a_unit && (!b_unit || ra >= rb);
+        make_split(by_a ? by_stride(kc, ta) : by_stride(kc, tb), ta, tb, g.sk, g.Ak, g.Bk, g.K, what);
     }
     g.aMfast = (g.Am.s[2] == 1) || (g.Ak.s[2] != 1);
     g.bNfast = (g.Bn.s[2] == 1) || (g.Bk.s[2] != 1);

@@ -245,19 +245,8 @@ bool Program::make_grouped(size_t budget) {
             const i64 nj = (i64)go.offC.size(), ks = cdiv(std::max(g.K, 1), kGroupTK);
             for (i64 j = 0; j < nj; ++j)
                 p.steps = std::max<int>(p.steps, (int)std::min<i64>((go.segBeg[j + 1] - go.segBeg[j]) * ks, INT32_MAX));
-            // the tile with the least work, edges included; a step costs its fragments' matrix
-            // instructions and, once per step, about half a fragment's time for loads and the barrier
-            double best = 0;
-            for (int tl = 0; tl < 4; ++tl) {
-                const GroupTile &gt = kGroupTiles[tl];
-                const i64 nt = nj * cdiv(g.M, gt.m) * cdiv(g.N, gt.n);
-                const double w = (double)nt * (gt.frags + 0.5);
-                // 64x64 needs enough tiles to fill the 256 compute units by itself
-                if (tl && ((gt.frags > 1 && nt < 512) || w >= 0.9 * best)) continue;
-                best = w;
-                p.tile = tl;
-                p.tiles = nt;
-            }
+            p.tile = best_tile(g.M, g.N, nj, true);
+            p.tiles = nj * cdiv(g.M, kGroupTiles[p.tile].m) * cdiv(g.N, kGroupTiles[p.tile].n);
             if (kGroupTiles[p.tile].frags > 1 && p.tiles >= kAloneTiles) {
                 p.alone = true;
                 continue;
