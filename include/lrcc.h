@@ -210,9 +210,10 @@ lrcc_status lrcc_set_ladder_mode(lrcc_ctx *ctx, int mode);
 lrcc_status lrcc_set_autotune(lrcc_ctx *ctx, int enable);
 
 /* HIP-graph replay of the sigma (and transpose) applications: when enabled,
- * each application on a non-null stream is captured once per set of buffer
- * addresses and replayed as one graph launch (the solver uses a stream of its
- * own).  Profiling events are not recorded inside graphs.  Disabling frees the
+ * each application on a non-null stream that runs op by op is captured once per
+ * set of buffer addresses and replayed as one graph launch (the solver uses a
+ * stream of its own); programs that run grouped launch their few kernels directly,
+ * which is faster than a graph of as many nodes.  Profiling events are not recorded inside graphs.  Disabling frees the
  * captured graphs. */
 lrcc_status lrcc_set_graphs(lrcc_ctx *ctx, int enable);
 

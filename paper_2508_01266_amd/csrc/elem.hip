@@ -195,7 +195,15 @@ __global__ void k_pp_out(SlabList zs, const double2 *x2, double2 *y2, const doub
                 const i64 at = zr[rw] + e;
                 auto z = reinterpret_cast<const typename Cx<T>::type *>(zs.p[0])[at];
                 if constexpr (NS == 0) {
-                    for (int s = 1; s < zs.n; ++s) {
+                    int s = 1;
+                    for (; s + 4 <= zs.n; s += 4) {     // four loads in flight
+                        typename Cx<T>::type t[4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) t[u] = reinterpret_cast<const typename Cx<T>::type *>(zs.p[s + u])[at];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) { z.x += t[u].x; z.y += t[u].y; }
+                    }
+                    for (; s < zs.n; ++s) {
                         const auto t = reinterpret_cast<const typename Cx<T>::type *>(zs.p[s])[at];
                         z.x += t.x;
                         z.y += t.y;

@@ -84,19 +84,20 @@ __global__ void k_gemm_reduce(GemmArgs g) {
 }
 
 int gemm_shape(const GemmArgs &g, bool fp64) {
-    if (g.shape >= 0) return g.shape;
+    return g.shape >= 0 ? g.shape : best_tile(g.M, g.N, g.K, 1, fp64, false);
+}
+
+// The tile with the least work, edges included: a step costs its matrix instructions and, once per step,
+// about half a fragment's time for loads and the barrier; 64x64 first, which reads its operands half as
+// often, unless another saves a tenth.
+int best_tile(int M, int N, int K, i64 jobs, bool fp64, bool fill) {
     // complex64: the bf16 products need a reduction that fills most of a 32-deep step and tiles that are
     // not mostly edge (Nk=5, o=8, v=40, 48 right-hand sides: M=3072 N=1600 K=28 0.43 against 0.49 ms of
     // 64x64, M=122880 N=40 K=40 3.4 against 4.6, M=3072 N=28 K=1600 0.44 against 0.52; but
     // M=2560 N=1920 K=8 2.2 against 2.0, M=64 N=76800 K=64 1.17 against 1.13)
-    if (!fp64 && g.K >= 24 && g.M >= 96 && g.N >= 24) return kSplitTile;
-    return best_tile(g.M, g.N, 1, false);
-}
-
-// the tile with the least work, edges included: a step costs its fragments' matrix instructions and, once
-// per step, about half a fragment's time for loads and the barrier; 64x64, which reads its operands half
-// as often, unless another saves a tenth
-int best_tile(int M, int N, i64 jobs, bool fill) {
+    const GroupTile &sp = kGroupTiles[kSplitTile];
+    if (!fp64 && K >= 24 && M >= 96 && N >= 24 && !(fill && jobs * ((M + sp.m - 1) / sp.m) * ((N + sp.n - 1) / sp.n) < 256))
+        return kSplitTile;
     int tile = -1;
     double best = 0;
     for (int t : {1, 0, 2, 3}) {

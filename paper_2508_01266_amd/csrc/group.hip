@@ -38,9 +38,13 @@ __global__ void __launch_bounds__(kTileThreads, 2) gemm_group_kernel(const GemmA
 }
 
 template <typename T>
-hipError_t launch_gemm_group(int large, const GemmArgs *ops, const GroupItem *items, int n, hipStream_t s) {
+hipError_t launch_gemm_group(int cls, const GemmArgs *ops, const GroupItem *items, int n, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    if (large) hipLaunchKernelGGL((gemm_group_kernel<T, 1>), dim3(n), dim3(kTileThreads), 0, s, ops, items);
+    if (cls == 2) {
+        if constexpr (sizeof(T) == 4) return launch_split_group(ops, items, n, s);
+        return hipErrorInvalidValue;
+    }
+    if (cls == 1) hipLaunchKernelGGL((gemm_group_kernel<T, 1>), dim3(n), dim3(kTileThreads), 0, s, ops, items);
     else hipLaunchKernelGGL((gemm_group_kernel<T, 0>), dim3(n), dim3(kTileThreads), 0, s, ops, items);
     return hipGetLastError();
 }
@@ -60,7 +64,15 @@ __global__ void k_sums(const SumSeg *__restrict__ segs, const void *const *__res
         C2 a;
         a.x = 0;
         a.y = 0;
-        for (int q = 0; q < g.nsrc; ++q) {
+        int q = 0;
+        for (; q + 4 <= g.nsrc; q += 4) {       // four loads in flight
+            C2 v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = reinterpret_cast<const C2 *>(src[g.src0 + q + u])[e];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) { a.x += v[u].x; a.y += v[u].y; }
+        }
+        for (; q < g.nsrc; ++q) {
             const C2 v = reinterpret_cast<const C2 *>(src[g.src0 + q])[e];
             a.x += v.x;
             a.y += v.y;

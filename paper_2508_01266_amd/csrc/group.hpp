@@ -23,11 +23,14 @@ struct SumSeg {
 };
 
 constexpr int kGroupTK = 16;          // reduction elements per step of a grouped product
-struct GroupTile { int m, n, frags; };   // rows, columns, 16x16 fragments per wave
-constexpr GroupTile kGroupTiles[4] = {{32, 32, 1}, {64, 64, 4}, {16, 64, 1}, {64, 16, 1}};
-constexpr int kSplitTile = 4;            // 128x64 on the bf16 matrix cores, complex64 (split.hip)
-// index of the tile for M x N outputs of each of `jobs` blocks; fill: the launch has to fill the device
-int best_tile(int M, int N, i64 jobs, bool fill);
+// rows, columns, reduction elements per step, and a step's matrix instructions of one wave in units of
+// those of one 16x16x16 complex product on the matrix cores of its type
+struct GroupTile { int m, n, k, frags; };
+constexpr GroupTile kGroupTiles[5] = {{32, 32, 16, 1}, {64, 64, 16, 4}, {16, 64, 16, 1}, {64, 16, 16, 1}, {128, 64, 32, 8}};
+constexpr int kSplitTile = 4;            // on the bf16 matrix cores, complex64 (split.hip)
+// Index of the tile for M x N outputs of each of `jobs` blocks with reductions of K; fill: the launch has
+// to fill the device.
+int best_tile(int M, int N, int K, i64 jobs, bool fp64, bool fill);
 constexpr int kSumChunk = 1024;       // elements of a SumSeg per workgroup
 constexpr int kMaxSlabs = 16;         // arrays an output kernel can sum
 
@@ -43,9 +46,12 @@ inline SlabList one_slab(const void *p) {
     return s;
 }
 
-// items [0, n) of the device table; large: 64x64 tiles, else the tiles of one fragment per wave
+// items [0, n) of the device table, all of one launch class: 0 the tiles of one fragment per wave, 1 64x64,
+// 2 the bf16 tiles
+inline int tile_class(int tile) { return tile == kSplitTile ? 2 : tile == 1 ? 1 : 0; }
 template <typename T>
-hipError_t launch_gemm_group(int large, const GemmArgs *ops, const GroupItem *items, int n, hipStream_t s);
+hipError_t launch_gemm_group(int cls, const GemmArgs *ops, const GroupItem *items, int n, hipStream_t s);
+hipError_t launch_split_group(const GemmArgs *ops, const GroupItem *items, int n, hipStream_t s);
 // work: one (segment, first element / kSumChunk) pair per workgroup
 template <typename T>
 hipError_t launch_sums(const SumSeg *segs, const void *const *src, const int2 *work, int n, hipStream_t s);

@@ -1315,7 +1315,8 @@ hipError_t run_sigma(lrcc_ctx *c, Program *p, hipStream_t st) {
             tune_store(p->tune_key, choice);
         }
     }
-    if (c->use_graphs && st != nullptr) {
+    // a grouped program's dozen launches go out faster one by one than as a graph of as many nodes
+    if (c->use_graphs && st != nullptr && !p->runs_grouped()) {
         Program::GraphKey key{c->io_x1, c->io_x2, c->io_y1, c->io_y2, c->io_omega};
         return p->run_graph(st, key);
     }

@@ -105,6 +105,7 @@ struct Program {
     };
     std::vector<Launch> grouped;
     bool use_grouped = true;             // run the grouped form where there is one
+    bool runs_grouped() const { return use_grouped && !grouped.empty(); }
     // node of the op recorded last
     Node &node(Node::Kind k, std::vector<const void *> reads, void *write, i64 count, bool acc = false) {
         Node n;

@@ -230,24 +230,25 @@ bool Program::make_grouped(size_t budget) {
     for (const Other &p : outs) nlev = std::max(nlev, p.level + 1);
     // ---- tiles and splits, level by level
     auto launch_of = [&](const Prod &p) {
-        return std::make_pair(p.node < tags.size() ? tags[p.node] : (int)TAG_NONE, kGroupTiles[p.tile].frags > 1 ? 1 : 0);
+        return std::make_pair(p.node < tags.size() ? tags[p.node] : (int)TAG_NONE, tile_class(p.tile));
     };
     std::vector<std::vector<int>> at(nlev);
     for (size_t q = 0; q < prods.size(); ++q) at[prods[q].level].push_back((int)q);
     size_t extra_bytes = 0;
     for (int l = 0; l < nlev; ++l) {
-        // 16x16 fragments x reduction steps per wave of each launch: (tag, large tile)
+        // work per wave (GroupTile::frags) of each launch: (tag, launch class of the tile)
         std::map<std::pair<int, int>, double> units;
         for (int q : at[l]) {
             Prod &p = prods[q];
             const GemmOp &go = gemm_ops.at(p.node);
             const GemmArgs &g = *go.args;
-            const i64 nj = (i64)go.offC.size(), ks = cdiv(std::max(g.K, 1), kGroupTK);
+            const i64 nj = (i64)go.offC.size();
+            p.tile = best_tile(g.M, g.N, g.K, nj, sizeof(T) == 8, true);
+            const i64 ks = cdiv(std::max(g.K, 1), kGroupTiles[p.tile].k);
             for (i64 j = 0; j < nj; ++j)
                 p.steps = std::max<int>(p.steps, (int)std::min<i64>((go.segBeg[j + 1] - go.segBeg[j]) * ks, INT32_MAX));
-            p.tile = best_tile(g.M, g.N, nj, true);
             p.tiles = nj * cdiv(g.M, kGroupTiles[p.tile].m) * cdiv(g.N, kGroupTiles[p.tile].n);
-            if (kGroupTiles[p.tile].frags > 1 && p.tiles >= kAloneTiles) {
+            if (p.tiles * kGroupTiles[p.tile].m * kGroupTiles[p.tile].n >= kAloneTiles * 64 * 64 && tile_class(p.tile) > 0) {
                 p.alone = true;
                 continue;
             }
@@ -335,7 +336,7 @@ bool Program::make_grouped(size_t budget) {
     std::vector<SumSeg> segs;
     std::vector<const void *> srcs;
     std::vector<int2> work;
-    struct Range { int level, kind, large, tag, begin, end; };   // kind 0: products, 1: sums
+    struct Range { int level, kind, cls, tag, begin, end; };   // kind 0: products, 1: sums
     std::vector<Range> ranges;
     std::map<size_t, int> argidx;
     for (const Prod &p : prods) {
@@ -358,7 +359,7 @@ bool Program::make_grouped(size_t budget) {
                 const GemmOp &go = gemm_ops.at(p.node);
                 const GemmArgs &g = *go.args;
                 const int tm = kGroupTiles[p.tile].m, tn = kGroupTiles[p.tile].n;
-                const i64 ks = cdiv(std::max(g.K, 1), kGroupTK);
+                const i64 ks = cdiv(std::max(g.K, 1), kGroupTiles[p.tile].k);
                 for (size_t j = 0; j < go.offC.size(); ++j) {
                     const i64 nst = (i64)(go.segBeg[j + 1] - go.segBeg[j]) * (g.K > 0 ? ks : 0);
                     if (nst > INT32_MAX) return false;
@@ -444,10 +445,10 @@ bool Program::make_grouped(size_t budget) {
             if (r.level != l) continue;
             if (r.kind == 0) {
                 const GroupItem *it = ditems + r.begin;
-                const int n = r.end - r.begin, large = r.large;
-                grouped.push_back({[=](hipStream_t s) { return launch_gemm_group<T>(large, dargs, it, n, s); }, r.tag,
+                const int n = r.end - r.begin, cls = r.cls;
+                grouped.push_back({[=](hipStream_t s) { return launch_gemm_group<T>(cls, dargs, it, n, s); }, r.tag,
                                    "level " + std::to_string(l) + " products, " + std::to_string(n) +
-                                       (large ? " large tiles" : " small tiles")});
+                                       (cls == 2 ? " bf16 tiles" : cls ? " large tiles" : " small tiles")});
             } else {
                 const int2 *w = dwork + r.begin;
                 const int n = r.end - r.begin;

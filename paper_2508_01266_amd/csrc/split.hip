@@ -6,7 +6,7 @@
 // are below 2^-24 |a b|.  The matrix cores run bf16 16 times as fast as fp32, so six products leave a
 // factor of 2.7; a complex product takes 24 of them.  An infinite operand gives NaN (its remainder is
 // NaN), a finite one above the largest bf16 number, 3.39e38, too.
-#include "common.hpp"
+#include "group.hpp"
 
 namespace lrcc {
 
@@ -46,21 +46,22 @@ __device__ __forceinline__ void split8(const float *x, u4 &h, u4 &m, u4 &l) {
 // and under 256 registers: two workgroups per compute unit, so that one converts while the other
 // multiplies.  Operands are loaded one step ahead, eight elements of a row per thread.
 // RUN: every unit lies in one run of the reduction index (its innermost extent is a multiple of 8).
+// Steps [t0, t1) of the (segment, k) range that starts at segment sb, then the outputs as tile_product's.
+constexpr int STM = 128, STN = 64, STK = 32, SKG = STK / 8;
+// the k groups of a row start 8 banks apart
+constexpr int SSA = STM + 2, SSB = STN + 2;
+struct SplitLds { u4 a[6 * SKG * SSA], b[6 * SKG * SSB]; };
+
 template <bool RUN>
-__global__ void __launch_bounds__(NT, 2) gemm_split_kernel(GemmArgs g) {
-    constexpr int TM = 128, TN = 64, TK = 32, KG = TK / 8;
+__device__ __forceinline__ void split_tile(const GemmArgs &g, SplitLds &lds, int m0, int n0, int sb, int tbeg, int tend,
+                                           float js, int beta, void *Cblock, float2 *dense) {
+    constexpr int TM = STM, TN = STN, TK = STK, KG = SKG, SA = SSA, SB = SSB;
     constexpr int FM = 4, FN = 2, UA = TM * KG / NT, UB = TN * KG / NT;
-    // the k groups of a row start 8 banks apart
-    constexpr int SA = TM + 2, SB = TN + 2;
-    __shared__ u4 lA[6 * KG * SA], lB[6 * KG * SB];
-    const int job = blockIdx.y, split = blockIdx.z;
-    const int tilesM = (g.M + TM - 1) / TM;
-    const int m0 = (blockIdx.x % tilesM) * TM, n0 = (blockIdx.x / tilesM) * TN;
+    u4 *const lA = lds.a, *const lB = lds.b;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = (wave & 1) * 64, wn = (wave >> 1) * 32;
     const float2 *A = reinterpret_cast<const float2 *>(g.A);
     const float2 *B = reinterpret_cast<const float2 *>(g.B);
-    float2 *C = reinterpret_cast<float2 *>(g.C);
     const int ak0 = (int)g.Ak.s[0], ak1 = (int)g.Ak.s[1], ak2 = (int)g.Ak.s[2];
     const int bk0 = (int)g.Bk.s[0], bk1 = (int)g.Bk.s[1], bk2 = (int)g.Bk.s[2];
     int arow[UA], akg[UA], am[UA], bcol[UB], bkg[UB], bn[UB];
@@ -87,10 +88,7 @@ __global__ void __launch_bounds__(NT, 2) gemm_split_kernel(GemmArgs g) {
 #pragma unroll
         for (int j = 0; j < FN; ++j) { accr[i][j] = v4{0, 0, 0, 0}; acci[i][j] = v4{0, 0, 0, 0}; }
 
-    const int sb = g.segBeg[job], se = g.segBeg[job + 1];
     const int ksteps = (g.K + TK - 1) / TK;
-    const i64 nsteps = (i64)(se - sb) * ksteps;
-    const int tbeg = (int)(nsteps * split / g.ksplit), tend = (int)(nsteps * (split + 1) / g.ksplit);
     float2 va[UA][8], vb[UB][8];
     auto unit = [&](const float2 *P, int row, bool ok, int k, int s0, int s1, int s2, float2 *v) {
         if (RUN) {
@@ -117,10 +115,12 @@ __global__ void __launch_bounds__(NT, 2) gemm_split_kernel(GemmArgs g) {
                 v[i] = ok && k + i < g.K ? P[row + split_off32<true>(k + i, g.sk, s0, s1, s2)] : make_float2(0, 0);
         }
     };
-    auto fetch = [&](int t) {
-        const int s = sb + t / ksteps, k0 = (t % ksteps) * TK;
-        const float2 *As = A + g.segA[s];
-        const float2 *Bs = B + g.segB[s];
+    int ps = sb + tbeg / (ksteps > 0 ? ksteps : 1), pk = tbeg % (ksteps > 0 ? ksteps : 1);   // next step to load
+    auto fetch = [&]() {
+        const int k0 = pk * TK;
+        const float2 *As = A + g.segA[ps];
+        const float2 *Bs = B + g.segB[ps];
+        if (++pk == ksteps) { pk = 0; ++ps; }
 #pragma unroll
         for (int q = 0; q < UA; ++q) unit(As, arow[q], aok[q], k0 + 8 * akg[q], ak0, ak1, ak2, va[q]);
 #pragma unroll
@@ -138,14 +138,14 @@ __global__ void __launch_bounds__(NT, 2) gemm_split_kernel(GemmArgs g) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) l[(3 + c) * KG * stride + at] = p[c];
     };
-    if (tbeg < tend) fetch(tbeg);
+    if (tbeg < tend) fetch();
     for (int t = tbeg; t < tend; ++t) {
 #pragma unroll
         for (int q = 0; q < UA; ++q) put(va[q], lA, SA, akg[q] * SA + am[q]);
 #pragma unroll
         for (int q = 0; q < UB; ++q) put(vb[q], lB, SB, bkg[q] * SB + bn[q]);
         __syncthreads();
-        if (t + 1 < tend) fetch(t + 1);
+        if (t + 1 < tend) fetch();
         const int kg = lane >> 4, c = lane & 15;
         bf8 b[FN][6];
 #pragma unroll
@@ -197,9 +197,7 @@ __global__ void __launch_bounds__(NT, 2) gemm_split_kernel(GemmArgs g) {
         }
         __syncthreads();
     }
-    if (g.ksplit > 1) {
-        // raw partial sums, reduced by a second kernel
-        float2 *Pj = reinterpret_cast<float2 *>(g.part) + ((i64)split * g.njobs_all + g.job0 + job) * g.M * g.N;
+    if (dense) {
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -208,13 +206,12 @@ __global__ void __launch_bounds__(NT, 2) gemm_split_kernel(GemmArgs g) {
                 for (int r = 0; r < 4; ++r) {
                     const int gm = m0 + wm + 16 * i + 4 * (lane >> 4) + r;
                     const int gn = n0 + wn + 16 * j + (lane & 15);
-                    if (gm < g.M && gn < g.N) Pj[(i64)gm * g.N + gn] = make_float2(accr[i][j][r], acci[i][j][r]);
+                    if (gm < g.M && gn < g.N) dense[(i64)gm * g.N + gn] = make_float2(accr[i][j][r], acci[i][j][r]);
                 }
         return;
     }
-    const float js = g.jscale ? g.jscale[g.job0 + job] : 1.0f;
     const float alr = js * (float)g.alpha_re, ali = js * (float)g.alpha_im;
-    float2 *Cj = C + g.offC[job];
+    float2 *Cj = reinterpret_cast<float2 *>(Cblock);
     i64 coff[FN];
     bool cok[FN];
 #pragma unroll
@@ -234,7 +231,7 @@ __global__ void __launch_bounds__(NT, 2) gemm_split_kernel(GemmArgs g) {
             roff[r] = rok[r] ? split_off(gm, g.sm, g.Cm) : 0;
         }
         float2 old[FN][4];
-        if (g.beta) {
+        if (beta) {
             // all reads before the first write; (0, 0) of the block stands in for outside elements
 #pragma unroll
             for (int j = 0; j < FN; ++j)
@@ -248,15 +245,47 @@ __global__ void __launch_bounds__(NT, 2) gemm_split_kernel(GemmArgs g) {
                 if (!(rok[r] && cok[j])) continue;
                 const float xr = accr[i][j][r], xi = acci[i][j][r];
                 float2 w = make_float2(alr * xr - ali * xi, alr * xi + ali * xr);
-                if (g.beta) { w.x += old[j][r].x; w.y += old[j][r].y; }
+                if (beta) { w.x += old[j][r].x; w.y += old[j][r].y; }
                 Cj[roff[r] + coff[j]] = w;
             }
     }
 }
 
+template <bool RUN>
+__global__ void __launch_bounds__(NT, 2) gemm_split_kernel(GemmArgs g) {
+    __shared__ SplitLds lds;
+    const int job = blockIdx.y, split = blockIdx.z;
+    const int tilesM = (g.M + STM - 1) / STM;
+    const int sb = g.segBeg[job], se = g.segBeg[job + 1];
+    const i64 nsteps = (i64)(se - sb) * ((g.K + STK - 1) / STK);
+    const int tbeg = (int)(nsteps * split / g.ksplit), tend = (int)(nsteps * (split + 1) / g.ksplit);
+    float2 *dense = g.ksplit > 1 ? reinterpret_cast<float2 *>(g.part) +
+                                       ((i64)split * g.njobs_all + g.job0 + job) * g.M * g.N : nullptr;
+    split_tile<RUN>(g, lds, (blockIdx.x % tilesM) * STM, (blockIdx.x / tilesM) * STN, sb, tbeg, tend,
+                    g.jscale ? g.jscale[g.job0 + job] : 1.0f, g.beta, reinterpret_cast<float2 *>(g.C) + g.offC[job], dense);
+}
+
+__device__ __host__ inline bool split_run(const GemmArgs &g) { return !g.sk.tri && g.sk.d2 % 8 == 0; }
+
+// the same tiles over a table of work items (GroupItem)
+__global__ void __launch_bounds__(NT, 2) gemm_split_group_kernel(const GemmArgs *__restrict__ ops,
+                                                                 const GroupItem *__restrict__ items) {
+    __shared__ SplitLds lds;
+    const GroupItem it = items[blockIdx.x];
+    const GemmArgs &g = ops[it.op];
+    if (split_run(g)) split_tile<true>(g, lds, it.m0, it.n0, it.sb, it.t0, it.t1, it.js, it.beta, it.C, nullptr);
+    else split_tile<false>(g, lds, it.m0, it.n0, it.sb, it.t0, it.t1, it.js, it.beta, it.C, nullptr);
+}
+
+hipError_t launch_split_group(const GemmArgs *ops, const GroupItem *items, int n, hipStream_t s) {
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(gemm_split_group_kernel, dim3(n), dim3(NT), 0, s, ops, items);
+    return hipGetLastError();
+}
+
 hipError_t launch_gemm_split(const GemmArgs &g, hipStream_t s) {
-    const int tilesM = (g.M + 127) / 128, tilesN = (g.N + 63) / 64;
-    const bool run = !g.sk.tri && g.sk.d2 % 8 == 0;
+    const int tilesM = (g.M + STM - 1) / STM, tilesN = (g.N + STN - 1) / STN;
+    const bool run = split_run(g);
     // grid.y is limited to 65535: launch the job list in chunks
     for (int j0 = 0; j0 < g.njobs; j0 += 65535) {
         GemmArgs c = g;
