@@ -112,6 +112,75 @@ hipError_t tau_like(const void *x1, const void *x2, const void *t1, void *out, K
     return hipGetLastError();
 }
 
+// Inputs of the forward product in one pass over x2: x1 and x2 from the caller's layout into the blocks'
+// (doubles scaled by `scale`), and dtau = x2 + x_ia t_jb + t_ia x_jb - x_ib t_ja - t_ib x_ja.  Bound by HBM;
+// as three kernels x2 was read twice and the smallest programs waited on three launches (batched complex64
+// input, Nk=5, o=8, v=40, 48 right-hand sides: 2.9 + 2.1 ms before, 3.7 ms now).
+template <typename T>
+__global__ void k_inputs(const double2 *x1, const double2 *x2, const typename Cx<T>::type *t1,
+                         typename Cx<T>::type *o1, typename Cx<T>::type *o2, typename Cx<T>::type *dtau, KMesh km,
+                         int R, int o, int v, double scale, i64 rows, unsigned b1) {
+    const int nk = km.size(), vv = v * v;
+    if (blockIdx.x < b1) {      // singles
+        const i64 E = (i64)o * v, n = (i64)R * nk * E;
+        for (i64 t = blockIdx.x * (i64)blockDim.x + threadIdx.x; t < n; t += (i64)b1 * blockDim.x) {
+            const i64 e = t % E;
+            const int k = (int)((t / E) % nk), r = (int)(t / (E * nk));
+            const double2 x = x1[t];
+            o1[((i64)k * R + r) * E + e] = mk<T>((T)x.x, (T)x.y);
+        }
+        return;
+    }
+    const i64 B = (i64)nk * nk * nk;
+    for (i64 row = blockIdx.x - b1; row < rows; row += gridDim.x - b1) {
+        // row = (((ki nk + kj) nk + ka) R + r) o + i) o + j of the block layout, elements (a, b)
+        i64 q = row;
+        const int j = (int)(q % o); q /= o;
+        const int i = (int)(q % o); q /= o;
+        const int r = (int)(q % R);
+        const i64 blk = q / R;
+        const int ka = (int)(blk % nk), kj = (int)((blk / nk) % nk), ki = (int)(blk / (nk * nk));
+        const int kb = km.comb(ki, kj, ka);
+        auto X = [&](int k, int ii, int aa) {
+            const double2 x = x1[(((i64)r * nk + k) * o + ii) * v + aa];
+            return mk<T>((T)x.x, (T)x.y);
+        };
+        auto Tt = [&](int k, int ii, int aa) { return t1[((i64)k * o + ii) * v + aa]; };
+        const double2 *src = x2 + ((((i64)r * B + blk) * o + i) * o + j) * vv;
+        typename Cx<T>::type *d2 = o2 + row * vv, *dt = dtau + row * vv;
+        for (int e = threadIdx.x; e < vv; e += blockDim.x) {
+            const double2 in = src[e];
+            const auto x = mk<T>((T)(scale * in.x), (T)(scale * in.y));
+            d2[e] = x;
+            const int a = e / v, b = e - a * v;
+            T sr = 0, si = 0;
+            if (ka == ki) {     // x_ia t_jb + t_ia x_jb  (kb == kj)
+                auto p = X(ki, i, a), q2 = Tt(kj, j, b), u = Tt(ki, i, a), w = X(kj, j, b);
+                sr += p.x * q2.x - p.y * q2.y + u.x * w.x - u.y * w.y;
+                si += p.x * q2.y + p.y * q2.x + u.x * w.y + u.y * w.x;
+            }
+            if (kb == ki) {     // - x_ib t_ja - t_ib x_ja  (ka == kj)
+                auto p = X(ki, i, b), q2 = Tt(kj, j, a), u = Tt(ki, i, b), w = X(kj, j, a);
+                sr -= p.x * q2.x - p.y * q2.y + u.x * w.x - u.y * w.y;
+                si -= p.x * q2.y + p.y * q2.x + u.x * w.y + u.y * w.x;
+            }
+            dt[e] = mk<T>(x.x + sr, x.y + si);
+        }
+    }
+}
+
+template <typename T>
+hipError_t inputs(const void *x1, const void *x2, const void *t1, void *o1, void *o2, void *dtau, KMesh km, int R,
+                  int o, int v, double scale, hipStream_t s) {
+    const int nk = km.size();
+    const i64 rows = (i64)nk * nk * nk * R * o * o;
+    const unsigned b1 = (unsigned)std::min<i64>(((i64)R * nk * o * v + 255) / 256, 1024);
+    hipLaunchKernelGGL(k_inputs<T>, dim3(b1 + rows_grid(rows)), dim3(256), 0, s, (const double2 *)x1,
+                       (const double2 *)x2, (const typename Cx<T>::type *)t1, (typename Cx<T>::type *)o1,
+                       (typename Cx<T>::type *)o2, (typename Cx<T>::type *)dtau, km, R, o, v, scale, rows, b1);
+    return hipGetLastError();
+}
+
 // One orbit of the antisymmetriser P(ij)P(ab): the four rows 0: (ki,kj,ka,i,j), 1: (kj,ki,ka,j,i),
 // 2: (ki,kj,kb,i,j), 3: (kj,ki,kb,j,i) of an array read by ld(row, e) become A, -A, -A^T and A^T with
 // A = row0 - row1 - (row2 - row3)^T (transposes in (a, b)), handed to st(row, e, value).  The workgroup
@@ -160,17 +229,66 @@ __device__ __forceinline__ void orbit_rows(OrbitLds &lds, int v, bool two_pairs,
         }
 }
 
-// y2[r][ki,kj,ka][i][j][a][b] = scale * (P_ij P_ab Z)[ki,kj,ka][r][i][j][a][b] - omega_r * x2[r][...],
-// Z the sum of zs.n arrays (NS of them, or any number for NS = 0).  The workgroup of an orbit's first
+// value at `at` of the sum of l.n arrays (NS of them, or any number for NS = 0), summed in double
+template <typename T, int NS>
+__device__ __forceinline__ double2 slab_sum(const SlabList &l, i64 at) {
+    typedef typename Cx<T>::type C2;
+    const C2 z0 = reinterpret_cast<const C2 *>(l.p[0])[at];
+    double2 z = make_double2((double)z0.x, (double)z0.y);
+    if constexpr (NS == 0) {
+        int s = 1;
+        for (; s + 4 <= l.n; s += 4) {     // four loads in flight
+            C2 t[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) t[u] = reinterpret_cast<const C2 *>(l.p[s + u])[at];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) { z.x += (double)t[u].x; z.y += (double)t[u].y; }
+        }
+        for (; s < l.n; ++s) {
+            const C2 t = reinterpret_cast<const C2 *>(l.p[s])[at];
+            z.x += (double)t.x;
+            z.y += (double)t.y;
+        }
+    } else {
+#pragma unroll
+        for (int s = 1; s < NS; ++s) {
+            const C2 t = reinterpret_cast<const C2 *>(l.p[s])[at];
+            z.x += (double)t.x;
+            z.y += (double)t.y;
+        }
+    }
+    return z;
+}
+
+// Outputs of a product in the caller's layout, one launch:
+//   y1[r][k][i][a] = s1[k][r][i][a] - omega_r x1[r][k][i][a];
+//   y2[r][ki,kj,ka][i][j][a][b] = scale * (P_ij P_ab Z)[ki,kj,ka][r][i][j][a][b] - omega_r * x2[r][...],
+// s1 and Z sums of arrays (NS of them in Z, or any number for NS = 0).  The workgroup of an orbit's first
 // row ((ki, i) <= (kj, j), ka <= kb) writes all of its distinct rows; the others return at once.
 template <typename T, int NS>
-__global__ void k_pp_out(SlabList zs, const double2 *x2, double2 *y2, const double *omega, KMesh km, int R, int o,
-                         int v, double scale) {
+__global__ void k_outputs(SlabList s1, SlabList zs, const double2 *x1, const double2 *x2, double2 *y1, double2 *y2,
+                          const double *omega, KMesh km, int R, int o, int v, double scale, unsigned b1) {
     __shared__ OrbitLds lds;
     const int nk = km.size(), vv = v * v;
+    if (blockIdx.x < b1) {      // singles
+        const i64 E = (i64)o * v, n = (i64)R * nk * E;
+        for (i64 t = blockIdx.x * (i64)blockDim.x + threadIdx.x; t < n; t += (i64)b1 * blockDim.x) {
+            const i64 e = t % E;
+            const int k = (int)((t / E) % nk), r = (int)(t / (E * nk));
+            double2 out = slab_sum<T, 0>(s1, ((i64)k * R + r) * E + e);
+            if (omega) {
+                const double w = omega[r];
+                const double2 xv = x1[t];
+                out.x -= w * xv.x;
+                out.y -= w * xv.y;
+            }
+            y1[t] = out;
+        }
+        return;
+    }
     const i64 B = (i64)nk * nk * nk;
     const i64 rows = B * R * o * o;
-    for (i64 row = blockIdx.x; row < rows; row += gridDim.x) {
+    for (i64 row = blockIdx.x - b1; row < rows; row += gridDim.x - b1) {
         // row indexes the caller layout [r][blk][i][j], elements (a, b)
         i64 q = row;
         const int j = (int)(q % o); q /= o;
@@ -190,102 +308,39 @@ __global__ void k_pp_out(SlabList zs, const double2 *x2, double2 *y2, const doub
         const i64 zr[4] = {zrow(ki, kj, ka, i, j), zrow(kj, ki, ka, j, i), zrow(ki, kj, kb, i, j), zrow(kj, ki, kb, j, i)};
         const i64 yr[4] = {row * vv, yrow(kj, ki, ka, j, i), yrow(ki, kj, kb, i, j), yrow(kj, ki, kb, j, i)};
         const double w = omega ? omega[r] : 0.0;
-        orbit_rows(lds, v, pi != pj, ka != kb,
-            [&](int rw, int e) {
-                const i64 at = zr[rw] + e;
-                auto z = reinterpret_cast<const typename Cx<T>::type *>(zs.p[0])[at];
-                if constexpr (NS == 0) {
-                    int s = 1;
-                    for (; s + 4 <= zs.n; s += 4) {     // four loads in flight
-                        typename Cx<T>::type t[4];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) t[u] = reinterpret_cast<const typename Cx<T>::type *>(zs.p[s + u])[at];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) { z.x += t[u].x; z.y += t[u].y; }
-                    }
-                    for (; s < zs.n; ++s) {
-                        const auto t = reinterpret_cast<const typename Cx<T>::type *>(zs.p[s])[at];
-                        z.x += t.x;
-                        z.y += t.y;
-                    }
-                } else {
-#pragma unroll
-                    for (int s = 1; s < NS; ++s) {
-                        const auto t = reinterpret_cast<const typename Cx<T>::type *>(zs.p[s])[at];
-                        z.x += t.x;
-                        z.y += t.y;
-                    }
-                }
-                return make_double2((double)z.x, (double)z.y);
-            },
-            [&](int rw, int e, double2 z) {
-                const i64 at = yr[rw] + e;
-                double2 out = make_double2(scale * z.x, scale * z.y);
-                if (omega) {
-                    const double2 xv = x2[at];
-                    out.x -= w * xv.x;
-                    out.y -= w * xv.y;
-                }
-                y2[at] = out;
-            });
+        orbit_rows(lds, v, pi != pj, ka != kb, [&](int rw, int e) { return slab_sum<T, NS>(zs, zr[rw] + e); },
+                   [&](int rw, int e, double2 z) {
+                       const i64 at = yr[rw] + e;
+                       double2 out = make_double2(scale * z.x, scale * z.y);
+                       if (omega) {
+                           const double2 xv = x2[at];
+                           out.x -= w * xv.x;
+                           out.y -= w * xv.y;
+                       }
+                       y2[at] = out;
+                   });
     }
 }
 
 template <typename T>
-hipError_t pp_out(const SlabList &Z, const void *x2, void *y2, const double *omega, KMesh km, int R, int o, int v,
-                  double scale, hipStream_t s) {
+hipError_t outputs(const SlabList &s1, const SlabList &Z, const void *x1, const void *x2, void *y1, void *y2,
+                   const double *omega, KMesh km, int R, int o, int v, double scale, hipStream_t s) {
     const int nk = km.size();
     const i64 rows = (i64)nk * nk * nk * R * o * o;
+    const unsigned b1 = (unsigned)std::min<i64>(((i64)R * nk * o * v + 255) / 256, 1024);
     auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(rows_grid(rows)), dim3(256), 0, s, Z, (const double2 *)x2, (double2 *)y2, omega,
-                           km, R, o, v, scale);
+        hipLaunchKernelGGL(kernel, dim3(b1 + rows_grid(rows)), dim3(256), 0, s, s1, Z, (const double2 *)x1,
+                           (const double2 *)x2, (double2 *)y1, (double2 *)y2, omega, km, R, o, v, scale, b1);
     };
     switch (Z.n) {
-    case 1: go(k_pp_out<T, 1>); break;
-    case 2: go(k_pp_out<T, 2>); break;
-    case 3: go(k_pp_out<T, 3>); break;
-    case 4: go(k_pp_out<T, 4>); break;
-    case 5: go(k_pp_out<T, 5>); break;
-    case 6: go(k_pp_out<T, 6>); break;
-    default: go(k_pp_out<T, 0>); break;
+    case 1: go(k_outputs<T, 1>); break;
+    case 2: go(k_outputs<T, 2>); break;
+    case 3: go(k_outputs<T, 3>); break;
+    case 4: go(k_outputs<T, 4>); break;
+    case 5: go(k_outputs<T, 5>); break;
+    case 6: go(k_outputs<T, 6>); break;
+    default: go(k_outputs<T, 0>); break;
     }
-    return hipGetLastError();
-}
-
-// y1[r][k][i][a] = s1[k][r][i][a] - omega_r x1[r][k][i][a], s1 the sum of s1.n arrays
-template <typename T>
-__global__ void k_s1_out(SlabList s1, const double2 *x1, double2 *y1, const double *omega,
-                         int nk, int R, int o, int v) {
-    const i64 E = (i64)o * v;
-    const i64 n = (i64)R * nk * E;
-    for (i64 t = blockIdx.x * (i64)blockDim.x + threadIdx.x; t < n; t += (i64)gridDim.x * blockDim.x) {
-        const i64 e = t % E;
-        const int k = (int)((t / E) % nk);
-        const int r = (int)(t / (E * nk));
-        const i64 at = ((i64)k * R + r) * E + e;
-        auto sv = reinterpret_cast<const typename Cx<T>::type *>(s1.p[0])[at];
-        for (int q = 1; q < s1.n; ++q) {
-            const auto w = reinterpret_cast<const typename Cx<T>::type *>(s1.p[q])[at];
-            sv.x += w.x;
-            sv.y += w.y;
-        }
-        double2 out;
-        out.x = (double)sv.x;
-        out.y = (double)sv.y;
-        if (omega) {
-            const double w = omega[r];
-            const double2 xv = x1[t];
-            out.x -= w * xv.x;
-            out.y -= w * xv.y;
-        }
-        y1[t] = out;
-    }
-}
-
-template <typename T>
-hipError_t s1_out(const SlabList &s1, const void *x1, void *y1, const double *omega, int nk, int R, int o, int v,
-                  hipStream_t s) {
-    hipLaunchKernelGGL(k_s1_out<T>, dim3(grid_for((i64)R * nk * o * v)), dim3(256), 0, s, s1, (const double2 *)x1, (double2 *)y1, omega, nk, R, o, v);
     return hipGetLastError();
 }
 
@@ -678,10 +733,10 @@ hipError_t outer_oovv(void *g, const void *x, const void *y, double c, int nk, i
     template hipError_t pair_transpose<T>(const void *, void *, int, int, int, hipStream_t);                                                                                              \
     template hipError_t tau_like<T>(const void *, const void *, const void *, void *, KMesh, int, int, int,  \
                                     double, int, hipStream_t);                                               \
-    template hipError_t pp_out<T>(const SlabList &, const void *, void *, const double *, KMesh, int, int, int,  \
-                                  double, hipStream_t);                                                      \
-    template hipError_t s1_out<T>(const SlabList &, const void *, void *, const double *, int, int, int, int,    \
-                                  hipStream_t);                                                              \
+    template hipError_t inputs<T>(const void *, const void *, const void *, void *, void *, void *, KMesh, int, \
+                                  int, int, double, hipStream_t);                                            \
+    template hipError_t outputs<T>(const SlabList &, const SlabList &, const void *, const void *, void *,   \
+                                   void *, const double *, KMesh, int, int, int, double, hipStream_t);       \
     template hipError_t chol_slice<T>(const void *, void *, int, int, int, int, int, int, int, double, int,  \
                                       hipStream_t);                                                          \
     template hipError_t one_body_slice<T>(const void *, void *, int, int, int, int, int, int, hipStream_t);  \

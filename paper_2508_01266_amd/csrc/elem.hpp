@@ -9,12 +9,14 @@ hipError_t rhs_to_block(const void *in, void *out, int R, i64 B, i64 E, double s
 template <typename T>
 hipError_t tau_like(const void *x1, const void *x2, const void *t1, void *out, KMesh km, int R, int o, int v,
                     double c, int x1_has_rhs, hipStream_t s);
+// x1, x2 (caller layout) -> o1, o2 (blocks, doubles scaled) and dtau (tau_like of them with t1)
 template <typename T>
-hipError_t pp_out(const SlabList &Z, const void *x2, void *y2, const double *omega, KMesh km, int R, int o, int v,
-                  double scale, hipStream_t s);
+hipError_t inputs(const void *x1, const void *x2, const void *t1, void *o1, void *o2, void *dtau, KMesh km, int R,
+                  int o, int v, double scale, hipStream_t s);
+// y1 = s1 - omega x1, y2 = scale P(ij)P(ab) Z - omega x2 (caller layout; omega may be null)
 template <typename T>
-hipError_t s1_out(const SlabList &s1, const void *x1, void *y1, const double *omega, int nk, int R, int o, int v,
-                  hipStream_t s);
+hipError_t outputs(const SlabList &s1, const SlabList &Z, const void *x1, const void *x2, void *y1, void *y2,
+                   const double *omega, KMesh km, int R, int o, int v, double scale, hipStream_t s);
 template <typename Tout>
 hipError_t chol_slice(const void *L, void *out, int nk, int naux, int n, int p0, int np, int q0, int nq,
                       double scale, int conj_pair, hipStream_t s);

@@ -61,23 +61,24 @@ __global__ void k_sums(const SumSeg *__restrict__ segs, const void *const *__res
     const i64 e1 = e0 + kSumChunk < g.n ? e0 + kSumChunk : g.n;
     C2 *dst = reinterpret_cast<C2 *>(g.dst);
     for (i64 e = e0 + threadIdx.x; e < e1; e += blockDim.x) {
-        C2 a;
-        a.x = 0;
-        a.y = 0;
+        double2 a = make_double2(0, 0);          // summed in double, rounded once
         int q = 0;
         for (; q + 4 <= g.nsrc; q += 4) {       // four loads in flight
             C2 v[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) v[u] = reinterpret_cast<const C2 *>(src[g.src0 + q + u])[e];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) { a.x += v[u].x; a.y += v[u].y; }
+            for (int u = 0; u < 4; ++u) { a.x += (double)v[u].x; a.y += (double)v[u].y; }
         }
         for (; q < g.nsrc; ++q) {
             const C2 v = reinterpret_cast<const C2 *>(src[g.src0 + q])[e];
-            a.x += v.x;
-            a.y += v.y;
+            a.x += (double)v.x;
+            a.y += (double)v.y;
         }
-        dst[e] = a;
+        C2 w2;
+        w2.x = (T)a.x;
+        w2.y = (T)a.y;
+        dst[e] = w2;
     }
 }
 

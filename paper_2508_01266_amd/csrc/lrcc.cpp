@@ -1017,19 +1017,14 @@ void ladder_block_gemms(lrcc_ctx *c, Program &P, bool transpose, const void *A, 
 // Output steps of a product: y1 = s1 - omega x1, y2 = scale P(ij)P(ab) Z - omega x2 (caller layouts).
 template <typename T>
 void emit_outputs(lrcc_ctx *c, Program &P, const KT &s1, const KT &Z, int R, double scale) {
-    const int nk = c->nk, o = c->no, v = c->nv;
+    const int o = c->no, v = c->nv;
     const void *sp = s1.p, *zp = Z.p;
     P.ops.push_back([=](hipStream_t s) {
-        return s1_out<T>(one_slab(sp), c->io_x1, c->io_y1, c->io_omega, nk, R, o, v, s);
+        return outputs<T>(one_slab(sp), one_slab(zp), c->io_x1, c->io_x2, c->io_y1, c->io_y2, c->io_omega, c->km, R, o,
+                          v, scale, s);
     });
-    P.node(Node::OUT, {sp}, nullptr, s1.count()).from = [=](hipStream_t s, const SlabList &l) {
-        return s1_out<T>(l, c->io_x1, c->io_y1, c->io_omega, nk, R, o, v, s);
-    };
-    P.ops.push_back([=](hipStream_t s) {
-        return pp_out<T>(one_slab(zp), c->io_x2, c->io_y2, c->io_omega, c->km, R, o, v, scale, s);
-    });
-    P.node(Node::OUT, {zp}, nullptr, Z.count()).from = [=](hipStream_t s, const SlabList &l) {
-        return pp_out<T>(l, c->io_x2, c->io_y2, c->io_omega, c->km, R, o, v, scale, s);
+    P.node(Node::OUT, {sp, zp}, nullptr, Z.count()).from = [=](hipStream_t s, const std::vector<SlabList> &l) {
+        return outputs<T>(l[0], l[1], c->io_x1, c->io_x2, c->io_y1, c->io_y2, c->io_omega, c->km, R, o, v, scale, s);
     };
 }
 
@@ -1041,16 +1036,32 @@ Program *build_sigma(lrcc_ctx *c, State<T> &S, int R, DevMem &wm, bool full = tr
     const i64 nb3 = (i64)nk * nk * nk;
     KT x1 = G.x1, x2 = G.x2, Z = G.Z, s1 = G.s1;
     // caller layout -> internal (paper -> crystal normalisation for doubles)
-    P->ops.push_back([=](hipStream_t s) { return rhs_to_block<double, T>(c->io_x1, x1.p, R, nk, (i64)o * v, 1.0, s); });
-    P->node(Node::WRITE, {}, x1.p, x1.count()).write_to = [=](hipStream_t s, void *d, bool) {
-        return rhs_to_block<double, T>(c->io_x1, d, R, nk, (i64)o * v, 1.0, s);
-    };
-    P->ops.push_back([=](hipStream_t s) {
-        return rhs_to_block<double, T>(c->io_x2, x2.p, R, nb3, (i64)o * o * v * v, 1.0 / nk, s);
-    });
-    P->node(Node::WRITE, {}, x2.p, x2.count()).write_to = [=](hipStream_t s, void *d, bool) {
-        return rhs_to_block<double, T>(c->io_x2, d, R, nb3, (i64)o * o * v * v, 1.0 / nk, s);
-    };
+    // (with dtau where the program has it: the first op of the list, formed from both)
+    const bool taus = !G.ops.empty() && G.ops[0].kind == SymOp::TAU;
+    if (taus) {
+        const void *t1p = S.t1.p;
+        void *dt = G.ops[0].C.p;
+        const KMesh km = c->km;
+        P->ops.push_back([=](hipStream_t s) {
+            return inputs<T>(c->io_x1, c->io_x2, t1p, x1.p, x2.p, dt, km, R, o, v, 1.0 / nk, s);
+        });
+        Node &nd = P->node(Node::WRITE, {}, x2.p, x2.count());
+        nd.also = {{x1.p, x1.count()}, {dt, G.ops[0].C.count()}};
+        nd.write_to = [=](hipStream_t s, void *, bool) {
+            return inputs<T>(c->io_x1, c->io_x2, t1p, x1.p, x2.p, dt, km, R, o, v, 1.0 / nk, s);
+        };
+    } else {
+        P->ops.push_back([=](hipStream_t s) { return rhs_to_block<double, T>(c->io_x1, x1.p, R, nk, (i64)o * v, 1.0, s); });
+        P->node(Node::WRITE, {}, x1.p, x1.count()).write_to = [=](hipStream_t s, void *d, bool) {
+            return rhs_to_block<double, T>(c->io_x1, d, R, nk, (i64)o * v, 1.0, s);
+        };
+        P->ops.push_back([=](hipStream_t s) {
+            return rhs_to_block<double, T>(c->io_x2, x2.p, R, nb3, (i64)o * o * v * v, 1.0 / nk, s);
+        });
+        P->node(Node::WRITE, {}, x2.p, x2.count()).write_to = [=](hipStream_t s, void *d, bool) {
+            return rhs_to_block<double, T>(c->io_x2, d, R, nb3, (i64)o * o * v * v, 1.0 / nk, s);
+        };
+    }
     for (const SymOp &op : G.ops) {
         switch (op.kind) {
         case SymOp::CON:
@@ -1060,15 +1071,8 @@ Program *build_sigma(lrcc_ctx *c, State<T> &S, int R, DevMem &wm, bool full = tr
         case SymOp::COPY:
             kt_copy<T>(*P, op.C, op.A);
             break;
-        case SymOp::TAU: {
-            void *t1p = S.t1.p, *xa = op.A.p, *xb = op.B.p, *out = op.C.p;
-            const KMesh km = c->km;
-            P->ops.push_back([=](hipStream_t s) { return tau_like<T>(xa, xb, t1p, out, km, R, o, v, 1.0, 1, s); });
-            P->node(Node::WRITE, {xa, xb}, out, op.C.count()).write_to = [=](hipStream_t s, void *d, bool) {
-                return tau_like<T>(xa, xb, t1p, d, km, R, o, v, 1.0, 1, s);
-            };
+        case SymOp::TAU:        // formed with the inputs
             break;
-        }
         case SymOp::LADDER: {
             const bool by_class = ladder_path(c, S.Wst, 2 * sizeof(T)) == 3 && S.La && S.Lb;
             P->ladder_path = S.Wst ? 2 : by_class ? 3 : 1;
@@ -1937,9 +1941,11 @@ void ensure_alpha_programs(lrcc_ctx *c) {
         contract<double>(*P, Z, "Rijab", t2, "ijac", Fx, "Rbc", 0.5, false);
         contract<double>(*P, Z, "Rijab", t2, "ikab", Gx, "Rkj", -0.5);
         void *xi1 = c->xi1, *xi2 = c->xi2;
-        P->ops.push_back([=](hipStream_t s) { return s1_out<double>(one_slab(s1.p), nullptr, xi1, nullptr, nk, R, o, v, s); });
         const KMesh km = c->km;
-        P->ops.push_back([=](hipStream_t s) { return pp_out<double>(one_slab(Z.p), nullptr, xi2, nullptr, km, R, o, v, (double)nk, s); });
+        P->ops.push_back([=](hipStream_t s) {
+            return outputs<double>(one_slab(s1.p), one_slab(Z.p), nullptr, nullptr, xi1, xi2, nullptr, km, R, o, v,
+                                   (double)nk, s);
+        });
         c->prog_xi = std::move(P);
     }
     // right-hand side of the lambda equations: -(S^-1 dE/dT) = -(f_ia + <ij||ab> t_jb, <ij||ab>/Nk)

@@ -78,10 +78,12 @@ struct Node {
     void *write = nullptr;            // tensor written (null for OUT)
     i64 count = 0;                    // its elements
     bool acc = false, full = true;
-    // WRITE: the op writing to dst, or adding to it.  OUT: the op reading the sum of the arrays that
-    // make up reads[0]
+    // WRITE: the op writing to dst, or adding to it.  OUT: the op reading, for each of its reads, the sum of
+    // the arrays that make it up
     std::function<hipError_t(hipStream_t, void *dst, bool acc)> write_to;
-    std::function<hipError_t(hipStream_t, const SlabList &)> from;
+    std::function<hipError_t(hipStream_t, const std::vector<SlabList> &)> from;
+    // further tensors the op of a WRITE node stores in full, always in their own buffers
+    std::vector<std::pair<void *, i64>> also;
 };
 
 // A recorded sequence of device launches plus the device memory it owns.

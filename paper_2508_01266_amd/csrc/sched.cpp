@@ -31,6 +31,7 @@ struct Tensor {
     std::vector<int> own;                // slabs written for this tensor
     std::vector<int> parts;              // own slabs and slabs taken over, in order
     bool read = false;                   // no contribution may follow
+    bool fixed = false;                  // written in its own buffer only
 };
 
 struct Prod {
@@ -138,6 +139,21 @@ bool Program::make_grouped(size_t budget) {
             outs.push_back({i, lvl});
             continue;
         }
+        for (const auto &x : nd.also) {      // stored by this op alone, in place
+            if (!ids.emplace(x.first, (int)tens.size()).second) return false;
+            Tensor xt;
+            xt.p = x.first;
+            xt.count = x.second;
+            xt.fixed = true;
+            Slab xs;
+            xs.tensor = (int)tens.size();
+            xs.last = lvl;
+            xs.all = true;
+            slabs.push_back(std::move(xs));
+            xt.own.push_back((int)slabs.size() - 1);
+            xt.parts = xt.own;
+            tens.push_back(std::move(xt));
+        }
         auto ins = ids.emplace(nd.write, (int)tens.size());
         if (ins.second) {
             tens.push_back(Tensor{});
@@ -147,7 +163,8 @@ bool Program::make_grouped(size_t budget) {
         const int ti = ins.first->second;
         Tensor &t = tens[ti];
         const bool fresh = ins.second;
-        if (t.count != nd.count || t.read) return false;
+        if (t.count != nd.count || t.read || t.fixed) return false;
+        if (!nd.also.empty()) t.fixed = true;
         if (nd.kind == Node::ZERO) {
             if (!t.parts.empty()) return false;
             continue;
@@ -307,8 +324,10 @@ bool Program::make_grouped(size_t budget) {
         return v;
     };
     for (const Other &o : outs) {
-        const int t = ids.at(nodes[o.node].reads.at(0));
-        if (!need_sum[t] && out_list(t).size() > (size_t)kMaxSlabs) need_sum[t] = 1;
+        for (const void *r : nodes[o.node].reads) {
+            const int t = ids.at(r);
+            if (!need_sum[t] && out_list(t).size() > (size_t)kMaxSlabs) need_sum[t] = 1;
+        }
     }
     for (size_t t = 0; t < tens.size(); ++t)
         if (need_sum[t])
@@ -459,11 +478,15 @@ bool Program::make_grouped(size_t budget) {
         for (const Other &o : outs) {
             if (o.level != l) continue;
             const Node &nd = nodes[o.node];
-            const int t = ids.at(nd.reads.at(0));
-            SlabList sl{};
-            if (need_sum[t]) sl = one_slab(tens[t].p);
-            else
-                for (int e : out_list(t)) sl.p[sl.n++] = e < 0 ? tens[-1 - e].p : slabs[e].p;
+            std::vector<SlabList> sl;
+            for (const void *r : nd.reads) {
+                const int t = ids.at(r);
+                SlabList one{};
+                if (need_sum[t]) one = one_slab(tens[t].p);
+                else
+                    for (int e : out_list(t)) one.p[one.n++] = e < 0 ? tens[-1 - e].p : slabs[e].p;
+                sl.push_back(one);
+            }
             const auto fn = nd.from;
             if (!fn) return false;
             grouped.push_back({[fn, sl](hipStream_t s) { return fn(s, sl); }, TAG_NONE, "output"});
