@@ -456,10 +456,10 @@ hipError_t scale_copy(void *y, const void *x, double ar, double ai, i64 n, hipSt
     return hipGetLastError();
 }
 
-// out = in with permuted indices: output dim d is input dim perm[d]; output blocks
+// out = scale * in with permuted indices: output dim d is input dim perm[d]; output blocks
 // [k0][k1][k2] with k3 from the output momentum signs sg (both tensors conserve momentum).
 __global__ void k_permute4(const double2 *in, double2 *out, KMesh km, int e0, int e1, int e2, int e3, int p0, int p1,
-                           int p2, int p3, int s0, int s1, int s2, int s3) {
+                           int p2, int p3, int s0, int s1, int s2, int s3, double scale) {
     const int ein[4] = {e0, e1, e2, e3}, perm[4] = {p0, p1, p2, p3}, sg[4] = {s0, s1, s2, s3};
     int eo[4];
     for (int d = 0; d < 4; ++d) eo[d] = ein[perm[d]];
@@ -478,17 +478,18 @@ __global__ void k_permute4(const double2 *in, double2 *out, KMesh km, int e0, in
         for (int d = 0; d < 4; ++d) { ii[perm[d]] = io[d]; ki[perm[d]] = ko[d]; }
         const i64 src = (((i64)(ki[0] * nk + ki[1]) * nk + ki[2]) * inner) +
                         (((i64)ii[0] * e1 + ii[1]) * e2 + ii[2]) * e3 + ii[3];
-        out[t] = in[src];
+        const double2 x = in[src];
+        out[t] = make_double2(scale * x.x, scale * x.y);
     }
 }
 
 hipError_t permute4(const void *in, void *out, KMesh km, const int *ext_in, const int *perm, const int *sg_out,
-                    hipStream_t s) {
+                    double scale, hipStream_t s) {
     const int nk = km.size();
     const i64 n = (i64)nk * nk * nk * ext_in[0] * ext_in[1] * ext_in[2] * ext_in[3];
     hipLaunchKernelGGL(k_permute4, dim3(grid_for(n)), dim3(256), 0, s, (const double2 *)in, (double2 *)out, km,
                        ext_in[0], ext_in[1], ext_in[2], ext_in[3], perm[0], perm[1], perm[2], perm[3], sg_out[0],
-                       sg_out[1], sg_out[2], sg_out[3]);
+                       sg_out[1], sg_out[2], sg_out[3], scale);
     return hipGetLastError();
 }
 

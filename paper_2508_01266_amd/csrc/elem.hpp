@@ -33,9 +33,9 @@ hipError_t axis_scatter(const void *in, void *out, int nax, int nk, int n, int p
 hipError_t conj_scale(void *y, const void *x, double s, i64 n, hipStream_t st);
 // caller-layout doubles: out = scale * c(P(ij) P(ab) y), c = conjugation when conj != 0 (out of place)
 hipError_t antisym(const void *y, void *out, int R, KMesh km, int o, int v, double scale, int conj, hipStream_t s);
-// four-index complex128 permutation: output dim d = input dim perm[d]; output momentum signs sg_out
+// four-index complex128 permutation, scaled: output dim d = input dim perm[d]; output momentum signs sg_out
 hipError_t permute4(const void *in, void *out, KMesh km, const int *ext_in, const int *perm, const int *sg_out,
-                    hipStream_t s);
+                    double scale, hipStream_t s);
 template <typename T>
 hipError_t pp_in(const void *y, void *Z, KMesh km, int R, int o, int v, double scale, hipStream_t s);
 // out (+)= scale * (in - in with (a,b) and ka/kb swapped), added where `add`: completes a doubles array that holds one

@@ -128,6 +128,8 @@ struct lrcc_ctx {
     // both linear in t2 alone.  With lin_on, the lean precompute replaces them by B(T) + lin_eps B(y)
     // from the buffers linU_* / linW_* (filled at T once per F evaluation and at y per direction).
     std::pair<size_t, size_t> pre64_U{0, 0}, pre64_Wt{0, 0};
+    // the lean precompute as grouped programs of their own (index: lin_on), made on first use
+    std::unique_ptr<Program> pre64_lean[2];
     void *pre64_Wraw = nullptr;
     i64 n_U = 0, n_Wraw = 0;
     void *linU_T = nullptr, *linU_y = nullptr, *linW_T = nullptr, *linW_y = nullptr, *lin_tmp = nullptr;
@@ -441,6 +443,9 @@ void convert_kt(Program &P, State<float> &dst_state, KT &dst, const KT &src, lrc
 }
 
 // ---------------------------------------------------------------- precompute
+// most device memory of the extra arrays of a program's grouped form (six doubles arrays of 64 MB, the
+// largest that are split over several, with room for the smaller tensors)
+constexpr size_t kGroupBudget = (size_t)1 << 30;
 // Allocate the amplitude-dependent state and record the programs that compute it
 // from the device amplitudes (run again whenever the amplitudes change).
 void build_state(lrcc_ctx *c) {
@@ -451,10 +456,17 @@ void build_state(lrcc_ctx *c) {
     S.ready = c->s32.ready = false;
     c->progs.clear();
     c->progmem.clear();
+    for (auto &l : c->pre64_lean) l.reset();
     ++c->gen;
     DevMem &m = S.mem;
     auto Pp = std::make_unique<Program>();
     Program &P = *Pp;
+    // an elementwise op that stores the whole tensor p
+    auto writes = [&P](void *p, i64 count, std::vector<const void *> reads,
+                       std::function<hipError_t(hipStream_t, void *)> fn) {
+        P.ops.push_back([=](hipStream_t s) { return fn(s, p); });
+        P.node(Node::WRITE, std::move(reads), p, count).write_to = [fn](hipStream_t s, void *d, bool) { return fn(s, d); };
+    };
 
     S.t1 = alloc_kt<double>(c, m, "ov");
     S.t2 = alloc_kt<double>(c, m, "oovv");
@@ -462,10 +474,15 @@ void build_state(lrcc_ctx *c) {
     KT foo = alloc_kt<double>(c, m, "oo"), fvv = alloc_kt<double>(c, m, "vv");
     void *fock = c->fock;
     {
-        void *a = S.fov.p, *b = foo.p, *d = fvv.p;
-        P.ops.push_back([=](hipStream_t s) { return one_body_slice<double>(fock, a, nk, n, 0, o, o, v, s); });
-        P.ops.push_back([=](hipStream_t s) { return one_body_slice<double>(fock, b, nk, n, 0, o, 0, o, s); });
-        P.ops.push_back([=](hipStream_t s) { return one_body_slice<double>(fock, d, nk, n, o, v, o, v, s); });
+        writes(S.fov.p, S.fov.count(), {}, [=](hipStream_t s, void *d) {
+            return one_body_slice<double>(fock, d, nk, n, 0, o, o, v, s);
+        });
+        writes(foo.p, foo.count(), {}, [=](hipStream_t s, void *d) {
+            return one_body_slice<double>(fock, d, nk, n, 0, o, 0, o, s);
+        });
+        writes(fvv.p, fvv.count(), {}, [=](hipStream_t s, void *d) {
+            return one_body_slice<double>(fock, d, nk, n, o, v, o, v, s);
+        });
     }
     S.g_oovv = c->g_oovv; S.g_ooov = c->g_ooov; S.g_ovov = c->g_ovov; S.g_ovvv = c->g_ovvv; S.g_ovoo = c->g_ovoo;
     const KT &oovv = c->g_oovv, &ooov = c->g_ooov, &ovvv = c->g_ovvv, &ovvo = c->g_ovvo, &oooo = c->g_oooo;
@@ -473,10 +490,14 @@ void build_state(lrcc_ctx *c) {
     S.tau = alloc_kt<double>(c, m, "oovv");
     KT tt = alloc_kt<double>(c, m, "oovv");
     {
-        void *t1p = S.t1.p, *t2p = S.t2.p, *tau = S.tau.p, *ttp = tt.p;
+        void *t1p = S.t1.p, *t2p = S.t2.p;
         const KMesh km = c->km;
-        P.ops.push_back([=](hipStream_t s) { return tau_like<double>(t1p, t2p, t1p, tau, km, 1, o, v, 0.5, 0, s); });
-        P.ops.push_back([=](hipStream_t s) { return tau_like<double>(t1p, t2p, t1p, ttp, km, 1, o, v, 0.25, 0, s); });
+        writes(S.tau.p, S.tau.count(), {}, [=](hipStream_t s, void *d) {
+            return tau_like<double>(t1p, t2p, t1p, d, km, 1, o, v, 0.5, 0, s);
+        });
+        writes(tt.p, tt.count(), {}, [=](hipStream_t s, void *d) {
+            return tau_like<double>(t1p, t2p, t1p, d, km, 1, o, v, 0.25, 0, s);
+        });
     }
     const KT &t1 = S.t1, &t2 = S.t2, &tau = S.tau;
     // F intermediates (full Fock matrix; the diagonal stays inside, Eq. D is only the preconditioner)
@@ -525,16 +546,15 @@ void build_state(lrcc_ctx *c) {
         // ring layout [m][e][b][j]: the (b,j) columns of the ring product become contiguous
         KT wr = alloc_kt<double>(c, m, "ovvo", 0, {1, -1, 1, -1});
         const int ext[4] = {o, v, v, o}, perm[4] = {0, 2, 1, 3}, sg[4] = {1, -1, 1, -1};
-        void *src = S.Wbar.p, *dst = wr.p;
+        void *src = S.Wbar.p;
         const KMesh km = c->km;
-        P.ops.push_back([=](hipStream_t s) { return permute4(src, dst, km, ext, perm, sg, s); });
+        writes(wr.p, wr.count(), {src}, [=](hipStream_t s, void *d) { return permute4(src, d, km, ext, perm, sg, 1.0, s); });
         // [m][e][j][b]: the transposed ring product sums over (j, b), contiguous in both operands with this
         // layout; from the other one each 16 bytes come from a 128-byte line of their own (Nk=5, o=8, v=40,
         // one complex128 vector: 6.4 ms against 2.9)
         KT wt = alloc_kt<double>(c, m, "ovov", 0, {1, -1, -1, 1});
         const int permT[4] = {0, 2, 3, 1}, sgT[4] = {1, -1, -1, 1};
-        void *dstT = wt.p;
-        P.ops.push_back([=](hipStream_t s) { return permute4(src, dstT, km, ext, permT, sgT, s); });
+        writes(wt.p, wt.count(), {src}, [=](hipStream_t s, void *d) { return permute4(src, d, km, ext, permT, sgT, 1.0, s); });
         S.Wbar = wr;
         S.WbarT = wt;
     }
@@ -573,9 +593,9 @@ void build_state(lrcc_ctx *c) {
         const i64 n = rp.count();
         const KMesh km = c->km;
         const size_t h_begin = P.ops.size();
-        P.ops.push_back([=](hipStream_t s) { return permute4(src, dst, km, ext, perm, sg, s); });
-        P.ops.push_back([=](hipStream_t s) { return scale_copy(dst, dst, -1.0, 0.0, n, s); });
+        writes(dst, n, {src}, [=](hipStream_t s, void *d) { return permute4(src, d, km, ext, perm, sg, -1.0, s); });
         P.ops.push_back([=](hipStream_t s) { return add_inplace<double>(h, dst, n, s); });
+        P.node(Node::ADD, {dst}, h, n);
         c->pre64_lean_skip.push_back({h_begin, P.ops.size()});
     }
     //   G2_ijbm = sum_e t_ie <mb||ej> + 1/2 <mb||ij>, entering as - G2_ijbm x_ma.
@@ -583,11 +603,8 @@ void build_state(lrcc_ctx *c) {
     {
         const int ext[4] = {o, v, o, o}, perm[4] = {2, 3, 1, 0}, sg[4] = {1, 1, -1, -1};
         const void *src = c->g_ovoo.p;
-        void *dst = S.G2.p;
-        const i64 n = S.G2.count();
         const KMesh km = c->km;
-        P.ops.push_back([=](hipStream_t s) { return permute4(src, dst, km, ext, perm, sg, s); });
-        P.ops.push_back([=](hipStream_t s) { return scale_copy(dst, dst, 0.5, 0.0, n, s); });
+        writes(S.G2.p, S.G2.count(), {}, [=](hipStream_t s, void *d) { return permute4(src, d, km, ext, perm, sg, 0.5, s); });
     }
     contract<double>(P, S.G2, "ijbm", t1, "ie", ovvo, "mbej", 1.0);
     // t1-dressed virtual Cholesky slices for the ladder
@@ -596,8 +613,8 @@ void build_state(lrcc_ctx *c) {
     S.Lb = m.get(lvv * 16);
     {
         void *Ls = c->Ls, *Lcs = c->Lcs, *La = S.La, *Lb = S.Lb;
-        P.ops.push_back([=](hipStream_t s) { return chol_slice<double>(Ls, La, nk, naux, n, o, v, o, v, 1.0, 0, s); });
-        P.ops.push_back([=](hipStream_t s) { return chol_slice<double>(Lcs, Lb, nk, naux, n, o, v, o, v, 1.0, 0, s); });
+        writes(La, lvv, {}, [=](hipStream_t s, void *d) { return chol_slice<double>(Ls, d, nk, naux, n, o, v, o, v, 1.0, 0, s); });
+        writes(Lb, lvv, {}, [=](hipStream_t s, void *d) { return chol_slice<double>(Lcs, d, nk, naux, n, o, v, o, v, 1.0, 0, s); });
         build_dressing(c, P, Ls, La, S.t1.p);
         build_dressing(c, P, Lcs, Lb, S.t1.p);
     }
@@ -612,20 +629,23 @@ void build_state(lrcc_ctx *c) {
     S.d_o1 = m.get((size_t)nk * o * 8); S.d_v1 = m.get((size_t)nk * v * 8);
     S.d_o2 = m.get((size_t)nk * o * 8); S.d_v2 = m.get((size_t)nk * v * 8);
     {
-        void *a = S.Fmi.p, *b = S.Fae.p, *cc = S.Fmj.p, *d = S.Fbe.p;
-        double *da = (double *)S.d_o1, *db = (double *)S.d_v1, *dc = (double *)S.d_o2, *dd = (double *)S.d_v2;
-        P.ops.push_back([=](hipStream_t s) { return diag_real(a, da, nk, o, s); });
-        P.ops.push_back([=](hipStream_t s) { return diag_real(b, db, nk, v, s); });
-        P.ops.push_back([=](hipStream_t s) { return diag_real(cc, dc, nk, o, s); });
-        P.ops.push_back([=](hipStream_t s) { return diag_real(d, dd, nk, v, s); });
+        auto diag = [&](const KT &t, void *out, int m) {
+            void *src = t.p;
+            writes(out, (i64)nk * m, {src}, [=](hipStream_t s, void *d) { return diag_real(src, (double *)d, nk, m, s); });
+        };
+        diag(S.Fmi, S.d_o1, o);
+        diag(S.Fae, S.d_v1, v);
+        diag(S.Fmj, S.d_o2, o);
+        diag(S.Fbe, S.d_v2, v);
     }
     S.LaT = m.get(lvv * 16);
     S.LbT = m.get(lvv * 16);
     {
-        void *La = S.La, *Lb = S.Lb, *LaT = S.LaT, *LbT = S.LbT;
-        P.ops.push_back([=](hipStream_t s) { return pair_transpose<double>(La, LaT, nk, naux, v, s); });
-        P.ops.push_back([=](hipStream_t s) { return pair_transpose<double>(Lb, LbT, nk, naux, v, s); });
+        void *La = S.La, *Lb = S.Lb;
+        writes(S.LaT, lvv, {La}, [=](hipStream_t s, void *d) { return pair_transpose<double>(La, d, nk, naux, v, s); });
+        writes(S.LbT, lvv, {Lb}, [=](hipStream_t s, void *d) { return pair_transpose<double>(Lb, d, nk, naux, v, s); });
     }
+    (void)P.group<double>(kGroupBudget, true);
     c->pre64 = std::move(Pp);
     S.ready = true;
 
@@ -686,6 +706,55 @@ static void tune_pre(lrcc_ctx *c, Program *p, const char *which, hipStream_t st)
     tune_store(b, choice);
 }
 
+// The lean precompute as a grouped program: the ops of pre64 without the skipped ranges, and with `lin` the
+// blocks linear in t2 from their parts at T and along y.  Null if it does not run grouped.
+Program *lean_program(lrcc_ctx *c, bool lin) {
+    auto &slot = c->pre64_lean[lin ? 1 : 0];
+    if (slot) return slot->runs_grouped() ? slot.get() : nullptr;
+    slot = std::make_unique<Program>();
+    Program &L = *slot;
+    const Program &P = *c->pre64;
+    if (P.nodes.size() != P.ops.size()) return nullptr;
+    auto within = [](const std::pair<size_t, size_t> &r, size_t i) { return i >= r.first && i < r.second; };
+    auto scaled = [&](void *dst, const void *src, i64 n) {
+        L.ops.push_back([=](hipStream_t s) { return scale_copy(dst, src, c->lin_eps, 0.0, n, s); });
+        L.node(Node::WRITE, {}, dst, n).write_to = [=](hipStream_t s, void *d, bool) {
+            return scale_copy(d, src, c->lin_eps, 0.0, n, s);
+        };
+    };
+    auto plus = [&](void *dst, const void *src, i64 n) {
+        L.ops.push_back([=](hipStream_t s) { return add_inplace<double>(dst, src, n, s); });
+        L.node(Node::ADD, {src}, dst, n);
+    };
+    for (size_t i = 0; i < P.ops.size(); ++i) {
+        bool skip = false;
+        for (const auto &r : c->pre64_lean_skip) skip = skip || within(r, i);
+        if (lin && within(c->pre64_U, i)) {
+            if (i == c->pre64_U.first) {
+                scaled(c->s64.U.p, c->linU_y, c->n_U);
+                plus(c->s64.U.p, c->linU_T, c->n_U);
+            }
+            skip = true;
+        }
+        if (lin && within(c->pre64_Wt, i)) {
+            if (i == c->pre64_Wt.first) {
+                scaled(c->lin_tmp, c->linW_y, c->n_Wraw);
+                plus(c->pre64_Wraw, c->lin_tmp, c->n_Wraw);
+                plus(c->pre64_Wraw, c->linW_T, c->n_Wraw);
+            }
+            skip = true;
+        }
+        if (skip) continue;
+        L.ops.push_back(P.ops[i]);
+        L.nodes.push_back(P.nodes[i]);
+        L.nodes.back().op = L.ops.size() - 1;
+        L.name_last(i < P.names.size() ? P.names[i] : std::string());
+        auto g = P.gemm_ops.find(i);
+        if (g != P.gemm_ops.end()) L.gemm_ops[L.ops.size() - 1] = g->second;
+    }
+    return L.group<double>(kGroupBudget, true) ? slot.get() : nullptr;
+}
+
 // Recompute every amplitude-dependent block from the device amplitudes.
 // lean: the complex128 blocks without R_iabf (H_abej then lacks its R part), for the lean sigma
 // programs only; a later full run restores every block.
@@ -693,6 +762,12 @@ void run_precompute(lrcc_ctx *c, bool fp32, hipStream_t st = nullptr, bool lean 
     static const bool timed = std::getenv("LRCC_PRE_TIMES") != nullptr;   // per-op timing report
     tune_pre(c, c->pre64.get(), "pre64", st);
     if (fp32) tune_pre(c, c->pre32.get(), "pre32", st);
+    if (Program *L = lean && c->pre64->use_grouped ? lean_program(c, c->lin_on) : nullptr) {
+        HIPCHK(L->run(st));
+        if (fp32) HIPCHK(c->pre32->run(st));
+        HIPCHK(hipStreamSynchronize(st));
+        return;
+    }
     if (lean) {
         // skipped ranges (kind 0) and, with lin_on, the blocks linear in t2 formed from their parts
         // at T and along y (kind 1: U, kind 2: the t2 term of W-bar)
@@ -1332,9 +1407,6 @@ hipError_t run_sigma(lrcc_ctx *c, Program *p, hipStream_t st) {
 // kLeanSigma: the CCSD Jacobian (complex128) without the term -x_ie R_jabe, on the blocks of the
 // lean precompute; kRTermSigma: that term alone (complex128).
 constexpr int kLeanSigma = -1, kRTermSigma = -2;
-// most device memory of the extra arrays of a program's grouped form (six doubles arrays of 64 MB, the
-// largest that are split over several, with room for the smaller tensors)
-constexpr size_t kGroupBudget = (size_t)1 << 30;
 Program *sigma_program(lrcc_ctx *c, int prec, int R, bool adjoint = false, int variant = 0) {
     auto key = std::make_pair(variant * 4 + prec * 2 + (adjoint ? 1 : 0), R);
     auto it = c->progs.find(key);
@@ -3128,7 +3200,7 @@ Program *build_state_reverse(lrcc_ctx *c, HamBar &B, DevMem &wm) {
         const void *sp = src.p;
         void *tp = tmp.p;
         const std::array<int, 4> sg{dst.sg[0], dst.sg[1], dst.sg[2], dst.sg[3]};
-        P->ops.push_back([=](hipStream_t s) { return permute4(sp, tp, km, ext.data(), perm.data(), sg.data(), s); });
+        P->ops.push_back([=](hipStream_t s) { return permute4(sp, tp, km, ext.data(), perm.data(), sg.data(), 1.0, s); });
         add(dst, tmp, a);
     };
     // G2_ijbm = 1/2 permute(ovoo) + t_ie <mb||ej>
@@ -3671,6 +3743,7 @@ void setup_hamiltonian(lrcc_ctx *c, int nk, int nocc, int nvir, int naux, const 
     c->prog_epp.reset();
     c->amem.release();
     c->linU_T = c->linU_y = c->linW_T = c->linW_y = c->lin_tmp = nullptr;
+    c->pre64_lean[1].reset();
     c->lin_T_ready = c->lin_on = false;
     c->solv.release();
     c->sol1 = c->sol2 = nullptr;
@@ -4531,6 +4604,7 @@ lrcc_status lrcc_plan_check_mesh(int n0, int n1, int n2, int nocc, int nvir, int
         for (int x = 0; x < 3; ++x) (void)sigma_program(&c, LRCC_FP64, 1, true, 1 + x);
         (void)dens_program(&c, 1);
         (void)dens_program(&c, 4);
+        (void)lean_program(&c, false);
         // the class-at-a-time ladder (mode 3) records other launches
         c.ladder_mode = 3;
         c.progs.clear();

@@ -121,11 +121,12 @@ struct Program {
         return nodes.back();
     }
     // make the grouped form if the data flow allows it and its extra arrays take at most `budget`
-    // bytes; returns whether it was made
+    // bytes; returns whether it was made.  keep: every tensor the program writes is read by others (else
+    // only through OUT nodes)
     template <typename T>
-    bool group(size_t budget);
+    bool group(size_t budget, bool keep = false);
     template <typename T>
-    bool make_grouped(size_t budget);
+    bool make_grouped(size_t budget, bool keep);
     std::vector<Tunable> tunables;
     bool tuned = false;
     std::string tune_key;

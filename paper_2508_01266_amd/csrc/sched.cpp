@@ -79,11 +79,11 @@ constexpr i64 kAloneTiles = 2048;
 }  // namespace
 
 template <typename T>
-bool Program::group(size_t budget) {
+bool Program::group(size_t budget, bool keep) {
     const size_t had = owned.size();
     bool ok = false;
     try {
-        ok = make_grouped<T>(budget);
+        ok = make_grouped<T>(budget, keep);
     } catch (const LrccError &e) {
         if (e.code != 4) throw;          // no room for the extra arrays: the program runs op by op
     }
@@ -103,7 +103,7 @@ bool Program::group(size_t budget) {
 }
 
 template <typename T>
-bool Program::make_grouped(size_t budget) {
+bool Program::make_grouped(size_t budget, bool keep) {
     grouped.clear();
     if (nodes.size() != ops.size()) return false;
     for (size_t i = 0; i < nodes.size(); ++i)
@@ -114,6 +114,7 @@ bool Program::make_grouped(size_t budget) {
     std::vector<Slab> slabs;
     std::vector<Prod> prods;
     std::vector<Other> others, outs;
+    std::unordered_set<const void *> constants;      // read, and not written by an earlier op
     auto last_of = [&](const Tensor &t) {
         int l = -1;
         for (int s : t.parts) l = std::max(l, slabs[s].last);
@@ -131,7 +132,10 @@ bool Program::make_grouped(size_t budget) {
         int lvl = 0;
         for (const void *r : nd.reads) {
             auto it = ids.find(r);
-            if (it == ids.end()) continue;
+            if (it == ids.end()) {
+                constants.insert(r);
+                continue;
+            }
             lvl = std::max(lvl, last_of(tens[it->second]) + 1);
             tens[it->second].read = true;
         }
@@ -140,7 +144,7 @@ bool Program::make_grouped(size_t budget) {
             continue;
         }
         for (const auto &x : nd.also) {      // stored by this op alone, in place
-            if (!ids.emplace(x.first, (int)tens.size()).second) return false;
+            if (constants.count(x.first) || !ids.emplace(x.first, (int)tens.size()).second) return false;
             Tensor xt;
             xt.p = x.first;
             xt.count = x.second;
@@ -154,6 +158,7 @@ bool Program::make_grouped(size_t budget) {
             xt.parts = xt.own;
             tens.push_back(std::move(xt));
         }
+        if (constants.count(nd.write)) return false;      // read before it is written
         auto ins = ids.emplace(nd.write, (int)tens.size());
         if (ins.second) {
             tens.push_back(Tensor{});
@@ -173,7 +178,21 @@ bool Program::make_grouped(size_t budget) {
         if ((nd.acc || nd.kind == Node::ADD) && fresh) return false;             // adds to unknown contents
         if (nd.kind == Node::COPY || nd.kind == Node::ADD) {
             auto src = ids.find(nd.reads.at(0));
-            if (src == ids.end()) return false;
+            if (src == ids.end()) {          // an array no op writes: one slab that is always there
+                src = ids.emplace(nd.reads.at(0), (int)tens.size()).first;
+                Slab xs;
+                xs.tensor = (int)tens.size();
+                xs.all = true;
+                xs.p = const_cast<void *>(nd.reads.at(0));
+                slabs.push_back(std::move(xs));
+                Tensor xt;
+                xt.p = const_cast<void *>(nd.reads.at(0));
+                xt.count = nd.count;
+                xt.read = xt.fixed = true;
+                xt.own = xt.parts = {(int)slabs.size() - 1};
+                tens.push_back(std::move(xt));
+            }
+            Tensor &t = tens[ti];            // (tens may have moved)
             const std::vector<int> &sp = tens[src->second].parts;
             if (sp.empty() || tens[src->second].count != t.count) return false;
             t.parts.insert(t.parts.end(), sp.begin(), sp.end());
@@ -313,6 +332,9 @@ bool Program::make_grouped(size_t budget) {
             if (nodes[i].kind != Node::OUT && !single(t)) need_sum[t] = 1;
         }
     }
+    if (keep)
+        for (size_t t = 0; t < tens.size(); ++t)
+            if (!parts[t].empty() && !single(t)) need_sum[t] = 1;
     // what an output step reads: own slabs, and of tensors taken over their sum where there is one
     auto out_list = [&](int t) {
         std::vector<int> v;                 // slab, or -1 - tensor
@@ -495,7 +517,7 @@ bool Program::make_grouped(size_t budget) {
     return true;
 }
 
-template bool Program::group<double>(size_t);
-template bool Program::group<float>(size_t);
+template bool Program::group<double>(size_t, bool);
+template bool Program::group<float>(size_t, bool);
 
 }  // namespace lrcc
