@@ -190,29 +190,34 @@ hipError_t inputs(const void *x1, const void *x2, const void *t1, void *o1, void
 // ran at 3.6 TB/s on the batched complex64 output, v = 40, and below 1 TB/s at v = 60 with two summands,
 // whose rows do not stay in the L1 cache.)
 constexpr int kOrbTile = 32;
-struct OrbitLds {
-    double2 d[kOrbTile * (kOrbTile + 1)], e[kOrbTile * (kOrbTile + 1)];
-};
+// tiles of at most 32x32, the same size over the row, and their LDS (two arrays, rows one element apart
+// from the tile's width): as little as the row needs, so that workgroups of short rows share a compute unit
+__host__ __device__ inline int orbit_tile(int v) {
+    const int nt = (v + kOrbTile - 1) / kOrbTile;
+    return (v + nt - 1) / nt;
+}
+inline size_t orbit_lds(int v) { return (size_t)2 * orbit_tile(v) * (orbit_tile(v) + 1) * sizeof(double2); }
 template <typename Ld, typename St>
-__device__ __forceinline__ void orbit_rows(OrbitLds &lds, int v, bool two_pairs, bool two_blocks, Ld ld, St st) {
-    const int nt = (v + kOrbTile - 1) / kOrbTile, ts = (v + nt - 1) / nt;
+__device__ __forceinline__ void orbit_rows(double2 *lds, int v, bool two_pairs, bool two_blocks, Ld ld, St st) {
+    const int ts = orbit_tile(v), w = ts + 1;
+    double2 *const ld0 = lds, *const ld1 = lds + ts * w;
     for (int a0 = 0; a0 < v; a0 += ts)
         for (int b0 = 0; b0 < v; b0 += ts) {
             const int na = min(ts, v - a0), nb = min(ts, v - b0), n = na * nb;
             for (int e = threadIdx.x; e < n; e += blockDim.x) {
                 const int a = e / nb, b = e - a * nb, at = (a0 + a) * v + b0 + b;
                 const double2 p = ld(0, at), q = ld(1, at);
-                lds.d[a * (kOrbTile + 1) + b] = make_double2(p.x - q.x, p.y - q.y);
+                ld0[a * w + b] = make_double2(p.x - q.x, p.y - q.y);
             }
             for (int e = threadIdx.x; e < n; e += blockDim.x) {
                 const int b = e / na, a = e - b * na, at = (b0 + b) * v + a0 + a;
                 const double2 p = ld(2, at), q = ld(3, at);
-                lds.e[b * (kOrbTile + 1) + a] = make_double2(p.x - q.x, p.y - q.y);
+                ld1[b * w + a] = make_double2(p.x - q.x, p.y - q.y);
             }
             __syncthreads();
             for (int e = threadIdx.x; e < n; e += blockDim.x) {
                 const int a = e / nb, b = e - a * nb, at = (a0 + a) * v + b0 + b;
-                const double2 x = lds.d[a * (kOrbTile + 1) + b], y = lds.e[b * (kOrbTile + 1) + a];
+                const double2 x = ld0[a * w + b], y = ld1[b * w + a];
                 const double2 z = make_double2(x.x - y.x, x.y - y.y);
                 st(0, at, z);
                 if (two_pairs) st(1, at, make_double2(-z.x, -z.y));
@@ -220,7 +225,7 @@ __device__ __forceinline__ void orbit_rows(OrbitLds &lds, int v, bool two_pairs,
             if (two_blocks)
                 for (int e = threadIdx.x; e < n; e += blockDim.x) {
                     const int b = e / na, a = e - b * na, at = (b0 + b) * v + a0 + a;
-                    const double2 x = lds.d[a * (kOrbTile + 1) + b], y = lds.e[b * (kOrbTile + 1) + a];
+                    const double2 x = ld0[a * w + b], y = ld1[b * w + a];
                     const double2 z = make_double2(x.x - y.x, x.y - y.y);
                     st(2, at, make_double2(-z.x, -z.y));
                     if (two_pairs) st(3, at, z);
@@ -268,7 +273,7 @@ __device__ __forceinline__ double2 slab_sum(const SlabList &l, i64 at) {
 template <typename T, int NS>
 __global__ void k_outputs(SlabList s1, SlabList zs, const double2 *x1, const double2 *x2, double2 *y1, double2 *y2,
                           const double *omega, KMesh km, int R, int o, int v, double scale, unsigned b1) {
-    __shared__ OrbitLds lds;
+    extern __shared__ __attribute__((aligned(16))) double2 lds[];
     const int nk = km.size(), vv = v * v;
     if (blockIdx.x < b1) {      // singles
         const i64 E = (i64)o * v, n = (i64)R * nk * E;
@@ -329,7 +334,7 @@ hipError_t outputs(const SlabList &s1, const SlabList &Z, const void *x1, const 
     const i64 rows = (i64)nk * nk * nk * R * o * o;
     const unsigned b1 = (unsigned)std::min<i64>(((i64)R * nk * o * v + 255) / 256, 1024);
     auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(b1 + rows_grid(rows)), dim3(256), 0, s, s1, Z, (const double2 *)x1,
+        hipLaunchKernelGGL(kernel, dim3(b1 + rows_grid(rows)), dim3(256), orbit_lds(v), s, s1, Z, (const double2 *)x1,
                            (const double2 *)x2, (double2 *)y1, (double2 *)y2, omega, km, R, o, v, scale, b1);
     };
     switch (Z.n) {
@@ -339,6 +344,8 @@ hipError_t outputs(const SlabList &s1, const SlabList &Z, const void *x1, const 
     case 4: go(k_outputs<T, 4>); break;
     case 5: go(k_outputs<T, 5>); break;
     case 6: go(k_outputs<T, 6>); break;
+    case 7: go(k_outputs<T, 7>); break;
+    case 8: go(k_outputs<T, 8>); break;
     default: go(k_outputs<T, 0>); break;
     }
     return hipGetLastError();
@@ -508,7 +515,7 @@ hipError_t conj_scale(void *y, const void *x, double s, i64 n, hipStream_t st) {
 // out = scale * c(y - y(ij swapped) - y(ab swapped) + y(both swapped)) on caller-layout doubles
 // [R][ki][kj][ka][i][j][a][b] (kb implied), c = complex conjugation when conj != 0.  Out of place.
 __global__ void k_antisym(const double2 *y, double2 *out, int R, KMesh km, int o, int v, double scale, int conj) {
-    __shared__ OrbitLds lds;
+    extern __shared__ __attribute__((aligned(16))) double2 lds[];
     const int nk = km.size(), vv = v * v;
     const i64 B = (i64)nk * nk * nk;
     const i64 rows = (i64)R * B * o * o;
@@ -538,7 +545,7 @@ __global__ void k_antisym(const double2 *y, double2 *out, int R, KMesh km, int o
 hipError_t antisym(const void *y, void *out, int R, KMesh km, int o, int v, double scale, int conj, hipStream_t s) {
     const int nk = km.size();
     const i64 rows = (i64)R * nk * nk * nk * o * o;
-    hipLaunchKernelGGL(k_antisym, dim3(rows_grid(rows)), dim3(256), 0, s, (const double2 *)y, (double2 *)out, R, km, o,
+    hipLaunchKernelGGL(k_antisym, dim3(rows_grid(rows)), dim3(256), orbit_lds(v), s, (const double2 *)y, (double2 *)out, R, km, o,
                        v, scale, conj);
     return hipGetLastError();
 }
@@ -558,7 +565,7 @@ hipError_t convert_f64_f32(const void *in, void *out, i64 n, hipStream_t s) {
 // Z[ki,kj,ka][r][i][j][a][b] = scale * (P_ij P_ab y)[r][ki,kj,ka][i][j][a][b]  (caller layout in, block layout out)
 template <typename T>
 __global__ void k_pp_in(const double2 *y, typename Cx<T>::type *Z, KMesh km, int R, int o, int v, double scale) {
-    __shared__ OrbitLds lds;
+    extern __shared__ __attribute__((aligned(16))) double2 lds[];
     const int nk = km.size(), vv = v * v;
     const i64 B = (i64)nk * nk * nk;
     const i64 rows = B * R * o * o;
@@ -590,7 +597,7 @@ template <typename T>
 hipError_t pp_in(const void *y, void *Z, KMesh km, int R, int o, int v, double scale, hipStream_t s) {
     const int nk = km.size();
     const i64 rows = (i64)nk * nk * nk * R * o * o;
-    hipLaunchKernelGGL(k_pp_in<T>, dim3(rows_grid(rows)), dim3(256), 0, s, (const double2 *)y,
+    hipLaunchKernelGGL(k_pp_in<T>, dim3(rows_grid(rows)), dim3(256), orbit_lds(v), s, (const double2 *)y,
                        (typename Cx<T>::type *)Z, km, R, o, v, scale);
     return hipGetLastError();
 }
