@@ -206,12 +206,12 @@ __device__ __forceinline__ void orbit_rows(double2 *lds, int v, bool two_pairs, 
             const int na = min(ts, v - a0), nb = min(ts, v - b0), n = na * nb;
             for (int e = threadIdx.x; e < n; e += blockDim.x) {
                 const int a = e / nb, b = e - a * nb, at = (a0 + a) * v + b0 + b;
-                const double2 p = ld(0, at), q = ld(1, at);
+                const double2 p = ld(0, at, a0 + a, b0 + b), q = ld(1, at, a0 + a, b0 + b);
                 ld0[a * w + b] = make_double2(p.x - q.x, p.y - q.y);
             }
             for (int e = threadIdx.x; e < n; e += blockDim.x) {
                 const int b = e / na, a = e - b * na, at = (b0 + b) * v + a0 + a;
-                const double2 p = ld(2, at), q = ld(3, at);
+                const double2 p = ld(2, at, a0 + a, b0 + b), q = ld(3, at, a0 + a, b0 + b);
                 ld1[b * w + a] = make_double2(p.x - q.x, p.y - q.y);
             }
             __syncthreads();
@@ -219,16 +219,16 @@ __device__ __forceinline__ void orbit_rows(double2 *lds, int v, bool two_pairs, 
                 const int a = e / nb, b = e - a * nb, at = (a0 + a) * v + b0 + b;
                 const double2 x = ld0[a * w + b], y = ld1[b * w + a];
                 const double2 z = make_double2(x.x - y.x, x.y - y.y);
-                st(0, at, z);
-                if (two_pairs) st(1, at, make_double2(-z.x, -z.y));
+                st(0, at, a0 + a, b0 + b, z);
+                if (two_pairs) st(1, at, a0 + a, b0 + b, make_double2(-z.x, -z.y));
             }
             if (two_blocks)
                 for (int e = threadIdx.x; e < n; e += blockDim.x) {
                     const int b = e / na, a = e - b * na, at = (b0 + b) * v + a0 + a;
                     const double2 x = ld0[a * w + b], y = ld1[b * w + a];
                     const double2 z = make_double2(x.x - y.x, x.y - y.y);
-                    st(2, at, make_double2(-z.x, -z.y));
-                    if (two_pairs) st(3, at, z);
+                    st(2, at, a0 + a, b0 + b, make_double2(-z.x, -z.y));
+                    if (two_pairs) st(3, at, a0 + a, b0 + b, z);
                 }
             __syncthreads();
         }
@@ -268,11 +268,17 @@ __device__ __forceinline__ double2 slab_sum(const SlabList &l, i64 at) {
 // Outputs of a product in the caller's layout, one launch:
 //   y1[r][k][i][a] = s1[k][r][i][a] - omega_r x1[r][k][i][a];
 //   y2[r][ki,kj,ka][i][j][a][b] = scale * (P_ij P_ab Z)[ki,kj,ka][r][i][j][a][b] - omega_r * x2[r][...],
-// s1 and Z sums of arrays (NS of them in Z, or any number for NS = 0).  The workgroup of an orbit's first
+// s1 and Z sums of arrays (NS of them in Z, or any number for NS = 0).  diag: the diagonal of
+// the one-body terms, (diag_a + diag_b - diag_i - diag_j) times x2_ijab (antisymmetric in both pairs), or with xs
+// a quarter of that times xs joins Z.  These are far the largest terms: they are added here, in double (in the ring
+// product with the other elements they double the rounding of a complex64 product's doubles, from 1.0e-7 to
+// 2.1e-7 at Nk=5, o=8, v=40), from x2 read for omega already (xs read besides, for the four rows: 8.8 against
+// 6.5 ms with 48 complex64 vectors of that size).  The workgroup of an orbit's first
 // row ((ki, i) <= (kj, j), ka <= kb) writes all of its distinct rows; the others return at once.
 template <typename T, int NS>
-__global__ void k_outputs(SlabList s1, SlabList zs, const double2 *x1, const double2 *x2, double2 *y1, double2 *y2,
-                          const double *omega, KMesh km, int R, int o, int v, double scale, unsigned b1) {
+__global__ void k_outputs(SlabList s1, SlabList zs, SlabList xs, const double2 *diag, const double2 *x1,
+                          const double2 *x2, double2 *y1, double2 *y2, const double *omega, KMesh km, int R, int o,
+                          int v, double scale, unsigned b1) {
     extern __shared__ __attribute__((aligned(16))) double2 lds[];
     const int nk = km.size(), vv = v * v;
     if (blockIdx.x < b1) {      // singles
@@ -313,14 +319,39 @@ __global__ void k_outputs(SlabList s1, SlabList zs, const double2 *x1, const dou
         const i64 zr[4] = {zrow(ki, kj, ka, i, j), zrow(kj, ki, ka, j, i), zrow(ki, kj, kb, i, j), zrow(kj, ki, kb, j, i)};
         const i64 yr[4] = {row * vv, yrow(kj, ki, ka, j, i), yrow(ki, kj, kb, i, j), yrow(kj, ki, kb, j, i)};
         const double w = omega ? omega[r] : 0.0;
-        orbit_rows(lds, v, pi != pj, ka != kb, [&](int rw, int e) { return slab_sum<T, NS>(zs, zr[rw] + e); },
-                   [&](int rw, int e, double2 z) {
+        const double2 *const da = diag + ka * (o + v) + o, *const db = diag + kb * (o + v) + o;
+        double2 dij = make_double2(0, 0);
+        if (diag) {
+            const double2 di = diag[ki * (o + v) + i], dj = diag[kj * (o + v) + j];
+            dij = make_double2(di.x + dj.x, di.y + dj.y);
+        }
+        auto dpair = [&](int a, int b) {        // the same for the four rows
+            const double2 fa = da[a], fb = db[b];
+            return make_double2(fa.x + fb.x - dij.x, fa.y + fb.y - dij.y);
+        };
+        orbit_rows(lds, v, pi != pj, ka != kb,
+                   [&](int rw, int e, int a, int b) {
+                       double2 z = slab_sum<T, NS>(zs, zr[rw] + e);
+                       if (xs.n) {
+                           const double2 x = slab_sum<T, 0>(xs, zr[rw] + e), d = dpair(a, b);
+                           z.x += 0.25 * (d.x * x.x - d.y * x.y);
+                           z.y += 0.25 * (d.x * x.y + d.y * x.x);
+                       }
+                       return z;
+                   },
+                   [&](int rw, int e, int a, int b, double2 z) {
                        const i64 at = yr[rw] + e;
                        double2 out = make_double2(scale * z.x, scale * z.y);
-                       if (omega) {
+                       if (omega || (diag && !xs.n)) {
                            const double2 xv = x2[at];
-                           out.x -= w * xv.x;
-                           out.y -= w * xv.y;
+                           double2 d = make_double2(-w, 0);
+                           if (diag && !xs.n) {
+                               const double2 f = dpair(a, b);
+                               d.x += f.x;
+                               d.y = f.y;
+                           }
+                           out.x += d.x * xv.x - d.y * xv.y;
+                           out.y += d.x * xv.y + d.y * xv.x;
                        }
                        y2[at] = out;
                    });
@@ -328,14 +359,15 @@ __global__ void k_outputs(SlabList s1, SlabList zs, const double2 *x1, const dou
 }
 
 template <typename T>
-hipError_t outputs(const SlabList &s1, const SlabList &Z, const void *x1, const void *x2, void *y1, void *y2,
-                   const double *omega, KMesh km, int R, int o, int v, double scale, hipStream_t s) {
+hipError_t outputs(const SlabList &s1, const SlabList &Z, const SlabList &X, const void *diag, const void *x1,
+                   const void *x2, void *y1, void *y2, const double *omega, KMesh km, int R, int o, int v,
+                   double scale, hipStream_t s) {
     const int nk = km.size();
     const i64 rows = (i64)nk * nk * nk * R * o * o;
     const unsigned b1 = (unsigned)std::min<i64>(((i64)R * nk * o * v + 255) / 256, 1024);
     auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(b1 + rows_grid(rows)), dim3(256), orbit_lds(v), s, s1, Z, (const double2 *)x1,
-                           (const double2 *)x2, (double2 *)y1, (double2 *)y2, omega, km, R, o, v, scale, b1);
+        hipLaunchKernelGGL(kernel, dim3(b1 + rows_grid(rows)), dim3(256), orbit_lds(v), s, s1, Z, X, (const double2 *)diag,
+                           (const double2 *)x1, (const double2 *)x2, (double2 *)y1, (double2 *)y2, omega, km, R, o, v, scale, b1);
     };
     switch (Z.n) {
     case 1: go(k_outputs<T, 1>); break;
@@ -500,6 +532,62 @@ hipError_t permute4(const void *in, void *out, KMesh km, const int *ext_in, cons
     return hipGetLastError();
 }
 
+// One thread per output element; bound by the strided reads of `in`, once per set of amplitudes.
+__global__ void k_ring_matrix(const double2 *in, const double2 *fbe, const double2 *fmj, double2 *out, KMesh km, int o,
+                              int v, int transposed) {
+    const int nk = km.size(), e2 = transposed ? o : v, e3 = transposed ? v : o;
+    const i64 n = (i64)nk * nk * nk * o * v * v * o;
+    for (i64 t = blockIdx.x * (i64)blockDim.x + threadIdx.x; t < n; t += (i64)gridDim.x * blockDim.x) {
+        i64 q = t;
+        const int i3 = (int)(q % e3); q /= e3;
+        const int i2 = (int)(q % e2); q /= e2;
+        const int e = (int)(q % v); q /= v;
+        const int m = (int)(q % o); q /= o;
+        const int k2 = (int)(q % nk); q /= nk;
+        const int ke = (int)(q % nk);
+        const int kmm = (int)(q / nk);
+        // k_m + k_b = k_e + k_j
+        const int k3 = transposed ? km.sum3(1, ke, 1, k2, -1, kmm) : km.sum3(1, kmm, -1, ke, 1, k2);
+        const int b = transposed ? i3 : i2, j = transposed ? i2 : i3, kb = transposed ? k3 : k2;
+        double2 x = in[((((((i64)kmm * nk + kb) * nk + ke) * o + m) * v + b) * v + e) * o + j];
+        if (ke == kb) {                     // and k_m = k_j
+            if (m == j && b != e) {
+                const double2 f = fbe[((i64)kb * v + b) * v + e];
+                x.x += 0.5 * f.x;
+                x.y += 0.5 * f.y;
+            }
+            if (b == e && m != j) {
+                const double2 f = fmj[((i64)kmm * o + m) * o + j];
+                x.x -= 0.5 * f.x;
+                x.y -= 0.5 * f.y;
+            }
+        }
+        out[t] = x;
+    }
+}
+
+// diag[k] = (fmj[k][m][m]; fbe[k][b][b])
+__global__ void k_pair_diag(const double2 *fbe, const double2 *fmj, double2 *diag, int nk, int o, int v) {
+    const int t = blockIdx.x * blockDim.x + threadIdx.x, n = o + v;
+    if (t >= nk * n) return;
+    const int k = t / n, p = t % n;
+    diag[t] = p < o ? fmj[(i64)k * o * o + (i64)p * (o + 1)] : fbe[(i64)k * v * v + (i64)(p - o) * (v + 1)];
+}
+hipError_t pair_diag(const void *fbe, const void *fmj, void *diag, int nk, int o, int v, hipStream_t s) {
+    hipLaunchKernelGGL(k_pair_diag, dim3((nk * (o + v) + 255) / 256), dim3(256), 0, s, (const double2 *)fbe,
+                       (const double2 *)fmj, (double2 *)diag, nk, o, v);
+    return hipGetLastError();
+}
+
+hipError_t ring_matrix(const void *in, const void *fbe, const void *fmj, void *out, KMesh km, int o, int v,
+                       int transposed, hipStream_t s) {
+    const int nk = km.size();
+    const i64 n = (i64)nk * nk * nk * o * v * v * o;
+    hipLaunchKernelGGL(k_ring_matrix, dim3(grid_for(n)), dim3(256), 0, s, (const double2 *)in, (const double2 *)fbe,
+                       (const double2 *)fmj, (double2 *)out, km, o, v, transposed);
+    return hipGetLastError();
+}
+
 // y = s * conj(x)
 __global__ void k_conj_scale(double2 *y, const double2 *x, double s, i64 n) {
     for (i64 t = blockIdx.x * (i64)blockDim.x + threadIdx.x; t < n; t += (i64)gridDim.x * blockDim.x) {
@@ -535,8 +623,8 @@ __global__ void k_antisym(const double2 *y, double2 *out, int R, KMesh km, int o
             return ((r * B + ((i64)k0 * nk + k1) * nk + k2) * o + p) * o * vv + (i64)q3 * vv;
         };
         const i64 yr[4] = {row * vv, rowp(kj, ki, ka, j, i), rowp(ki, kj, kb, i, j), rowp(kj, ki, kb, j, i)};
-        orbit_rows(lds, v, pi != pj, ka != kb, [&](int rw, int e) { return y[yr[rw] + e]; },
-                   [&](int rw, int e, double2 z) {
+        orbit_rows(lds, v, pi != pj, ka != kb, [&](int rw, int e, int, int) { return y[yr[rw] + e]; },
+                   [&](int rw, int e, int, int, double2 z) {
                        out[yr[rw] + e] = make_double2(scale * z.x, conj ? -scale * z.y : scale * z.y);
                    });
     }
@@ -588,8 +676,8 @@ __global__ void k_pp_in(const double2 *y, typename Cx<T>::type *Z, KMesh km, int
         };
         const i64 yr[4] = {yrow(ki, kj, ka, i, j), yrow(kj, ki, ka, j, i), yrow(ki, kj, kb, i, j), yrow(kj, ki, kb, j, i)};
         const i64 zr[4] = {row * vv, zrow(kj, ki, ka, j, i), zrow(ki, kj, kb, i, j), zrow(kj, ki, kb, j, i)};
-        orbit_rows(lds, v, pi != pj, ka != kb, [&](int rw, int e) { return y[yr[rw] + e]; },
-                   [&](int rw, int e, double2 z) { Z[zr[rw] + e] = mk<T>((T)(scale * z.x), (T)(scale * z.y)); });
+        orbit_rows(lds, v, pi != pj, ka != kb, [&](int rw, int e, int, int) { return y[yr[rw] + e]; },
+                   [&](int rw, int e, int, int, double2 z) { Z[zr[rw] + e] = mk<T>((T)(scale * z.x), (T)(scale * z.y)); });
     }
 }
 
@@ -743,8 +831,9 @@ hipError_t outer_oovv(void *g, const void *x, const void *y, double c, int nk, i
                                     double, int, hipStream_t);                                               \
     template hipError_t inputs<T>(const void *, const void *, const void *, void *, void *, void *, KMesh, int, \
                                   int, int, double, hipStream_t);                                            \
-    template hipError_t outputs<T>(const SlabList &, const SlabList &, const void *, const void *, void *,   \
-                                   void *, const double *, KMesh, int, int, int, double, hipStream_t);       \
+    template hipError_t outputs<T>(const SlabList &, const SlabList &, const SlabList &, const void *,        \
+                                   const void *, const void *, void *, void *, const double *, KMesh, int,    \
+                                   int, int, double, hipStream_t);                                            \
     template hipError_t chol_slice<T>(const void *, void *, int, int, int, int, int, int, int, double, int,  \
                                       hipStream_t);                                                          \
     template hipError_t one_body_slice<T>(const void *, void *, int, int, int, int, int, int, hipStream_t);  \

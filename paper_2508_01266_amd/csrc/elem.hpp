@@ -13,10 +13,12 @@ hipError_t tau_like(const void *x1, const void *x2, const void *t1, void *out, K
 template <typename T>
 hipError_t inputs(const void *x1, const void *x2, const void *t1, void *o1, void *o2, void *dtau, KMesh km, int R,
                   int o, int v, double scale, hipStream_t s);
-// y1 = s1 - omega x1, y2 = scale P(ij)P(ab) Z - omega x2 (caller layout; omega may be null)
+// y1 = s1 - omega x1, y2 = scale P(ij)P(ab) Z + (D - omega) x2 (caller layout; omega may be null), D = diag_a + diag_b
+// - diag_i - diag_j (diag: complex128 [nk][o + v], null for D = 0); with X.n: D X / 4 added to Z instead
 template <typename T>
-hipError_t outputs(const SlabList &s1, const SlabList &Z, const void *x1, const void *x2, void *y1, void *y2,
-                   const double *omega, KMesh km, int R, int o, int v, double scale, hipStream_t s);
+hipError_t outputs(const SlabList &s1, const SlabList &Z, const SlabList &X, const void *diag, const void *x1,
+                   const void *x2, void *y1, void *y2, const double *omega, KMesh km, int R, int o, int v,
+                   double scale, hipStream_t s);
 template <typename Tout>
 hipError_t chol_slice(const void *L, void *out, int nk, int naux, int n, int p0, int np, int q0, int nq,
                       double scale, int conj_pair, hipStream_t s);
@@ -36,6 +38,13 @@ hipError_t antisym(const void *y, void *out, int R, KMesh km, int o, int v, doub
 // four-index complex128 permutation, scaled: output dim d = input dim perm[d]; output momentum signs sg_out
 hipError_t permute4(const void *in, void *out, KMesh km, const int *ext_in, const int *perm, const int *sg_out,
                     double scale, hipStream_t s);
+// W-bar in the layouts of the ring products, with the off-diagonal one-body terms of x2: out[m][e][b][j]
+// (transposed: [m][e][j][b]) = in[m][b][e][j] + delta_mj fbe[b][e] / 2 (b != e) - delta_be fmj[m][j] / 2 (m != j)
+// (complex128; fbe, fmj k-diagonal)
+hipError_t ring_matrix(const void *in, const void *fbe, const void *fmj, void *out, KMesh km, int o, int v,
+                       int transposed, hipStream_t s);
+// diag[k] = the diagonals of fmj and fbe (complex128 [nk][o + v])
+hipError_t pair_diag(const void *fbe, const void *fmj, void *diag, int nk, int o, int v, hipStream_t s);
 template <typename T>
 hipError_t pp_in(const void *y, void *Z, KMesh km, int R, int o, int v, double scale, hipStream_t s);
 // out (+)= scale * (in - in with (a,b) and ka/kb swapped), added where `add`: completes a doubles array that holds one

@@ -66,11 +66,12 @@ struct State {
     DevMem mem;
     KT fov, t1, t2, tau;
     KT g_oovv, g_ooov, g_ovov, g_ovvv, g_ovoo;
-    KT Fae, Fmi, Fme, Fbe, Fmj, Fg, Wp, Wbar, R, S, U, H, G2;
+    KT Fae, Fmi, Fme, Fbe, Fmj, Fg, Wp, Wbar, S, U, H;
     KT WbarT;                               // W-bar with (b, j) as [j][b], for the transposed ring product
     void *La = nullptr, *Lb = nullptr;      // dressed virtual Cholesky slices (ladder)
     void *LaT = nullptr, *LbT = nullptr;    // pair-transposed copies (adjoint ladder)
     void *d_o1 = nullptr, *d_v1 = nullptr, *d_o2 = nullptr, *d_v2 = nullptr;  // preconditioner diagonals
+    void *dpair = nullptr;                  // complex128 [nk][o + v]: diagonals of Fbar_mj, Fbar_be
     void *Wst = nullptr;                    // stored antisymmetrised ladder integrals (null: rebuild in LDS)
     bool ready = false;
 };
@@ -543,27 +544,28 @@ void build_state(lrcc_ctx *c) {
     contract<double>(P, ytmp, "mnej", t1, "jf", oovv, "mnef", 1.0, false);
     contract<double>(P, S.Wbar, "mbej", t1, "nb", ytmp, "mnej", -1.0);
     {
-        // ring layout [m][e][b][j]: the (b,j) columns of the ring product become contiguous
+        // Ring layout [m][e][b][j]: the (b,j) columns of the ring product become contiguous.  The one-body
+        // terms of x2, 1/2 x_ijae Fbar_be - 1/2 x_imab Fbar_mj, are the ring product of
+        //   delta_mj Fbar_be / 2 - delta_be Fbar_mj / 2
+        // in the blocks k_m = k_j, so the layout step adds its off-diagonal elements (b != e, m != j) here, the
+        // diagonal is added to the outputs, and no passes over Z are made for them (Nk=5, o=8, v=40: 5.6 of 120 ms with 48 complex64 vectors, 3.3 of 79.7
+        // with 12 complex128 ones)
         KT wr = alloc_kt<double>(c, m, "ovvo", 0, {1, -1, 1, -1});
-        const int ext[4] = {o, v, v, o}, perm[4] = {0, 2, 1, 3}, sg[4] = {1, -1, 1, -1};
-        void *src = S.Wbar.p;
+        const void *src = S.Wbar.p, *fbe = S.Fbe.p, *fmj = S.Fmj.p;
         const KMesh km = c->km;
-        writes(wr.p, wr.count(), {src}, [=](hipStream_t s, void *d) { return permute4(src, d, km, ext, perm, sg, 1.0, s); });
+        writes(wr.p, wr.count(), {src, fbe, fmj}, [=](hipStream_t s, void *d) {
+            return ring_matrix(src, fbe, fmj, d, km, o, v, 0, s);
+        });
         // [m][e][j][b]: the transposed ring product sums over (j, b), contiguous in both operands with this
         // layout; from the other one each 16 bytes come from a 128-byte line of their own (Nk=5, o=8, v=40,
         // one complex128 vector: 6.4 ms against 2.9)
         KT wt = alloc_kt<double>(c, m, "ovov", 0, {1, -1, -1, 1});
-        const int permT[4] = {0, 2, 3, 1}, sgT[4] = {1, -1, -1, 1};
-        writes(wt.p, wt.count(), {src}, [=](hipStream_t s, void *d) { return permute4(src, d, km, ext, permT, sgT, 1.0, s); });
+        writes(wt.p, wt.count(), {src, fbe, fmj}, [=](hipStream_t s, void *d) {
+            return ring_matrix(src, fbe, fmj, d, km, o, v, 1, s);
+        });
         S.Wbar = wr;
         S.WbarT = wt;
     }
-    // R_iabf = sum_me t_imae <mb||ef>   (k_i + k_f = k_a + k_b)
-    c->pre64_lean_skip.clear();
-    S.R = alloc_kt<double>(c, m, "ovvv", 0, {1, -1, -1, 1});
-    const size_t r_begin = P.ops.size();
-    contract<double>(P, S.R, "iabf", t2, "imae", ovvv, "mbef", 1.0, false);
-    c->pre64_lean_skip.push_back({r_begin, P.ops.size()});
     // U_ianf = sum_me t_imae <mn||ef>   (k_i + k_f = k_a + k_n)
     S.U = alloc_kt<double>(c, m, "ovov", 0, {1, -1, -1, 1});
     c->n_U = S.U.count();
@@ -574,39 +576,41 @@ void build_state(lrcc_ctx *c) {
     // of amplitudes, so that each pattern costs one product over all (i, j, a, b) per sigma (the
     // final P(ij)P(ab) antisymmetrisation makes a term and its (i <-> j) image with opposite
     // sign equivalent):
-    //   S_ijan = sum_me t_imae <mn||ej> + sum_f t_jf U_ianf + 1/4 sum_ef tau_ijef <an||ef>,
-    //     entering as - S_ijan x_nb (the former S, Yp and Q / 4 terms);
+    //   S_ijan = sum_me t_imae <mn||ej> + sum_f t_jf U_ianf + 1/4 sum_ef tau_ijef <an||ef>
+    //            - sum_e t_ie <ma||ej> (n for m) - 1/2 <na||ij>, entering as - S_ijan x_nb (a term G_ijbm x_ma
+    //     is minus its own (a <-> b) image, G_ijan x_nb);
     S.S = alloc_kt<double>(c, m, "oovo");
-    contract<double>(P, S.S, "ijan", t2, "imae", ooov, "mnje", -1.0, false);
-    contract<double>(P, S.S, "ijan", t1, "jf", S.U, "ianf", 1.0);
-    contract<double>(P, S.S, "ijan", tau, "ijef", ovvv, "naef", -0.25);
-    //   H_abej = 1/2 <ab||ej> - sum_m t_ma <mb||ej> - R_jabe, entering as x_ie H_abej (the R
-    //     term R_iabf x_jf is minus its own (i <-> j) image, R_jabf x_if);
-    S.H = alloc_kt<double>(c, m, "vvvo");
-    build_eri(c, P, S.H, 0.5);
-    contract<double>(P, S.H, "abej", t1, "ma", ovvo, "mbej", -1.0);
-    {
-        KT rp = alloc_kt<double>(c, m, "vvvo");
-        const int ext[4] = {o, v, v, v}, perm[4] = {1, 2, 3, 0}, sg[4] = {1, 1, -1, -1};
-        const void *src = S.R.p;
-        void *dst = rp.p, *h = S.H.p;
-        const i64 n = rp.count();
-        const KMesh km = c->km;
-        const size_t h_begin = P.ops.size();
-        writes(dst, n, {src}, [=](hipStream_t s, void *d) { return permute4(src, d, km, ext, perm, sg, -1.0, s); });
-        P.ops.push_back([=](hipStream_t s) { return add_inplace<double>(h, dst, n, s); });
-        P.node(Node::ADD, {dst}, h, n);
-        c->pre64_lean_skip.push_back({h_begin, P.ops.size()});
-    }
-    //   G2_ijbm = sum_e t_ie <mb||ej> + 1/2 <mb||ij>, entering as - G2_ijbm x_ma.
-    S.G2 = alloc_kt<double>(c, m, "oovo");
     {
         const int ext[4] = {o, v, o, o}, perm[4] = {2, 3, 1, 0}, sg[4] = {1, 1, -1, -1};
         const void *src = c->g_ovoo.p;
         const KMesh km = c->km;
-        writes(S.G2.p, S.G2.count(), {}, [=](hipStream_t s, void *d) { return permute4(src, d, km, ext, perm, sg, 0.5, s); });
+        writes(S.S.p, S.S.count(), {}, [=](hipStream_t s, void *d) { return permute4(src, d, km, ext, perm, sg, -0.5, s); });
     }
-    contract<double>(P, S.G2, "ijbm", t1, "ie", ovvo, "mbej", 1.0);
+    contract<double>(P, S.S, "ijan", t1, "ie", ovvo, "naej", -1.0);
+    contract<double>(P, S.S, "ijan", t2, "imae", ooov, "mnje", -1.0);
+    contract<double>(P, S.S, "ijan", t1, "jf", S.U, "ianf", 1.0);
+    contract<double>(P, S.S, "ijan", tau, "ijef", ovvv, "naef", -0.25);
+    //   H_abej = 1/2 <ab||ej> - sum_m t_ma <mb||ej> + sum_n U_jane t_nb - 1/4 sum_mn tau_mnab <mn||je>
+    //            - R_jabe, R_iabf = sum_me t_imae <mb||ef>, entering as x_ie H_abej (the terms - U_ianf x_jf t_nb,
+    //     R_iabf x_jf and (x_je <mn||ie> - x_ie <mn||je>) tau_mnab / 8 by their (i <-> j) images),
+    //     stored [j][e][a][b]: (a, b) contiguous as in Z (stored [a][b][e][j], x_ie H_abej over Z took
+    //     3.2 ms at Nk=5, o=8, v=40 with 12 complex128 vectors, 2.0 in this order).
+    KT h0 = alloc_kt<double>(c, m, "vvvo");
+    build_eri(c, P, h0, 0.5);
+    S.H = alloc_kt<double>(c, m, "ovvv", 0, {1, 1, -1, -1});
+    {
+        const int ext[4] = {v, v, v, o}, perm[4] = {3, 2, 0, 1}, sg[4] = {1, 1, -1, -1};
+        const void *src = h0.p;
+        const KMesh km = c->km;
+        writes(S.H.p, S.H.count(), {src}, [=](hipStream_t s, void *d) { return permute4(src, d, km, ext, perm, sg, 1.0, s); });
+    }
+    contract<double>(P, S.H, "jeab", t1, "ma", ovvo, "mbej", -1.0);
+    contract<double>(P, S.H, "jeab", S.U, "jane", t1, "nb", 1.0);
+    contract<double>(P, S.H, "jeab", tau, "mnab", ooov, "mnje", -0.25, true, c->pack_pairs ? "mn" : "");
+    c->pre64_lean_skip.clear();
+    const size_t r_begin = P.ops.size();
+    contract<double>(P, S.H, "jeab", t2, "jmaf", ovvv, "mbfe", -1.0);
+    c->pre64_lean_skip.push_back({r_begin, P.ops.size()});
     // t1-dressed virtual Cholesky slices for the ladder
     const i64 lvv = (i64)nk * nk * naux * v * v;
     S.La = m.get(lvv * 16);
@@ -638,6 +642,11 @@ void build_state(lrcc_ctx *c) {
         diag(S.Fmj, S.d_o2, o);
         diag(S.Fbe, S.d_v2, v);
     }
+    S.dpair = m.get((size_t)nk * n * 16);
+    {
+        const void *fbe = S.Fbe.p, *fmj = S.Fmj.p;
+        writes(S.dpair, (i64)nk * n, {fbe, fmj}, [=](hipStream_t s, void *d) { return pair_diag(fbe, fmj, d, nk, o, v, s); });
+    }
     S.LaT = m.get(lvv * 16);
     S.LbT = m.get(lvv * 16);
     {
@@ -657,9 +666,14 @@ void build_state(lrcc_ctx *c) {
     cv(F.fov, S.fov); cv(F.t1, S.t1); cv(F.t2, S.t2); cv(F.tau, S.tau);
     cv(F.g_oovv, S.g_oovv); cv(F.g_ooov, S.g_ooov); cv(F.g_ovov, S.g_ovov); cv(F.g_ovvv, S.g_ovvv);
     cv(F.g_ovoo, S.g_ovoo);
-    cv(F.Fae, S.Fae); cv(F.Fmi, S.Fmi); cv(F.Fme, S.Fme); cv(F.Fbe, S.Fbe); cv(F.Fmj, S.Fmj);
-    cv(F.Fg, S.Fg); cv(F.Wp, S.Wp); cv(F.Wbar, S.Wbar); cv(F.WbarT, S.WbarT); cv(F.R, S.R); cv(F.S, S.S); cv(F.U, S.U);
-    cv(F.H, S.H); cv(F.G2, S.G2);
+    cv(F.Fae, S.Fae); cv(F.Fmi, S.Fmi); cv(F.Fme, S.Fme);
+    cv(F.Fg, S.Fg); cv(F.Wp, S.Wp); cv(F.Wbar, S.Wbar); cv(F.WbarT, S.WbarT); cv(F.S, S.S);
+    cv(F.H, S.H);
+    F.dpair = F.mem.get((size_t)nk * n * 16);
+    {
+        void *d = F.dpair, *src = S.dpair;
+        P2.ops.push_back([=](hipStream_t s) { return scale_copy(d, src, 1.0, 0.0, (i64)nk * n, s); });
+    }
     F.La = F.mem.get(lvv * 8);
     F.Lb = F.mem.get(lvv * 8);
     F.LaT = F.mem.get(lvv * 8);
@@ -881,7 +895,7 @@ SigmaGraph record_sigma(lrcc_ctx *c, State<T> &S, int R, DevMem &wm, bool full =
     };
     KT x1 = A("ov"), x2 = A("oovv"), dtau = A("oovv"), Z = A("oovv"), s1 = A("ov");
     KT dFae = A("vv"), dFmi = A("oo"), dFme = A("ov"), dFbe = A("vv"), dFmj = A("oo");
-    KT Zmn = A("oooo"), Vx = A("oooo"), Yx = A("oovo");
+    KT Zmn = A("oooo");
     G.x1 = x1; G.x2 = x2; G.Z = Z; G.s1 = s1;
     if (terms == TERMS_R) {
         // -x_ie R_jabe = -sum_mf t_jmaf Q_ibmf, Q_ibmf = sum_e x_ie <mb||fe> (k_i + k_f = k_b + k_m):
@@ -941,9 +955,10 @@ SigmaGraph record_sigma(lrcc_ctx *c, State<T> &S, int R, DevMem &wm, bool full =
     // operands are antisymmetric in a summed pair, or whose output pair reaches sigma2 (or the
     // transposed output) only antisymmetrised, run on unique pairs (pack / transposed pack: see
     // contract); dtau_bar's (e, f) pair is read unsymmetrised and is never packed.
-    con(Z, "Rijab", x2, "Rijae", S.Fbe, "be", 0.5, false);
-    con(Z, "Rijab", t2, "ijae", dFbe, "Rbe", 0.5);
-    con(Z, "Rijab", x2, "Rimab", S.Fmj, "mj", -0.5, true, "ab", "", "ab");
+    // (with the full operator, W-bar and the output step carry the one-body terms of x2: see W-bar's layout)
+    if (!full) con(Z, "Rijab", x2, "Rijae", S.Fbe, "be", 0.5, false);
+    con(Z, "Rijab", t2, "ijae", dFbe, "Rbe", 0.5, !full);
+    if (!full) con(Z, "Rijab", x2, "Rimab", S.Fmj, "mj", -0.5, true, "ab", "", "ab");
     con(Z, "Rijab", t2, "imab", dFmj, "Rmj", -0.5, true, "ab", "", "ab");
     if (!full) return G;  // one-body (perturbation) operator: no two-electron terms
     {
@@ -952,34 +967,21 @@ SigmaGraph record_sigma(lrcc_ctx *c, State<T> &S, int R, DevMem &wm, bool full =
         op.C = Z; op.A = dtau; op.alpha = 0.25; op.actA = true;
         G.ops.push_back(op);
     }
-    // hole-hole terms: Z += Zmn t2 / 16 + Vx tau / 8, Vx_ijmn = x_je <mn||ie> - (i <-> j).
-    // With tau_mnab = t2_mnab + t_ma t_nb - t_mb t_na, Vx tau / 8 is Vx t2 / 8 plus a part
-    // antisymmetric in (a, b), which P(ab) turns into Vx_ijmn t_ma t_nb / 4: the t2 parts share
-    // one product with (Zmn + 2 Vx), and the t1 t1 part joins the Yx t1 product below
-    // (Yx -= Vx t1 / 4), so no product over all (i, j, a, b) is spent on it.
+    // hole-hole terms: Z += Zmn t2 / 16 (+ Wp dtau / 8); their parts linear in x1 are in H.
     // Every operand of these three products is antisymmetric in each of its index pairs, and
     // Z enters sigma2 only through P(ij)P(ab): the forward products run on unique pairs (ij, mn,
     // ef, ab), Zmn being defined on the unique (ij, mn) pairs that its one consumer reads.
     // Transposed: dtau_bar is read by the transposed tau step alone, which antisymmetrises its rows
-    // (ij); Z_bar is antisymmetric in both pairs; Zmn_bar is also read in full by the transposes of
-    // the x1 terms, so it stays complete.
+    // (ij); Z_bar is antisymmetric in both pairs.
     con(Zmn, "Rijmn", dtau, "Rijef", S.g_oovv, "mnef", 1.0, false, "ijmnef", "im", "ijmn");
-    con(Zmn, "Rijmn", x1, "Rje", S.g_ooov, "mnie", 2.0);
-    con(Zmn, "Rjimn", x1, "Rje", S.g_ooov, "mnie", -2.0);
     con(Z, "Rijab", Zmn, "Rijmn", t2, "mnab", 1.0 / 16, true, "ijabmn", "", "ab");
     con(Z, "Rijab", S.Wp, "mnij", dtau, "Rmnab", 1.0 / 8, true, "ijabmn", "", "mnij");
-    con(Vx, "Rijmn", x1, "Rje", S.g_ooov, "mnie", 1.0, false);
-    con(Vx, "Rjimn", x1, "Rje", S.g_ooov, "mnie", -1.0);
-    // ring terms (P(ij)P(ab))
+    // ring terms (P(ij)P(ab)), with the one-body terms of x2
     con(Z, "Rijab", x2, "Rimae", S.Wbar, "mebj", 1.0);
     G.ops.back().Bt = S.WbarT;
     G.ops.back().btl = "mejb";
     con(Z, "Rijab", S.S, "ijan", x1, "Rnb", -1.0);
-    con(Yx, "Rijan", x1, "Rjf", S.U, "ianf", 1.0, false);
-    con(Yx, "Rijan", Vx, "Rijmn", t1, "ma", -0.25);
-    con(Z, "Rijab", Yx, "Rijan", t1, "nb", -1.0);
-    con(Z, "Rijab", x1, "Rie", S.H, "abej", 1.0);   // with TERMS_LEAN, H lacks its R part
-    con(Z, "Rijab", S.G2, "ijbm", x1, "Rma", -1.0);
+    con(Z, "Rijab", x1, "Rie", S.H, "jeab", 1.0);   // with TERMS_LEAN, H lacks its R part
     return G;
 }
 
@@ -1089,19 +1091,26 @@ void ladder_block_gemms(lrcc_ctx *c, Program &P, bool transpose, const void *A, 
             }
 }
 
-// Output steps of a product: y1 = s1 - omega x1, y2 = scale P(ij)P(ab) Z - omega x2 (caller layouts).
+// Output steps of a product: y1 = s1 - omega x1, y2 = scale P(ij)P(ab) Z - omega x2 (caller layouts), and the
+// diagonal one-body part of x2 where dpair is given, formed from X (antisymmetric, Z's layout) if that is given.
 template <typename T>
-void emit_outputs(lrcc_ctx *c, Program &P, const KT &s1, const KT &Z, int R, double scale) {
+void emit_outputs(lrcc_ctx *c, Program &P, const KT &s1, const KT &Z, int R, double scale, const void *dpair = nullptr,
+                  const void *X = nullptr) {
     const int o = c->no, v = c->nv;
     const void *sp = s1.p, *zp = Z.p;
-    P.ops.push_back([=](hipStream_t s) {
-        return outputs<T>(one_slab(sp), one_slab(zp), c->io_x1, c->io_x2, c->io_y1, c->io_y2, c->io_omega, c->km, R, o,
-                          v, scale, s);
-    });
-    P.node(Node::OUT, {sp, zp}, nullptr, Z.count()).from = [=](hipStream_t s, const std::vector<SlabList> &l) {
-        return outputs<T>(l[0], l[1], c->io_x1, c->io_x2, c->io_y1, c->io_y2, c->io_omega, c->km, R, o, v, scale, s);
+    auto fn = [=](hipStream_t s, const SlabList &ls, const SlabList &lz, const SlabList &lx) {
+        return outputs<T>(ls, lz, lx, dpair, c->io_x1, c->io_x2, c->io_y1, c->io_y2, c->io_omega, c->km, R, o, v, scale, s);
+    };
+    P.ops.push_back([=](hipStream_t s) { return fn(s, one_slab(sp), one_slab(zp), X ? one_slab(X) : SlabList{}); });
+    std::vector<const void *> reads{sp, zp};
+    if (X) reads.push_back(X);
+    P.node(Node::OUT, reads, nullptr, Z.count()).from = [=](hipStream_t s, const std::vector<SlabList> &l) {
+        return fn(s, l[0], l[1], X ? l[2] : SlabList{});
     };
 }
+
+// whether the program's one-body terms of x2 are W-bar's and the output's (the full operator, all terms)
+inline bool pair_terms(bool full, int terms) { return full && terms != TERMS_R; }
 
 template <typename T>
 Program *build_sigma(lrcc_ctx *c, State<T> &S, int R, DevMem &wm, bool full = true, int terms = TERMS_ALL) {
@@ -1198,7 +1207,7 @@ Program *build_sigma(lrcc_ctx *c, State<T> &S, int R, DevMem &wm, bool full = tr
         }
     }
     // outputs in the caller layout: y = (A - omega) x, paper normalisation
-    emit_outputs<T>(c, *P, s1, Z, R, (double)nk);
+    emit_outputs<T>(c, *P, s1, Z, R, (double)nk, pair_terms(full, terms) ? S.dpair : nullptr);
     return P;
 }
 
@@ -1221,7 +1230,9 @@ Program *build_sigma_adjoint(lrcc_ctx *c, State<T> &S, int R, DevMem &wm, bool f
     emit_reverse_sweep<T>(c, S, R, G, P, &c->io_x1, &c->io_x2);
     KT x1 = G.x1, x2 = G.x2;
     // y1 = x1bar - omega z1 ; y2 = P(ij)P(ab) x2bar / Nk - omega z2
-    emit_outputs<T>(c, *P, x1, x2, R, 1.0 / nk);
+    // (the diagonal from Zbar, the antisymmetric part of z2 / 4)
+    const bool pairs = pair_terms(full, terms);
+    emit_outputs<T>(c, *P, x1, x2, R, 1.0 / nk, pairs ? S.dpair : nullptr, pairs ? G.Z.p : nullptr);
     return P;
 }
 
@@ -2015,7 +2026,7 @@ void ensure_alpha_programs(lrcc_ctx *c) {
         void *xi1 = c->xi1, *xi2 = c->xi2;
         const KMesh km = c->km;
         P->ops.push_back([=](hipStream_t s) {
-            return outputs<double>(one_slab(s1.p), one_slab(Z.p), nullptr, nullptr, xi1, xi2, nullptr, km, R, o, v,
+            return outputs<double>(one_slab(s1.p), one_slab(Z.p), SlabList{}, nullptr, nullptr, nullptr, xi1, xi2, nullptr, km, R, o, v,
                                    (double)nk, s);
         });
         c->prog_xi = std::move(P);
@@ -2942,7 +2953,7 @@ void alpha_fock_grad(lrcc_ctx *c, int j, int X, int Y, const lrcc_solve_opts &o,
 // evaluation point), the integral classes and the scaled Cholesky arrays (accumulated).
 struct HamBar {
     DevMem mem;
-    KT fov, Fae, Fmi, Fme, Fg, Fbe, Fmj, Wp, Wbar, S, U, H, G2;
+    KT fov, Fae, Fmi, Fme, Fg, Fbe, Fmj, Wp, Wbar, S, U, H;
     KT oooo, ooov, oovv, ovov, ovvo, ovvv, ovoo;
     void *La = nullptr, *Lb = nullptr;           // [nk][nk][naux][v][v]
     void *Ls = nullptr, *Lcs = nullptr;          // [nk][nk][naux][n][n]
@@ -2960,7 +2971,7 @@ void hambar_alloc(lrcc_ctx *c, HamBar &B) {
     like(B.fov, S.fov, B.blocks); like(B.Fae, S.Fae, B.blocks); like(B.Fmi, S.Fmi, B.blocks);
     like(B.Fme, S.Fme, B.blocks); like(B.Fg, S.Fg, B.blocks); like(B.Fbe, S.Fbe, B.blocks);
     like(B.Fmj, S.Fmj, B.blocks); like(B.Wp, S.Wp, B.blocks); like(B.Wbar, S.Wbar, B.blocks);
-    like(B.S, S.S, B.blocks); like(B.U, S.U, B.blocks); like(B.H, S.H, B.blocks); like(B.G2, S.G2, B.blocks);
+    like(B.S, S.S, B.blocks); like(B.U, S.U, B.blocks); like(B.H, S.H, B.blocks);
     like(B.oooo, c->g_oooo, B.classes); like(B.ooov, c->g_ooov, B.classes); like(B.oovv, c->g_oovv, B.classes);
     like(B.ovov, c->g_ovov, B.classes); like(B.ovvo, c->g_ovvo, B.classes); like(B.ovvv, c->g_ovvv, B.classes);
     like(B.ovoo, c->g_ovoo, B.classes);
@@ -2985,8 +2996,8 @@ const KT *bar_of(lrcc_ctx *c, const HamBar &B, const KT &t) {
     const State<double> &S = c->s64;
     const std::pair<const void *, const KT *> map[] = {
         {S.fov.p, &B.fov}, {S.Fae.p, &B.Fae}, {S.Fmi.p, &B.Fmi}, {S.Fme.p, &B.Fme}, {S.Fg.p, &B.Fg},
-        {S.Fbe.p, &B.Fbe}, {S.Fmj.p, &B.Fmj}, {S.Wp.p, &B.Wp}, {S.Wbar.p, &B.Wbar}, {S.S.p, &B.S},
-        {S.U.p, &B.U}, {S.H.p, &B.H}, {S.G2.p, &B.G2}, {c->g_oovv.p, &B.oovv}, {c->g_ooov.p, &B.ooov},
+        {S.Wp.p, &B.Wp}, {S.Wbar.p, &B.Wbar}, {S.S.p, &B.S},
+        {S.H.p, &B.H}, {c->g_oovv.p, &B.oovv}, {c->g_ooov.p, &B.ooov},
         {c->g_ovov.p, &B.ovov}, {c->g_ovvv.p, &B.ovvv}};
     for (const auto &m : map)
         if (m.first == t.p) return m.second;
@@ -3091,6 +3102,9 @@ Program *build_param_vjp(lrcc_ctx *c, HamBar &B, DevMem &wm) {
             ladder_param_vjp(c, *P, f.A, a.C, f.alpha.real(), S.La, S.Lb, B.La, B.Lb, R);
         }
     }
+    // the one-body terms of x2, which W-bar carries in the product (B.Wbar is W-bar's without them)
+    contract<double>(*P, B.Fbe, "be", Gf.x2, "Rijae", Ga.Z, "Rijab", 0.5, true);
+    contract<double>(*P, B.Fmj, "mj", Gf.x2, "Rimab", Ga.Z, "Rijab", -0.5, true);
     return P;
 }
 
@@ -3203,22 +3217,25 @@ Program *build_state_reverse(lrcc_ctx *c, HamBar &B, DevMem &wm) {
         P->ops.push_back([=](hipStream_t s) { return permute4(sp, tp, km, ext.data(), perm.data(), sg.data(), 1.0, s); });
         add(dst, tmp, a);
     };
-    // G2_ijbm = 1/2 permute(ovoo) + t_ie <mb||ej>
-    contract<double>(*P, B.ovvo, "mbej", t1, "ie", B.G2, "ijbm", 1.0);
-    padd(B.ovoo, B.G2, {o, o, v, o}, {3, 2, 0, 1}, 0.5);
-    // H_abej = 1/2 <ab||ej> - t_ma <mb||ej> - permute(R)
-    eri_vjp(c, *P, B.H, 0.5, B.Ls, B.Lcs);
-    contract<double>(*P, B.ovvo, "mbej", t1, "ma", B.H, "abej", -1.0);
-    KT Rb = alloc_kt<double>(c, wm, "ovvv", 0, {1, -1, -1, 1});
-    zero(Rb);
-    padd(Rb, B.H, {v, v, v, o}, {3, 0, 1, 2}, -1.0);
-    // S_ijan = -t_imae <mn||je> + t_jf U_ianf - 1/4 tau_ijef <na||ef>
+    // H_abej [j][e][a][b] = 1/2 <ab||ej> - t_ma <mb||ej> + U_jane t_nb - 1/4 tau_mnab <mn||je> - t_jmaf <mb||fe>
+    {
+        KT hb = alloc_kt<double>(c, wm, "vvvo");
+        zero(hb);
+        padd(hb, B.H, {o, v, v, v}, {2, 3, 1, 0}, 1.0);
+        eri_vjp(c, *P, hb, 0.5, B.Ls, B.Lcs);
+    }
+    contract<double>(*P, B.ovvo, "mbej", t1, "ma", B.H, "jeab", -1.0);
+    contract<double>(*P, B.U, "jane", t1, "nb", B.H, "jeab", 1.0);
+    contract<double>(*P, B.ooov, "mnje", tau, "mnab", B.H, "jeab", -0.25);
+    contract<double>(*P, B.ovvv, "mbfe", t2, "jmaf", B.H, "jeab", -1.0);
+    // S_ijan = -1/2 permute(ovoo) - t_ie <na||ej> - t_imae <mn||je> + t_jf U_ianf - 1/4 tau_ijef <na||ef>
+    padd(B.ovoo, B.S, {o, o, v, o}, {3, 2, 0, 1}, -0.5);
+    contract<double>(*P, B.ovvo, "naej", t1, "ie", B.S, "ijan", -1.0);
     contract<double>(*P, B.ooov, "mnje", t2, "imae", B.S, "ijan", -1.0);
     contract<double>(*P, B.U, "ianf", t1, "jf", B.S, "ijan", 1.0);
     contract<double>(*P, B.ovvv, "naef", tau, "ijef", B.S, "ijan", -0.25);
-    // U_ianf = t_imae <mn||ef> ; R_iabf = t_imae <mb||ef>
+    // U_ianf = t_imae <mn||ef>
     contract<double>(*P, B.oovv, "mnef", t2, "imae", B.U, "ianf", 1.0);
-    contract<double>(*P, B.ovvv, "mbef", t2, "imae", Rb, "iabf", 1.0);
     // Wbar (ring layout [m][e][b][j]) = permute of Wbar0 (ovvo):
     //   Wbar0 = <mb||ej> + t_jf <mb||ef> + t_nb <mn||je> - t_jnfb <mn||ef> - t_nb (t_jf <mn||ef>)
     KT W0 = alloc_kt<double>(c, wm, "ovvo");
