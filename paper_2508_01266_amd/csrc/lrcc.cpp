@@ -1698,13 +1698,9 @@ hipError_t arnoldi_step(SolveCtx &S, GmresWork &W, int j, int precision, double 
     e = selfdot(vn.s, vn.d, R, n1, n2, W.part, W.hn2, 1.0, W.f32, st);
     if (e != hipSuccess) return e;
     e = gmres_step(W.g, j, W.h1, passes == 2 ? W.h2 : nullptr, W.hn2, tol, precision == LRCC_FP64 ? kSingularPivot : 0.0,
-                   st);
+                   (double *)W.stat_d, st);
     if (e != hipSuccess) return e;
-    e = basis_axpby(vn.s, vn.s, W.g.scal, 0.0, R, n1, W.f32, st);
-    if (e != hipSuccess) return e;
-    e = basis_axpby(vn.d, vn.d, W.g.scal, 0.0, R, n2, W.f32, st);
-    if (e != hipSuccess) return e;
-    e = gmres_status(W.g, (double *)W.stat_d, st);
+    e = basis_scale(vn.s, vn.d, W.g.scal, R, n1, n2, W.f32, st);
     if (e != hipSuccess) return e;
     return hipMemcpyAsync(W.stat_h, W.stat_d, (size_t)R * 3 * 8, hipMemcpyDeviceToHost, st);
 }
@@ -1762,8 +1758,7 @@ std::vector<double> gmres(SolveCtx &S, GmresWork &W, const Vecs &b, const Vecs &
                          max_nan(rel));
         // a non-finite residual cannot recover: stop at once (the caller reports it)
         if (all || nonfinite || applied >= max_apply) return done();
-        HIPCHK(basis_axpby(v0.s, v0.s, W.g.scal, 0.0, R, n1, W.f32, st));
-        HIPCHK(basis_axpby(v0.d, v0.d, W.g.scal, 0.0, R, n2p, W.f32, st));
+        HIPCHK(basis_scale(v0.s, v0.d, W.g.scal, R, n1, n2p, W.f32, st));
         int j = 0;
         for (; j < m && applied < max_apply; ++j) {
             // graph replay of the step once the sigma program has been tuned (the first run of a

@@ -49,12 +49,21 @@ __global__ void __launch_bounds__(DB) k_dot_partial(const double2 *u, const doub
     if (t == 0) part[(i64)r * nblk + b] = make_double2(sr[0], si[0]);
 }
 
-__global__ void k_dot_final(const double2 *part, int nblk, int R, double scale, double2 *out) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= R) return;
+// one wave per right-hand side (fixed order; one thread took 5 us over a few dozen partial sums)
+__global__ void __launch_bounds__(64) k_dot_final(const double2 *part, int nblk, int R, double scale, double2 *out) {
+    const int r = blockIdx.x, t = threadIdx.x;
     double ar = 0, ai = 0;
-    for (int b = 0; b < nblk; ++b) { ar += part[(i64)r * nblk + b].x; ai += part[(i64)r * nblk + b].y; }
-    out[r] = make_double2(scale * ar, scale * ai);
+    for (int b = t; b < nblk; b += 64) {
+        const double2 x = part[(i64)r * nblk + b];
+        ar += x.x;
+        ai += x.y;
+    }
+#pragma unroll
+    for (int m = 32; m >= 1; m /= 2) {
+        ar += __shfl_xor(ar, m);
+        ai += __shfl_xor(ai, m);
+    }
+    if (t == 0) out[r] = make_double2(scale * ar, scale * ai);
 }
 
 int dot_blocks(i64 n) {
@@ -69,7 +78,7 @@ hipError_t batched_dot(const void *u, const void *v, int R, i64 n, double scale,
     const int nblk = dot_blocks(n);
     hipLaunchKernelGGL(k_dot_partial, dim3(nblk, R), dim3(DB), 0, s, (const double2 *)u, (const double2 *)v, n, nblk,
                        (double2 *)part, conj_u);
-    hipLaunchKernelGGL(k_dot_final, dim3((R + 63) / 64), dim3(64), 0, s, (const double2 *)part, nblk, R, scale,
+    hipLaunchKernelGGL(k_dot_final, dim3(R), dim3(64), 0, s, (const double2 *)part, nblk, R, scale,
                        (double2 *)out);
     return hipGetLastError();
 }
@@ -87,29 +96,26 @@ __global__ void k_axpby(double2 *y, const double2 *x, const double2 *alpha, doub
     }
 }
 
-// y_r = beta * y_r + alpha_r * x_r on Krylov-vector storage (complex128 or complex64)
+// v_r *= alpha_r on Krylov-vector storage (complex128 or complex64), singles and doubles (grid y = right-hand side)
 template <typename V>
-__global__ void k_basis_axpby(V *y, const V *x, const double2 *alpha, double beta, int R, i64 n) {
-    const i64 N = (i64)R * n;
-    for (i64 t = blockIdx.x * (i64)blockDim.x + threadIdx.x; t < N; t += (i64)gridDim.x * blockDim.x) {
-        const int r = (int)(t / n);
-        const double2 a = alpha[r], xv = ld2(x, t);
-        double2 yv = beta == 0.0 ? make_double2(0, 0) : ld2(y, t);
-        yv.x = beta * yv.x + a.x * xv.x - a.y * xv.y;
-        yv.y = beta * yv.y + a.x * xv.y + a.y * xv.x;
-        st2(y, t, yv);
+__global__ void k_basis_scale(V *vs, V *vd, const double2 *alpha, i64 n1, i64 n2) {
+    const int r = blockIdx.y;
+    const double2 a = alpha[r];
+    for (i64 e = blockIdx.x * (i64)blockDim.x + threadIdx.x; e < n1 + n2; e += (i64)gridDim.x * blockDim.x) {
+        V *p = e < n1 ? vs + (i64)r * n1 + e : vd + (i64)r * n2 + (e - n1);
+        const double2 x = ld2(p, 0);
+        st2(p, 0, make_double2(a.x * x.x - a.y * x.y, a.x * x.y + a.y * x.x));
     }
 }
 
-hipError_t basis_axpby(void *y, const void *x, const void *alpha, double beta, int R, i64 n, int f32, hipStream_t s) {
-    i64 g = ((i64)R * n + 255) / 256;
-    g = std::max<i64>(1, std::min<i64>(g, 262144));
+hipError_t basis_scale(void *vs, void *vd, const void *alpha, int R, i64 n1, i64 n2, int f32, hipStream_t s) {
+    const i64 g = std::max<i64>(1, std::min<i64>((n1 + n2 + 255) / 256, 16384));
     if (f32)
-        hipLaunchKernelGGL(k_basis_axpby<float2>, dim3((unsigned)g), dim3(256), 0, s, (float2 *)y, (const float2 *)x,
-                           (const double2 *)alpha, beta, R, n);
+        hipLaunchKernelGGL(k_basis_scale<float2>, dim3((unsigned)g, R), dim3(256), 0, s, (float2 *)vs, (float2 *)vd,
+                           (const double2 *)alpha, n1, n2);
     else
-        hipLaunchKernelGGL(k_basis_axpby<double2>, dim3((unsigned)g), dim3(256), 0, s, (double2 *)y,
-                           (const double2 *)x, (const double2 *)alpha, beta, R, n);
+        hipLaunchKernelGGL(k_basis_scale<double2>, dim3((unsigned)g, R), dim3(256), 0, s, (double2 *)vs,
+                           (double2 *)vd, (const double2 *)alpha, n1, n2);
     return hipGetLastError();
 }
 
@@ -376,60 +382,85 @@ constexpr int MD = 256;        // threads of the multi-dot and multi-axpy kernel
 constexpr int MDV = 8;         // basis vectors per multi-dot workgroup
 }
 
-// part[(r*k + i)*nblk + b] = sum over chunk b of conj(V_i[r]) w[r] (singles weight 1, doubles dw)
+// part[(r*k + i)*nblk + b] = sum over chunk b of conj(V_i[r]) w[r] (singles weight 1, doubles dw).
+// Small vectors are bound by latency: the loads of an element's basis vectors are in flight together (past the
+// last vector the last one is loaded again, and not stored), the 16 sums of a lane are reduced over the wave by
+// halving (17 exchanges instead of 96), and a workgroup takes at most 1024 elements while there are fewer than
+// 512 (4 occupied, 12 virtual orbitals, 6 right-hand sides, up to 12 vectors: 12.8 us a call with a branch per
+// vector, a tree in LDS and 4096 elements per workgroup, 7.1 so; Nk=3, o=4, v=20, 12 right-hand
+// sides: 30 against 20).
 template <typename V>
 __global__ void __launch_bounds__(MD) k_multidot_partial(const V *Vs, const V *Vd, const V *ws, const V *wd, int R,
                                                          i64 n1, i64 n2, int k, int nblk, double dw, double2 *part) {
-    __shared__ double sr[MDV][MD], si[MDV][MD];
-    const int b = blockIdx.x, r = blockIdx.y, i0 = blockIdx.z * MDV, t = threadIdx.x;
+    __shared__ double red[MD / 64][2 * MDV];
+    const int b = blockIdx.x, r = blockIdx.y, i0 = blockIdx.z * MDV, t = threadIdx.x, lane = t & 63;
     const int nv = min(MDV, k - i0);
-    double ar[MDV], ai[MDV];
+    double a[2 * MDV];                     // re, im of each vector's product
 #pragma unroll
-    for (int q = 0; q < MDV; ++q) { ar[q] = 0; ai[q] = 0; }
+    for (int q = 0; q < 2 * MDV; ++q) a[q] = 0;
     const i64 N = n1 + n2;
     for (i64 e = (i64)b * MD + t; e < N; e += (i64)nblk * MD) {
         const bool single = e < n1;
         const i64 off = single ? (i64)r * n1 + e : (i64)r * n2 + (e - n1);
-        const double2 y = single ? ld2(ws, off) : ld2(wd, off);
+        const V *v0 = (single ? Vs : Vd) + off;
+        const i64 step = (i64)R * (single ? n1 : n2);
+        double2 x[MDV];
+#pragma unroll
+        for (int q = 0; q < MDV; ++q) x[q] = ld2(v0, (i64)(i0 + min(q, nv - 1)) * step);
+        const double2 y = ld2(single ? ws : wd, off);
         const double wt = single ? 1.0 : dw;
 #pragma unroll
         for (int q = 0; q < MDV; ++q) {
-            if (q < nv) {
-                const i64 vo = single ? (i64)(i0 + q) * R * n1 + off : (i64)(i0 + q) * R * n2 + off;
-                const double2 x = single ? ld2(Vs, vo) : ld2(Vd, vo);
-                ar[q] += wt * (x.x * y.x + x.y * y.y);
-                ai[q] += wt * (x.x * y.y - x.y * y.x);
-            }
+            a[2 * q] += wt * (x[q].x * y.x + x[q].y * y.y);
+            a[2 * q + 1] += wt * (x[q].x * y.y - x[q].y * y.x);
         }
     }
+    // each exchange leaves a lane half of its sums, those that its lane bit selects
 #pragma unroll
-    for (int q = 0; q < MDV; ++q) { sr[q][t] = ar[q]; si[q][t] = ai[q]; }
-    __syncthreads();
-    for (int st = MD / 2; st > 0; st >>= 1) {
-        if (t < st)
+    for (int h = MDV; h >= 1; h /= 2) {
+        const int mask = 4 * h;
+        const bool up = (lane & mask) != 0;
 #pragma unroll
-            for (int q = 0; q < MDV; ++q) { sr[q][t] += sr[q][t + st]; si[q][t] += si[q][t + st]; }
-        __syncthreads();
+        for (int q = 0; q < h; ++q) {
+            const double keep = up ? a[q + h] : a[q], send = up ? a[q] : a[q + h];
+            a[q] = keep + __shfl_xor(send, mask);
+        }
     }
-    if (t < nv) part[((i64)r * k + i0 + t) * nblk + b] = make_double2(sr[t][0], si[t][0]);
+    static_assert(MDV == 8, "four halvings: lane bits 5 to 2 are the index of the sum");
+    a[0] += __shfl_xor(a[0], 2);
+    a[0] += __shfl_xor(a[0], 1);
+    if ((lane & 3) == 0) red[t >> 6][lane >> 2] = a[0];
+    __syncthreads();
+    if (t < nv) {
+        double re = 0, im = 0;
+#pragma unroll
+        for (int w = 0; w < MD / 64; ++w) { re += red[w][2 * t]; im += red[w][2 * t + 1]; }
+        part[((i64)r * k + i0 + t) * nblk + b] = make_double2(re, im);
+    }
 }
 
-// out[r*ostride + i] = sum_b part[(r*k + i)*nblk + b]  (fixed order)
-__global__ void k_multidot_final(const double2 *part, int R, int k, int nblk, double2 *out, int ostride) {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
+// out[r*ostride + i] = sum_b part[(r*k + i)*nblk + b], one wave each (fixed order)
+__global__ void __launch_bounds__(MD) k_multidot_final(const double2 *part, int R, int k, int nblk, double2 *out,
+                                                       int ostride) {
+    const int q = blockIdx.x * (MD / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (q >= R * k) return;
     const int r = q / k, i = q - r * k;
     double ar = 0, ai = 0;
-    for (int b = 0; b < nblk; ++b) {
+    for (int b = lane; b < nblk; b += 64) {
         const double2 x = part[(i64)q * nblk + b];
         ar += x.x;
         ai += x.y;
     }
-    out[(i64)r * ostride + i] = make_double2(ar, ai);
+#pragma unroll
+    for (int m = 32; m >= 1; m /= 2) {
+        ar += __shfl_xor(ar, m);
+        ai += __shfl_xor(ai, m);
+    }
+    if (lane == 0) out[(i64)r * ostride + i] = make_double2(ar, ai);
 }
 
 int multidot_blocks(i64 n) {
-    i64 b = (n + MD * 16 - 1) / (MD * 16);
+    i64 b = (n + MD * 4 - 1) / (MD * 4);
     return (int)std::max<i64>(1, std::min<i64>(b, 512));
 }
 
@@ -444,8 +475,8 @@ hipError_t multidot(const void *Vs, const void *Vd, const void *ws, const void *
         hipLaunchKernelGGL(k_multidot_partial<double2>, grid, dim3(MD), 0, s, (const double2 *)Vs,
                            (const double2 *)Vd, (const double2 *)ws, (const double2 *)wd, R, n1, n2, k, nblk, dw,
                            (double2 *)part);
-    hipLaunchKernelGGL(k_multidot_final, dim3((R * k + 63) / 64), dim3(64), 0, s, (const double2 *)part, R, k, nblk,
-                       (double2 *)out, ostride);
+    hipLaunchKernelGGL(k_multidot_final, dim3((R * k + MD / 64 - 1) / (MD / 64)), dim3(MD), 0, s,
+                       (const double2 *)part, R, k, nblk, (double2 *)out, ostride);
     return hipGetLastError();
 }
 
@@ -518,64 +549,86 @@ __global__ void k_gmres_init(GmresState g, const double2 *beta2, double tol) {
     g.scal[r] = make_double2(act ? 1.0 / beta : 0.0, 0.0);
 }
 
+// rel[r], act[r], sing[r] -> status words for the host
+static __device__ void write_status(const GmresState &g, int r, double *out) {
+    out[3 * r] = g.rel[r];
+    out[3 * r + 1] = g.act[r];
+    out[3 * r + 2] = g.sing[r];
+}
+
 // Arnoldi step j for right-hand side r: column j of the Hessenberg matrix from the two
 // Gram-Schmidt passes, the previous Givens rotations applied to it, a new rotation, the residual
-// estimate, and the scale 1/h_{j+1,j} of the next basis vector.  A pivot at or below `sing_pivot`
-// (> 0 only in complex128) marks the right-hand side singular and stops it.
-__global__ void k_gmres_step(GmresState g, int j, const double2 *h1, const double2 *h2, const double2 *hn2, double tol,
-                             double sing_pivot) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= g.R) return;
-    const int m = g.m, ld = m + 1;
+// estimate, the scale 1/h_{j+1,j} of the next basis vector and the status words.  A pivot at or below
+// `sing_pivot` (> 0 only in complex128) marks the right-hand side singular and stops it.
+// One wave per right-hand side: its lanes move the column and the rotations between memory and LDS, lane 0
+// runs the serial chain of rotations there (on memory, one thread per right-hand side: 4.6 us at a
+// dozen steps and 9.9 at 30; 4.2 and 5.1 so).
+constexpr int kMaxStep = 64;
+__global__ void __launch_bounds__(64) k_gmres_step(GmresState g, int j, const double2 *h1, const double2 *h2,
+                                                   const double2 *hn2, double tol, double sing_pivot, double *status) {
+    __shared__ double2 col[kMaxStep + 1], c_[kMaxStep], s_[kMaxStep];
+    const int r = blockIdx.x, t = threadIdx.x, m = g.m, ld = m + 1;
     double2 *H = g.H + (i64)r * (m + 1) * m, *cs = g.cs + (i64)r * m, *sn = g.sn + (i64)r * m;
     double2 *gg = g.g + (i64)r * ld;
-    if (!g.act[r]) {
+    const bool on = g.act[r] != 0;
+    if (on) {
+        if (t <= j) {
+            const double2 a = h1[(i64)r * ld + t], b = h2 ? h2[(i64)r * ld + t] : make_double2(0, 0);
+            col[t] = make_double2(a.x + b.x, a.y + b.y);
+        }
+        if (t < j) {
+            c_[t] = cs[t];
+            s_[t] = sn[t];
+        }
+    }
+    __syncthreads();
+    auto chain = [&]() {
         g.scal[r] = make_double2(0, 0);
-        return;
+        if (!on) return;
+        const double n2 = hn2[r].x;
+        if (!isfinite(n2) || !isfinite(hn2[r].y)) {
+            g.rel[r] = nan("");
+            g.act[r] = 0;
+            return;
+        }
+        const double hn = sqrt(fmax(0.0, n2));
+        double2 a = col[0];
+        for (int i = 0; i < j; ++i) {
+            const double2 b = col[i + 1];
+            const double2 t0 = cmul(cconj(c_[i]), a), t1 = cmul(cconj(s_[i]), b);
+            const double2 u0 = cmul(s_[i], a), u1 = cmul(c_[i], b);
+            col[i] = make_double2(t0.x + t1.x, t0.y + t1.y);
+            a = make_double2(u1.x - u0.x, u1.y - u0.y);
+        }
+        const double2 b = make_double2(hn, 0.0);
+        const double den = sqrt(cabs2(a) + cabs2(b));
+        if (sing_pivot > 0 && den <= sing_pivot) {
+            g.sing[r] = 1;
+            g.act[r] = 0;
+            return;
+        }
+        const double2 cj = den > 0 ? make_double2(a.x / den, a.y / den) : make_double2(1, 0);
+        const double2 sj = den > 0 ? make_double2(b.x / den, b.y / den) : make_double2(0, 0);
+        cs[j] = cj;
+        sn[j] = sj;
+        col[j] = make_double2(den, 0);
+        const double2 gj = gg[j], ng = cmul(sj, gj);
+        gg[j] = cmul(cconj(cj), gj);
+        gg[j + 1] = make_double2(-ng.x, -ng.y);
+        g.kr[r] = j + 1;
+        const double bn = g.bn[r];
+        const double rel = bn > 0 ? sqrt(cabs2(ng)) / bn : 0.0;
+        g.rel[r] = rel;
+        const bool act = !(rel <= tol || hn == 0 || isnan(rel));
+        g.act[r] = act ? 1 : 0;
+        g.scal[r] = make_double2(act && hn > 0 ? 1.0 / hn : 0.0, 0.0);
+    };
+    if (t == 0) {
+        chain();
+        write_status(g, r, status);
     }
-    for (int i = 0; i <= j; ++i) {
-        const double2 a = h1[(i64)r * ld + i], b = h2 ? h2[(i64)r * ld + i] : make_double2(0, 0);
-        H[i * m + j] = make_double2(a.x + b.x, a.y + b.y);
-    }
-    const double n2 = hn2[r].x;
-    if (!isfinite(n2) || !isfinite(hn2[r].y)) {
-        g.rel[r] = nan("");
-        g.act[r] = 0;
-        g.scal[r] = make_double2(0, 0);
-        return;
-    }
-    const double hn = sqrt(fmax(0.0, n2));
-    H[(j + 1) * m + j] = make_double2(hn, 0.0);
-    for (int i = 0; i < j; ++i) {
-        const double2 a = H[i * m + j], b = H[(i + 1) * m + j];
-        const double2 t0 = cmul(cconj(cs[i]), a), t1 = cmul(cconj(sn[i]), b);
-        const double2 u0 = cmul(sn[i], a), u1 = cmul(cs[i], b);
-        H[i * m + j] = make_double2(t0.x + t1.x, t0.y + t1.y);
-        H[(i + 1) * m + j] = make_double2(u1.x - u0.x, u1.y - u0.y);
-    }
-    const double2 a = H[j * m + j], b = H[(j + 1) * m + j];
-    const double den = sqrt(cabs2(a) + cabs2(b));
-    if (sing_pivot > 0 && den <= sing_pivot) {
-        g.sing[r] = 1;
-        g.act[r] = 0;
-        g.scal[r] = make_double2(0, 0);
-        return;
-    }
-    cs[j] = den > 0 ? make_double2(a.x / den, a.y / den) : make_double2(1, 0);
-    sn[j] = den > 0 ? make_double2(b.x / den, b.y / den) : make_double2(0, 0);
-    H[j * m + j] = make_double2(den, 0);
-    H[(j + 1) * m + j] = make_double2(0, 0);
-    const double2 gj = gg[j];
-    gg[j] = cmul(cconj(cs[j]), gj);
-    const double2 ng = cmul(sn[j], gj);
-    gg[j + 1] = make_double2(-ng.x, -ng.y);
-    g.kr[r] = j + 1;
-    const double bn = g.bn[r];
-    const double rel = bn > 0 ? sqrt(cabs2(gg[j + 1])) / bn : 0.0;
-    g.rel[r] = rel;
-    const bool act = !(rel <= tol || hn == 0 || isnan(rel));
-    g.act[r] = act ? 1 : 0;
-    g.scal[r] = make_double2(act && hn > 0 ? 1.0 / hn : 0.0, 0.0);
+    __syncthreads();
+    if (on && t <= j) H[t * m + j] = col[t];      // (a column that kr does not count is not read)
 }
 
 // End of a cycle: y = H^-1 g on the first kr[r] steps (back substitution), coefficients y[r][i].
@@ -600,13 +653,9 @@ __global__ void k_gmres_solve(GmresState g, double2 *y) {
     }
 }
 
-// rel[r] -> status words for the host: (rel, act, sing) packed per right-hand side
 __global__ void k_gmres_status(GmresState g, double *out) {
     const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= g.R) return;
-    out[3 * r] = g.rel[r];
-    out[3 * r + 1] = g.act[r];
-    out[3 * r + 2] = g.sing[r];
+    if (r < g.R) write_status(g, r, out);
 }
 
 hipError_t gmres_init(const GmresState &g, const void *beta2, double tol, hipStream_t s) {
@@ -614,9 +663,10 @@ hipError_t gmres_init(const GmresState &g, const void *beta2, double tol, hipStr
     return hipGetLastError();
 }
 hipError_t gmres_step(const GmresState &g, int j, const void *h1, const void *h2, const void *hn2, double tol,
-                      double sing_pivot, hipStream_t s) {
-    hipLaunchKernelGGL(k_gmres_step, dim3((g.R + 63) / 64), dim3(64), 0, s, g, j, (const double2 *)h1,
-                       (const double2 *)h2, (const double2 *)hn2, tol, sing_pivot);
+                      double sing_pivot, double *status, hipStream_t s) {
+    if (j < 0 || j >= kMaxStep || j >= g.m) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_gmres_step, dim3(g.R), dim3(64), 0, s, g, j, (const double2 *)h1, (const double2 *)h2,
+                       (const double2 *)hn2, tol, sing_pivot, status);
     return hipGetLastError();
 }
 hipError_t gmres_solve(const GmresState &g, void *y, hipStream_t s) {

@@ -12,7 +12,7 @@ hipError_t batched_axpby(void *y, const void *x, const void *alpha, double beta,
 // Krylov vectors (and the vectors orthogonalised against them) are stored in complex128, or in
 // complex64 with f32 = 1 (the complex64 inner solves); arithmetic is complex128 in both.
 // y = beta y + alpha_r x on that storage
-hipError_t basis_axpby(void *y, const void *x, const void *alpha, double beta, int R, i64 n, int f32, hipStream_t s);
+hipError_t basis_scale(void *vs, void *vd, const void *alpha, int R, i64 n1, i64 n2, int f32, hipStream_t s);
 // singles divided by (ev - eo - w), doubles by (ev2 + ev2 - eo2 - eo2 - w)
 hipError_t precond(void *o1, void *o2, const void *i1, const void *i2, const double *eo, const double *ev,
                    const double *eo2, const double *ev2, const double *omega, KMesh km, int R, int no, int nv,
@@ -67,9 +67,10 @@ hipError_t selfdot(const void *ws, const void *wd, int R, i64 n1, i64 n2, void *
 hipError_t multiaxpy(void *ws, void *wd, const void *Vs, const void *Vd, const void *C, int cstride, double sign,
                      const int *mask, double beta, int R, i64 n1, i64 n2, int k, int f32, hipStream_t s);
 hipError_t gmres_init(const GmresState &g, const void *beta2, double tol, hipStream_t s);
-// h2: the second Gram-Schmidt pass's coefficients, or null after a single pass
+// h2: the second Gram-Schmidt pass's coefficients, or null after a single pass; writes the status words as
+// gmres_status; j < 64
 hipError_t gmres_step(const GmresState &g, int j, const void *h1, const void *h2, const void *hn2, double tol,
-                      double sing_pivot, hipStream_t s);
+                      double sing_pivot, double *status, hipStream_t s);
 hipError_t gmres_solve(const GmresState &g, void *y, hipStream_t s);
 hipError_t gmres_status(const GmresState &g, double *out, hipStream_t s);
 }  // namespace lrcc
