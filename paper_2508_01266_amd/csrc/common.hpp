@@ -170,6 +170,18 @@ int gemm_shape(const GemmArgs &g, bool fp64);
 // tile shapes the autotuner tries for g (the heuristic one first)
 std::vector<int> gemm_candidates(const GemmArgs &g, bool fp64);
 
+// Index splitting: quotient, and digit d of q (the remainder; q becomes the quotient), with 32-bit division where
+// the numbers allow it (a 64-bit one is a hundred instructions, and a row or an element takes half a dozen).
+__device__ inline i64 quot(i64 n, i64 d) {
+    return ((n | d) >> 32) == 0 ? (i64)((unsigned)n / (unsigned)d) : n / d;
+}
+__device__ inline int take(i64 &q, int d) {
+    const i64 n = quot(q, d);
+    const int r = (int)(q - n * d);
+    q = n;
+    return r;
+}
+
 // Ladder: sigma2[ki,kj,ka][R][i][j][a][b] += alpha * sum_{ke} sum_{e,f}
 //   Y[ki,kj,ke][R][i][j][e][f] * sum_Q La[ka][ke][Q][a][e] * Lb[kb][kf][Q][b][f]
 struct LadderArgs {

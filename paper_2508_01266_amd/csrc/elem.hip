@@ -26,6 +26,11 @@ template <typename T> __device__ inline typename Cx<T>::type mk(T x, T y) {
 // row index (the same for every lane) is split with 64-bit arithmetic once per row and
 // the position inside the row with 32-bit arithmetic; splitting a flat 64-bit element
 // index with 64-bit divisions costs more than the memory traffic of these kernels.
+// Many short rows (up to 512 elements) go to a wave each: a workgroup of four waves spends longer on starting
+// and on splitting the row's index than on its 256 elements.  2x2x2 mesh, o=4, v=16, 12 complex64 vectors (98304
+// rows): inputs 0.365 -> 0.155 ms (805 MB), outputs 0.45 -> 0.28 ms.  Few rows leave the device idle that way:
+// one k point, o=4, v=12 (144 rows): a product 62 -> 69 us; Nk=3, o=4, v=20 (5184 rows): 601 -> 616 us.
+inline bool wave_rows(i64 rows, int v) { return (i64)v * v <= 512 && rows >= 32768; }
 inline unsigned rows_grid(i64 rows) {
     return (unsigned)std::max<i64>(1, std::min<i64>(rows, 65536 * 4));
 }
@@ -68,11 +73,11 @@ __global__ void k_tau_like(const typename Cx<T>::type *x1, const typename Cx<T>:
     for (i64 row = blockIdx.x; row < rows; row += gridDim.x) {
         // row = (((ki nk + kj) nk + ka) R + r) o + i) o + j, elements (a, b)
         i64 q = row;
-        const int j = (int)(q % o); q /= o;
-        const int i = (int)(q % o); q /= o;
-        const int r = (int)(q % R); q /= R;
-        const int ka = (int)(q % nk); q /= nk;
-        const int kj = (int)(q % nk); q /= nk;
+        const int j = take(q, o);
+        const int i = take(q, o);
+        const int r = take(q, R);
+        const int ka = take(q, nk);
+        const int kj = take(q, nk);
         const int ki = (int)q;
         const int kb = km.comb(ki, kj, ka);
         const int rx = x1_has_rhs ? r : 0;
@@ -121,9 +126,10 @@ __global__ void k_inputs(const double2 *x1, const double2 *x2, const typename Cx
                          typename Cx<T>::type *o1, typename Cx<T>::type *o2, typename Cx<T>::type *dtau, KMesh km,
                          int R, int o, int v, double scale, i64 rows, unsigned b1) {
     const int nk = km.size(), vv = v * v;
+    const int lane = threadIdx.x, lanes = blockDim.x, ty = threadIdx.y, ny = blockDim.y;   // ny rows at a time
     if (blockIdx.x < b1) {      // singles
         const i64 E = (i64)o * v, n = (i64)R * nk * E;
-        for (i64 t = blockIdx.x * (i64)blockDim.x + threadIdx.x; t < n; t += (i64)b1 * blockDim.x) {
+        for (i64 t = ((i64)blockIdx.x * ny + ty) * lanes + lane; t < n; t += (i64)b1 * ny * lanes) {
             const i64 e = t % E;
             const int k = (int)((t / E) % nk), r = (int)(t / (E * nk));
             const double2 x = x1[t];
@@ -132,11 +138,11 @@ __global__ void k_inputs(const double2 *x1, const double2 *x2, const typename Cx
         return;
     }
     const i64 B = (i64)nk * nk * nk;
-    for (i64 row = blockIdx.x - b1; row < rows; row += gridDim.x - b1) {
+    for (i64 row = (i64)(blockIdx.x - b1) * ny + ty; row < rows; row += (i64)(gridDim.x - b1) * ny) {
         // row = (((ki nk + kj) nk + ka) R + r) o + i) o + j of the block layout, elements (a, b)
         i64 q = row;
-        const int j = (int)(q % o); q /= o;
-        const int i = (int)(q % o); q /= o;
+        const int j = take(q, o);
+        const int i = take(q, o);
         const int r = (int)(q % R);
         const i64 blk = q / R;
         const int ka = (int)(blk % nk), kj = (int)((blk / nk) % nk), ki = (int)(blk / (nk * nk));
@@ -148,7 +154,8 @@ __global__ void k_inputs(const double2 *x1, const double2 *x2, const typename Cx
         auto Tt = [&](int k, int ii, int aa) { return t1[((i64)k * o + ii) * v + aa]; };
         const double2 *src = x2 + ((((i64)r * B + blk) * o + i) * o + j) * vv;
         typename Cx<T>::type *d2 = o2 + row * vv, *dt = dtau + row * vv;
-        for (int e = threadIdx.x; e < vv; e += blockDim.x) {
+#pragma unroll 4
+        for (int e = lane; e < vv; e += lanes) {
             const double2 in = src[e];
             const auto x = mk<T>((T)(scale * in.x), (T)(scale * in.y));
             d2[e] = x;
@@ -175,7 +182,8 @@ hipError_t inputs(const void *x1, const void *x2, const void *t1, void *o1, void
     const int nk = km.size();
     const i64 rows = (i64)nk * nk * nk * R * o * o;
     const unsigned b1 = (unsigned)std::min<i64>(((i64)R * nk * o * v + 255) / 256, 1024);
-    hipLaunchKernelGGL(k_inputs<T>, dim3(b1 + rows_grid(rows)), dim3(256), 0, s, (const double2 *)x1,
+    const dim3 block = wave_rows(rows, v) ? dim3(64, 4) : dim3(256, 1);
+    hipLaunchKernelGGL(k_inputs<T>, dim3(b1 + rows_grid((rows + block.y - 1) / block.y)), block, 0, s, (const double2 *)x1,
                        (const double2 *)x2, (const typename Cx<T>::type *)t1, (typename Cx<T>::type *)o1,
                        (typename Cx<T>::type *)o2, (typename Cx<T>::type *)dtau, km, R, o, v, scale, rows, b1);
     return hipGetLastError();
@@ -204,17 +212,20 @@ __device__ __forceinline__ void orbit_rows(double2 *lds, int v, bool two_pairs, 
     for (int a0 = 0; a0 < v; a0 += ts)
         for (int b0 = 0; b0 < v; b0 += ts) {
             const int na = min(ts, v - a0), nb = min(ts, v - b0), n = na * nb;
+#pragma unroll 4
             for (int e = threadIdx.x; e < n; e += blockDim.x) {
                 const int a = e / nb, b = e - a * nb, at = (a0 + a) * v + b0 + b;
                 const double2 p = ld(0, at, a0 + a, b0 + b), q = ld(1, at, a0 + a, b0 + b);
                 ld0[a * w + b] = make_double2(p.x - q.x, p.y - q.y);
             }
+#pragma unroll 4
             for (int e = threadIdx.x; e < n; e += blockDim.x) {
                 const int b = e / na, a = e - b * na, at = (b0 + b) * v + a0 + a;
                 const double2 p = ld(2, at, a0 + a, b0 + b), q = ld(3, at, a0 + a, b0 + b);
                 ld1[b * w + a] = make_double2(p.x - q.x, p.y - q.y);
             }
             __syncthreads();
+#pragma unroll 4
             for (int e = threadIdx.x; e < n; e += blockDim.x) {
                 const int a = e / nb, b = e - a * nb, at = (a0 + a) * v + b0 + b;
                 const double2 x = ld0[a * w + b], y = ld1[b * w + a];
@@ -223,7 +234,8 @@ __device__ __forceinline__ void orbit_rows(double2 *lds, int v, bool two_pairs, 
                 if (two_pairs) st(1, at, a0 + a, b0 + b, make_double2(-z.x, -z.y));
             }
             if (two_blocks)
-                for (int e = threadIdx.x; e < n; e += blockDim.x) {
+    #pragma unroll 4
+            for (int e = threadIdx.x; e < n; e += blockDim.x) {
                     const int b = e / na, a = e - b * na, at = (b0 + b) * v + a0 + a;
                     const double2 x = ld0[a * w + b], y = ld1[b * w + a];
                     const double2 z = make_double2(x.x - y.x, x.y - y.y);
@@ -302,8 +314,8 @@ __global__ void k_outputs(SlabList s1, SlabList zs, SlabList xs, const double2 *
     for (i64 row = blockIdx.x - b1; row < rows; row += gridDim.x - b1) {
         // row indexes the caller layout [r][blk][i][j], elements (a, b)
         i64 q = row;
-        const int j = (int)(q % o); q /= o;
-        const int i = (int)(q % o); q /= o;
+        const int j = take(q, o);
+        const int i = take(q, o);
         const i64 blk = q % B;
         const int r = (int)(q / B);
         const int ka = (int)(blk % nk), kj = (int)((blk / nk) % nk), ki = (int)(blk / (nk * nk));
@@ -366,7 +378,7 @@ hipError_t outputs(const SlabList &s1, const SlabList &Z, const SlabList &X, con
     const i64 rows = (i64)nk * nk * nk * R * o * o;
     const unsigned b1 = (unsigned)std::min<i64>(((i64)R * nk * o * v + 255) / 256, 1024);
     auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(b1 + rows_grid(rows)), dim3(256), orbit_lds(v), s, s1, Z, X, (const double2 *)diag,
+        hipLaunchKernelGGL(kernel, dim3(b1 + rows_grid(rows)), dim3(wave_rows(rows, v) ? 64 : 256), orbit_lds(v), s, s1, Z, X, (const double2 *)diag,
                            (const double2 *)x1, (const double2 *)x2, (double2 *)y1, (double2 *)y2, omega, km, R, o, v, scale, b1);
     };
     switch (Z.n) {
@@ -391,9 +403,9 @@ __global__ void k_chol_slice(const double2 *L, typename Cx<Tout>::type *out, int
     const i64 n_out = (i64)nk * nk * naux * np * nq;
     for (i64 t = blockIdx.x * (i64)blockDim.x + threadIdx.x; t < n_out; t += (i64)gridDim.x * blockDim.x) {
         i64 q = t;
-        const int qq = (int)(q % nq); q /= nq;
-        const int pp = (int)(q % np); q /= np;
-        const int Q = (int)(q % naux); q /= naux;
+        const int qq = take(q, nq);
+        const int pp = take(q, np);
+        const int Q = take(q, naux);
         const int k2 = (int)(q % nk);
         const int k1 = (int)(q / nk);
         double2 v;
@@ -441,8 +453,8 @@ __global__ void k_axis_slice(const double2 *in, typename Cx<Tout>::type *out, in
     const i64 N = (i64)nk * nax * np * nq;
     for (i64 t = blockIdx.x * (i64)blockDim.x + threadIdx.x; t < N; t += (i64)gridDim.x * blockDim.x) {
         i64 q = t;
-        const int qq = (int)(q % nq); q /= nq;
-        const int pp = (int)(q % np); q /= np;
+        const int qq = take(q, nq);
+        const int pp = take(q, np);
         const int x = (int)(q % nax);
         const int k = (int)(q / nax);
         const double2 v = transpose ? in[(((i64)x * nk + k) * n + q0 + qq) * n + p0 + pp]
@@ -466,8 +478,8 @@ __global__ void k_axis_scatter(const double2 *in, double2 *out, int nax, int nk,
     const i64 N = (i64)nk * nax * np * nq;
     for (i64 t = blockIdx.x * (i64)blockDim.x + threadIdx.x; t < N; t += (i64)gridDim.x * blockDim.x) {
         i64 q = t;
-        const int qq = (int)(q % nq); q /= nq;
-        const int pp = (int)(q % np); q /= np;
+        const int qq = take(q, nq);
+        const int pp = take(q, np);
         const int x = (int)(q % nax);
         const int k = (int)(q / nax);
         const i64 dst = transpose ? (((i64)x * nk + k) * n + q0 + qq) * n + p0 + pp
@@ -509,8 +521,8 @@ __global__ void k_permute4(const double2 *in, double2 *out, KMesh km, int e0, in
         i64 q = t;
         int io[4], ko[4];
         for (int d = 3; d >= 0; --d) { io[d] = (int)(q % eo[d]); q /= eo[d]; }
-        ko[2] = (int)(q % nk); q /= nk;
-        ko[1] = (int)(q % nk); q /= nk;
+        ko[2] = take(q, nk);
+        ko[1] = take(q, nk);
         ko[0] = (int)q;
         ko[3] = km.sum3(-sg[3] * sg[0], ko[0], -sg[3] * sg[1], ko[1], -sg[3] * sg[2], ko[2]);
         int ii[4], ki[4];
@@ -539,11 +551,11 @@ __global__ void k_ring_matrix(const double2 *in, const double2 *fbe, const doubl
     const i64 n = (i64)nk * nk * nk * o * v * v * o;
     for (i64 t = blockIdx.x * (i64)blockDim.x + threadIdx.x; t < n; t += (i64)gridDim.x * blockDim.x) {
         i64 q = t;
-        const int i3 = (int)(q % e3); q /= e3;
-        const int i2 = (int)(q % e2); q /= e2;
-        const int e = (int)(q % v); q /= v;
-        const int m = (int)(q % o); q /= o;
-        const int k2 = (int)(q % nk); q /= nk;
+        const int i3 = take(q, e3);
+        const int i2 = take(q, e2);
+        const int e = take(q, v);
+        const int m = take(q, o);
+        const int k2 = take(q, nk);
         const int ke = (int)(q % nk);
         const int kmm = (int)(q / nk);
         // k_m + k_b = k_e + k_j
@@ -610,10 +622,10 @@ __global__ void k_antisym(const double2 *y, double2 *out, int R, KMesh km, int o
     for (i64 row = blockIdx.x; row < rows; row += gridDim.x) {
         // row = [r][ki][kj][ka][i][j], elements (a, b)
         i64 q = row;
-        const int j = (int)(q % o); q /= o;
-        const int i = (int)(q % o); q /= o;
-        const int ka = (int)(q % nk); q /= nk;
-        const int kj = (int)(q % nk); q /= nk;
+        const int j = take(q, o);
+        const int i = take(q, o);
+        const int ka = take(q, nk);
+        const int kj = take(q, nk);
         const int ki = (int)(q % nk);
         const i64 r = q / nk;
         const int kb = km.comb(ki, kj, ka);
@@ -660,8 +672,8 @@ __global__ void k_pp_in(const double2 *y, typename Cx<T>::type *Z, KMesh km, int
     for (i64 row = blockIdx.x; row < rows; row += gridDim.x) {
         // row indexes the block layout [blk][r][i][j], elements (a, b)
         i64 q = row;
-        const int j = (int)(q % o); q /= o;
-        const int i = (int)(q % o); q /= o;
+        const int j = take(q, o);
+        const int i = take(q, o);
         const int r = (int)(q % R);
         const i64 blk = q / R;
         const int ka = (int)(blk % nk), kj = (int)((blk / nk) % nk), ki = (int)(blk / (nk * nk));
@@ -685,7 +697,7 @@ template <typename T>
 hipError_t pp_in(const void *y, void *Z, KMesh km, int R, int o, int v, double scale, hipStream_t s) {
     const int nk = km.size();
     const i64 rows = (i64)nk * nk * nk * R * o * o;
-    hipLaunchKernelGGL(k_pp_in<T>, dim3(rows_grid(rows)), dim3(256), orbit_lds(v), s, (const double2 *)y,
+    hipLaunchKernelGGL(k_pp_in<T>, dim3(rows_grid(rows)), dim3(wave_rows(rows, v) ? 64 : 256), orbit_lds(v), s, (const double2 *)y,
                        (typename Cx<T>::type *)Z, km, R, o, v, scale);
     return hipGetLastError();
 }
@@ -758,9 +770,9 @@ __global__ void k_pair_transpose(const typename Cx<T>::type *in, typename Cx<T>:
     const i64 n = (i64)nk * nk * naux * m * m;
     for (i64 t = blockIdx.x * (i64)blockDim.x + threadIdx.x; t < n; t += (i64)gridDim.x * blockDim.x) {
         i64 q = t;
-        const int p = (int)(q % m); q /= m;
-        const int qq = (int)(q % m); q /= m;
-        const int Q = (int)(q % naux); q /= naux;
+        const int p = take(q, m);
+        const int qq = take(q, m);
+        const int Q = take(q, naux);
         const int k1 = (int)(q % nk);
         const int k2 = (int)(q / nk);
         // t = [k2][k1][Q][qq][p]
@@ -781,8 +793,8 @@ __global__ void k_slice_add(const double2 *in, double2 *out, int nk, int naux, i
     const i64 N = (i64)nk * nk * naux * np * nq;
     for (i64 t = blockIdx.x * (i64)blockDim.x + threadIdx.x; t < N; t += (i64)gridDim.x * blockDim.x) {
         i64 q = t;
-        const int qq = (int)(q % nq); q /= nq;
-        const int pp = (int)(q % np); q /= np;
+        const int qq = take(q, nq);
+        const int pp = take(q, np);
         const i64 dst = (q * n + p0 + pp) * n + q0 + qq;   // q = (k1 * nk + k2) * naux + Q
         const double2 a = out[dst], b = in[t];
         out[dst] = make_double2(a.x + b.x, a.y + b.y);
@@ -802,10 +814,10 @@ __global__ void k_outer_oovv(double2 *g, const double2 *x, const double2 *y, dou
     const i64 N = (i64)nk * nk * o * o * v * v;
     for (i64 t = blockIdx.x * (i64)blockDim.x + threadIdx.x; t < N; t += (i64)gridDim.x * blockDim.x) {
         i64 q = t;
-        const int b = (int)(q % v); q /= v;
-        const int a = (int)(q % v); q /= v;
-        const int j = (int)(q % o); q /= o;
-        const int i = (int)(q % o); q /= o;
+        const int b = take(q, v);
+        const int a = take(q, v);
+        const int j = take(q, o);
+        const int i = take(q, o);
         const int kj = (int)(q % nk);
         const int ki = (int)(q / nk);
         const double2 xv = x[((i64)ki * o + i) * v + a], yv = y[((i64)kj * o + j) * v + b];

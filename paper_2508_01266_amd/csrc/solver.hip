@@ -141,9 +141,9 @@ __global__ void k_precond(double2 *o1, double2 *o2, const double2 *i1, const dou
         double2 x;
         double2 *dst;
         if (t < (i64)R * n1) {
-            const int r = (int)(t / n1);
-            i64 q = t % n1;
-            const int a = (int)(q % nv); q /= nv;
+            const int r = (int)quot(t, n1);
+            i64 q = t - r * n1;
+            const int a = take(q, nv);
             const int i = (int)(q % no);
             const int k = (int)(q / no);
             d = ev[k * nv + a] - eo[k * no + i] - (omega ? omega[r] : 0.0);
@@ -151,13 +151,13 @@ __global__ void k_precond(double2 *o1, double2 *o2, const double2 *i1, const dou
             dst = o1 + t;
         } else {
             const i64 u = t - (i64)R * n1;
-            const int r = (int)(u / n2);
-            i64 q = u % n2;
-            const int b = (int)(q % nv); q /= nv;
-            const int a = (int)(q % nv); q /= nv;
-            const int j = (int)(q % no); q /= no;
-            const int i = (int)(q % no); q /= no;
-            const int ka = (int)(q % nk); q /= nk;
+            const int r = (int)quot(u, n2);
+            i64 q = u - r * n2;
+            const int b = take(q, nv);
+            const int a = take(q, nv);
+            const int j = take(q, no);
+            const int i = take(q, no);
+            const int ka = take(q, nk);
             const int kj = (int)(q % nk);
             const int ki = (int)(q / nk);
             const int kb = km.comb(ki, kj, ka);
@@ -232,9 +232,9 @@ __global__ void k_pack(V *o1, V *o2, const double2 *a1, const double2 *a2, const
             st2(o1, t, x);
         } else {
             const i64 u = t - N1;
-            const int r = (int)(u / n2p);
+            const int r = (int)quot(u, n2p);
             const i64 q = u - (i64)r * n2p;
-            const int p = (int)(q / blk);
+            const int p = (int)quot(q, blk);
             const i64 src = (i64)r * n2 + (i64)canon[p] * blk + (q - (i64)p * blk);
             double2 x = a2[src];
             if (b2) {
@@ -282,9 +282,9 @@ __global__ void k_unpack_precond(double2 *o1, double2 *o2, const V *i1, const V 
         double2 x;
         double2 *dst;
         if (t < (i64)R * n1) {
-            const int r = (int)(t / n1);
-            i64 q = t % n1;
-            const int a = (int)(q % nv); q /= nv;
+            const int r = (int)quot(t, n1);
+            i64 q = t - r * n1;
+            const int a = take(q, nv);
             const int i = (int)(q % no);
             const int k = (int)(q / no);
             d = ev[k * nv + a] - eo[k * no + i] - (omega ? omega[r] : 0.0);
@@ -292,12 +292,12 @@ __global__ void k_unpack_precond(double2 *o1, double2 *o2, const V *i1, const V 
             dst = o1 + t;
         } else {
             const i64 u = t - (i64)R * n1;
-            const int r = (int)(u / n2);
-            i64 q = u % n2;
-            const int b = (int)(q % nv); q /= nv;
-            const int a = (int)(q % nv); q /= nv;
-            const int j = (int)(q % no); q /= no;
-            const int i = (int)(q % no); q /= no;
+            const int r = (int)quot(u, n2);
+            i64 q = u - r * n2;
+            const int b = take(q, nv);
+            const int a = take(q, nv);
+            const int j = take(q, no);
+            const int i = take(q, no);
             const int f = (int)q;
             const int ka = f % nk, kj = (f / nk) % nk, ki = f / (nk * nk);
             const int kb = km.comb(ki, kj, ka);
