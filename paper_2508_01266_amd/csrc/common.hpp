@@ -142,7 +142,9 @@ struct GemmArgs {
     Strides Am, Ak, Bk, Bn, Cm, Cn;
     int aMfast, bNfast;  // tile-load thread maps: 1 = run along m (resp. n)
     int shape;           // tile: -1 automatic, else an index into kGroupTiles, or kSplitTile
-    int alt;             // unused (kept zero)
+    // +1 (-1): the jobs from upper_job of the full list on need only outputs whose row's leading digit (of a
+    // two-digit split) is below (above) their column's; tiles without any are skipped and not stored.  0: all
+    int upper, upper_job;
     double alpha_re, alpha_im;
     int beta;
     const i64 *offC;
@@ -161,6 +163,14 @@ struct GemmArgs {
                          // profiling); the launcher takes instances 2 (generic) and 3 (ladder) when
                          // sk is a triangle split
 };
+
+// whether the tm x tn tile at (m0, n0) of a job (index in the full list) has no output that is needed
+__host__ __device__ inline bool tile_skipped(const GemmArgs &g, int job, int m0, int n0, int tm, int tn) {
+    if (g.upper == 0 || job < g.upper_job) return false;
+    const int r0 = m0 / g.sm.d2, c0 = n0 / g.sn.d2;
+    const int r1 = ((m0 + tm < g.M ? m0 + tm : g.M) - 1) / g.sm.d2, c1 = ((n0 + tn < g.N ? n0 + tn : g.N) - 1) / g.sn.d2;
+    return g.upper > 0 ? r0 >= c1 : r1 <= c0;
+}
 
 template <typename T>
 hipError_t launch_gemm(const GemmArgs &g, hipStream_t s);

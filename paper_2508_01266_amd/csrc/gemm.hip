@@ -22,6 +22,7 @@ __global__ void __launch_bounds__(kTileThreads, 2) gemm_kernel(GemmArgs g) {
     const int job = blockIdx.y, split = blockIdx.z;
     const int tilesM = (g.M + TM - 1) / TM;
     const int m0 = (blockIdx.x % tilesM) * TM, n0 = (blockIdx.x / tilesM) * TN;
+    if (tile_skipped(g, g.job0 + job, m0, n0, TM, TN)) return;
     const int sb = g.segBeg[job], se = g.segBeg[job + 1];
     const i64 nsteps = (i64)(se - sb) * ((g.K + kGroupTK - 1) / kGroupTK);
     const int t0 = (int)(nsteps * split / g.ksplit), t1 = (int)(nsteps * (split + 1) / g.ksplit);

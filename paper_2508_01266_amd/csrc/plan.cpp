@@ -482,7 +482,6 @@ void raw_gemm(Program &P, GemmArgs g, const std::vector<i64> &offC, const std::v
     g.sm = split_magic(g.sm);
     g.sn = split_magic(g.sn);
     g.sk = split_magic(g.sk);
-    g.alt = 0;
     // split-K when the job x tile grid cannot fill the chip but the jobs have long reductions
     {
         const i64 tn = g.M <= 16 ? (g.N + 255) / 256 : (g.N + 63) / 64;
@@ -497,6 +496,14 @@ void raw_gemm(Program &P, GemmArgs g, const std::vector<i64> &offC, const std::v
         g.part = g.ksplit > 1 ? P.alloc((size_t)g.ksplit * g.njobs * g.M * g.N * sizeof(T) * 2) : nullptr;
     }
     P.last_flops = 8LL * g.M * g.N * g.K * (i64)segA.size();
+    if (g.upper) {                          // the tiles formed (counted as 64x64) of the jobs that skip some
+        const int j0 = std::min(g.upper_job, (int)offC.size());
+        i64 rows = 0;
+        for (int n0 = 0; n0 < g.N; n0 += 64)
+            for (int m0 = 0; m0 < g.M; m0 += 64)
+                if (!tile_skipped(g, g.upper_job, m0, n0, 64, 64)) rows += (i64)std::min(64, g.M - m0) * std::min(64, g.N - n0);
+        P.last_flops -= 8LL * ((i64)g.M * g.N - rows) * g.K * (segBeg.back() - segBeg[j0]);
+    }
     P.flops += P.last_flops;
     auto gp = std::make_shared<GemmArgs>(g);
     P.ops.push_back([gp](hipStream_t s) { return launch_gemm<T>(*gp, s); });

@@ -407,6 +407,7 @@ bool Program::make_grouped(size_t budget, bool keep) {
                     for (int s = 0; s < p.ksplit; ++s)
                         for (int n0 = 0; n0 < g.N; n0 += tn)
                             for (int m0 = 0; m0 < g.M; m0 += tm) {
+                                if (tile_skipped(g, (int)j, m0, n0, tm, tn)) continue;
                                 GroupItem it{};
                                 char *c = (char *)slabs[s == 0 ? p.slab : p.extra[s - 1]].p;
                                 it.C = c + go.offC[j] * esz;

@@ -256,12 +256,14 @@ __global__ void __launch_bounds__(NT, 2) gemm_split_kernel(GemmArgs g) {
     __shared__ SplitLds lds;
     const int job = blockIdx.y, split = blockIdx.z;
     const int tilesM = (g.M + STM - 1) / STM;
+    const int m0 = (blockIdx.x % tilesM) * STM, n0 = (blockIdx.x / tilesM) * STN;
+    if (tile_skipped(g, g.job0 + job, m0, n0, STM, STN)) return;
     const int sb = g.segBeg[job], se = g.segBeg[job + 1];
     const i64 nsteps = (i64)(se - sb) * ((g.K + STK - 1) / STK);
     const int tbeg = (int)(nsteps * split / g.ksplit), tend = (int)(nsteps * (split + 1) / g.ksplit);
     float2 *dense = g.ksplit > 1 ? reinterpret_cast<float2 *>(g.part) +
                                        ((i64)split * g.njobs_all + g.job0 + job) * g.M * g.N : nullptr;
-    split_tile<RUN>(g, lds, (blockIdx.x % tilesM) * STM, (blockIdx.x / tilesM) * STN, sb, tbeg, tend,
+    split_tile<RUN>(g, lds, m0, n0, sb, tbeg, tend,
                     g.jscale ? g.jscale[g.job0 + job] : 1.0f, g.beta, reinterpret_cast<float2 *>(g.C) + g.offC[job], dense);
 }
 
