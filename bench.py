@@ -42,8 +42,8 @@ LADDER_PATH_TEXT = {1: "ladder integrals rebuilt in LDS from the Cholesky vector
                     3: "ladder integral blocks built from the Cholesky vectors one momentum class at a time "
                        "in every application"}
 LADDER_KERNEL = {1: "ladder_kernel_pipe (one launch, integrals rebuilt in LDS)",
-                 2: "gemm_kernel<..., 1, ...> over the stored blocks (one launch)",
-                 3: "gemm_kernel<..., 1, ...> over the class-built blocks (one launch per momentum class)"}
+                 2: "gemm_split_kernel / gemm_kernel<..., 1, ...> over the stored blocks",
+                 3: "gemm_split_kernel / gemm_kernel<..., 1, ...> over the blocks of a batch of momentum classes"}
 
 
 def ladder_sources_sha(path):
@@ -51,13 +51,22 @@ def ladder_sources_sha(path):
     kernel (paths 2 and 3), with the shared header."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("ladder.hip" if path == 1 else "gemm.hip", "common.hpp"):
+    for f in ("ladder.hip",) if path == 1 else ("gemm.hip", "split.hip", "tile.hpp", "common.hpp"):
         with open(os.path.join(ROOT, "paper_2508_01266_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()
 
 
-PEAK = {"f32": 157.3, "f64": 78.6}          # MI355X dense matrix-core TFLOP/s
+PEAK = {"f32": 157.3, "f64": 78.6, "bf16": 2516.6}          # MI355X dense matrix-core TFLOP/s
+BF16_PRODUCTS = 6                           # bf16 products that form one fp32 product
+
+
+def f32_peak(executed, mfma):
+    """Matrix-core peak of the complex64 products, the instructions they run on and that pipe's peak:
+    products formed from six bf16 ones (most of the launches' work) or fp32 ones."""
+    if mfma > 0.5 * (1 + BF16_PRODUCTS) * executed:
+        return PEAK["bf16"] / BF16_PRODUCTS, "bf16, six products per fp32 one", PEAK["bf16"]
+    return PEAK["f32"], "fp32", PEAK["f32"]
 
 
 def sigma_alg_flops(nk, o, v):
@@ -425,6 +434,7 @@ def main():
     lad_exec64 = ctx.ladder_flops(nrhs, lr.FP64)
     lad_mfma = ctx.ladder_mfma_flops(nrhs, lr.FP32)
     achieved = lad_unique / lad_s / 1e12
+    peak32, peak32_on, pipe32 = f32_peak(lad_exec, lad_mfma)
     traffic = None
     tr = LADDER_TRAFFIC.get(path)
     if tr and args.workload == tr["workload"] and tr["sources_sha256"] == ladder_sources_sha(path):
@@ -447,15 +457,15 @@ def main():
                                f"in one sigma launch, complex64 on the matrix cores, {LADDER_PATH_TEXT[path]}",
                    "nk": nk, "nocc": o, "nvir": v, "naux": w.naux, "nrhs": nrhs,
                    "ladder_mode": args.ladder_mode, "ladder_path": path},
-        "roofline": {"bound": "mfma", "achieved": achieved, "peak": PEAK["f32"], "unit": "TFLOP/s",
-                     "frac": achieved / PEAK["f32"], "traffic": traffic, "kernel": LADDER_KERNEL[path],
+        "roofline": {"bound": "mfma", "achieved": achieved, "peak": peak32, "unit": "TFLOP/s", "peak_of": peak32_on,
+                     "frac": achieved / peak32, "traffic": traffic, "kernel": LADDER_KERNEL[path],
                      "work": "unique antisymmetric pairs (rows, outputs, inputs); integral rebuilds are overhead",
                      "unique_flops_per_step": lad_unique, "launches_per_step": lad_n,
                      "ladder_ms_avg": lad_s / lad_n * 1e3, "ladder_ms_per_step": lad_s * 1e3,
                      "build_ms_per_step": bld_s * 1e3,
-                     "frac_with_builds": lad_unique / (lad_s + bld_s) / 1e12 / PEAK["f32"],
-                     "executed_flops_per_step": lad_exec, "executed_frac": lad_exec / lad_s / 1e12 / PEAK["f32"],
-                     "mfma_flops_per_step": lad_mfma, "mfma_frac": lad_mfma / lad_s / 1e12 / PEAK["f32"],
+                     "frac_with_builds": lad_unique / (lad_s + bld_s) / 1e12 / peak32,
+                     "executed_flops_per_step": lad_exec, "executed_frac": lad_exec / lad_s / 1e12 / peak32,
+                     "mfma_flops_per_step": lad_mfma, "mfma_frac": lad_mfma / lad_s / 1e12 / pipe32,
                      "full_range_flops_per_step": lad, "full_range_tflops": lad / lad_s / 1e12},
         "fp64": {"value": alg / dt64 / 1e12, "ms_per_step": dt64 * 1e3, "steps": args.fp64_steps,
                  "ladder_path": path64, "ladder_ms_per_step": lad64_s * 1e3, "build_ms_per_step": bld64_s * 1e3,
@@ -488,13 +498,14 @@ def main():
         ctx2.set_autotune(not args.no_tune)
         s32, sl32, _, sb32 = time_sigma(ctx2, X1, X2, Y1, Y2, OM, lr.FP32, args.steps, args.warmup, torch)
         s64, sl64, _, sb64 = time_sigma(ctx2, X1, X2, Y1, Y2, OM, lr.FP64, args.fp64_steps, 1, torch)
+        p32, p32_on, _ = f32_peak(ctx2.ladder_flops(nrhs, lr.FP32), ctx2.ladder_mfma_flops(nrhs, lr.FP32))
         out[key] = {
-            "ladder_mode": mode,
+            "ladder_mode": mode, "ladder_peak": p32, "ladder_peak_of": p32_on,
             "ms_per_step": s32 * 1e3, "value": alg / s32 / 1e12, "ladder_ms_per_step": sl32 * 1e3,
             "build_ms_per_step": sb32 * 1e3,
-            "ladder_achieved": lad_unique / sl32 / 1e12, "ladder_frac": lad_unique / sl32 / 1e12 / PEAK["f32"],
-            "ladder_frac_with_builds": lad_unique / (sl32 + sb32) / 1e12 / PEAK["f32"],
-            "ladder_executed_frac": ctx2.ladder_flops(nrhs, lr.FP32) / sl32 / 1e12 / PEAK["f32"],
+            "ladder_achieved": lad_unique / sl32 / 1e12, "ladder_frac": lad_unique / sl32 / 1e12 / p32,
+            "ladder_frac_with_builds": lad_unique / (sl32 + sb32) / 1e12 / p32,
+            "ladder_executed_frac": ctx2.ladder_flops(nrhs, lr.FP32) / sl32 / 1e12 / p32,
             "fp64_ms_per_step": s64 * 1e3, "fp64_value": alg / s64 / 1e12, "fp64_ladder_ms_per_step": sl64 * 1e3,
             "fp64_build_ms_per_step": sb64 * 1e3,
             "fp64_ladder_frac": lad_unique / sl64 / 1e12 / PEAK["f64"],

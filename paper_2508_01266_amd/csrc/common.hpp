@@ -164,6 +164,16 @@ struct GemmArgs {
                          // sk is a triangle split
 };
 
+// Tile of workgroup x of a job: workgroups x, x + 8, ... run on one die and its L2, and take a contiguous run of
+// tiles, column tiles fastest, so that the column tiles of a row tile start together and share its operand (row
+// tiles fastest over all dies: the complex64 ring at Nk=5, o=8, v=40, 48 vectors 43.8 ms, so 42.6; at Nk=3, o=10,
+// v=60, 6 vectors, transposed 6.45 and 6.06).
+__device__ inline void tile_of(int x, int tilesM, int tilesN, int &tm, int &tn) {
+    const int T = tilesM * tilesN, die = x & 7, per = T >> 3, left = T & 7;
+    const int t = die * per + (die < left ? die : left) + (x >> 3);
+    tm = t / tilesN;
+    tn = t - tm * tilesN;
+}
 // whether the tm x tn tile at (m0, n0) of a job (index in the full list) has no output that is needed
 __host__ __device__ inline bool tile_skipped(const GemmArgs &g, int job, int m0, int n0, int tm, int tn) {
     if (g.upper == 0 || job < g.upper_job) return false;

@@ -21,7 +21,9 @@ __global__ void __launch_bounds__(kTileThreads, 2) gemm_kernel(GemmArgs g) {
     typedef typename Cx<T>::type C2;
     const int job = blockIdx.y, split = blockIdx.z;
     const int tilesM = (g.M + TM - 1) / TM;
-    const int m0 = (blockIdx.x % tilesM) * TM, n0 = (blockIdx.x / tilesM) * TN;
+    int tm, tn;
+    tile_of(blockIdx.x, tilesM, gridDim.x / tilesM, tm, tn);
+    const int m0 = tm * TM, n0 = tn * TN;
     if (tile_skipped(g, g.job0 + job, m0, n0, TM, TN)) return;
     const int sb = g.segBeg[job], se = g.segBeg[job + 1];
     const i64 nsteps = (i64)(se - sb) * ((g.K + kGroupTK - 1) / kGroupTK);

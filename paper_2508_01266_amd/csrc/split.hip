@@ -256,7 +256,9 @@ __global__ void __launch_bounds__(NT, 2) gemm_split_kernel(GemmArgs g) {
     __shared__ SplitLds lds;
     const int job = blockIdx.y, split = blockIdx.z;
     const int tilesM = (g.M + STM - 1) / STM;
-    const int m0 = (blockIdx.x % tilesM) * STM, n0 = (blockIdx.x / tilesM) * STN;
+    int tm, tn;
+    tile_of(blockIdx.x, tilesM, gridDim.x / tilesM, tm, tn);
+    const int m0 = tm * STM, n0 = tn * STN;
     if (tile_skipped(g, g.job0 + job, m0, n0, STM, STN)) return;
     const int sb = g.segBeg[job], se = g.segBeg[job + 1];
     const i64 nsteps = (i64)(se - sb) * ((g.K + STK - 1) / STK);
