@@ -291,11 +291,15 @@ bool Program::make_grouped(size_t budget, bool keep) {
             units[launch_of(p)] += (double)p.tiles * kGroupTiles[p.tile].frags * p.steps;
         }
         // a workgroup runs at most about half of its launch's average work per compute unit in one
-        // piece, and not less than 6 steps (a step of a small tile is shorter than starting one)
+        // piece, and not less than 6 steps (a step of a small tile is shorter than starting one).  Pieces longer
+        // than 48 steps are cut to a quarter of that, down to 48: with one or two pieces per compute unit the
+        // last ones run alone (a level of Nk=3, o=10, v=60, transposed: 678 pieces 1.59 ms, 1725 1.13; of Nk=5,
+        // o=8, v=40, complex128: 3.33 against 2.84).  Cut everywhere, Nk=3, o=4, v=20 takes 650 us against 583.
         for (int q : at[l]) {
             Prod &p = prods[q];
             if (p.alone) continue;
-            const double most = std::max(6.0, units[launch_of(p)] / 512);
+            const double all = units[launch_of(p)];
+            const double most = std::max(6.0, std::min(all / 512, std::max(48.0, all / 2048)));
             const double mine = (double)p.steps * kGroupTiles[p.tile].frags;
             i64 ks = (i64)std::ceil(mine / most);
             const i64 bytes = tens[slabs[p.slab].tensor].count * esz;
