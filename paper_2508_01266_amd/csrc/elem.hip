@@ -194,7 +194,9 @@ hipError_t inputs(const void *x1, const void *x2, const void *t1, void *o1, void
 // A = row0 - row1 - (row2 - row3)^T (transposes in (a, b)), handed to st(row, e, value).  The workgroup
 // takes the rows tile by tile: the differences row0 - row1 of tile (a, b) and row2 - row3 of tile (b, a)
 // go through LDS, so every element is read once, along its unit-stride index, and both A and -A^T are
-// written along theirs.  Bound by HBM.  (Reading the transposed elements from memory instead, twice,
+// written along theirs.  Where ka = kb rows 2 and 3 are rows 0 and 1: the tiles a0 <= b0 then make the whole
+// row, so that in every orbit an element is read and written in the step of one tile alone and `st` may write
+// the array that `ld` reads.  Bound by HBM.  (Reading the transposed elements from memory instead, twice,
 // ran at 3.6 TB/s on the batched complex64 output, v = 40, and below 1 TB/s at v = 60 with two summands,
 // whose rows do not stay in the L1 cache.)
 constexpr int kOrbTile = 32;
@@ -210,7 +212,8 @@ __device__ __forceinline__ void orbit_rows(double2 *lds, int v, bool two_pairs, 
     const int ts = orbit_tile(v), w = ts + 1;
     double2 *const ld0 = lds, *const ld1 = lds + ts * w;
     for (int a0 = 0; a0 < v; a0 += ts)
-        for (int b0 = 0; b0 < v; b0 += ts) {
+        for (int b0 = two_blocks ? 0 : a0; b0 < v; b0 += ts) {
+            const bool both = two_blocks || a0 != b0;
             const int na = min(ts, v - a0), nb = min(ts, v - b0), n = na * nb;
 #pragma unroll 4
             for (int e = threadIdx.x; e < n; e += blockDim.x) {
@@ -233,15 +236,16 @@ __device__ __forceinline__ void orbit_rows(double2 *lds, int v, bool two_pairs, 
                 st(0, at, a0 + a, b0 + b, z);
                 if (two_pairs) st(1, at, a0 + a, b0 + b, make_double2(-z.x, -z.y));
             }
-            if (two_blocks)
-    #pragma unroll 4
-            for (int e = threadIdx.x; e < n; e += blockDim.x) {
+            if (both) {
+#pragma unroll 4
+                for (int e = threadIdx.x; e < n; e += blockDim.x) {
                     const int b = e / na, a = e - b * na, at = (b0 + b) * v + a0 + a;
                     const double2 x = ld0[a * w + b], y = ld1[b * w + a];
                     const double2 z = make_double2(x.x - y.x, x.y - y.y);
                     st(2, at, a0 + a, b0 + b, make_double2(-z.x, -z.y));
                     if (two_pairs) st(3, at, a0 + a, b0 + b, z);
                 }
+            }
             __syncthreads();
         }
 }
@@ -281,11 +285,12 @@ __device__ __forceinline__ double2 slab_sum(const SlabList &l, i64 at) {
 //   y1[r][k][i][a] = s1[k][r][i][a] - omega_r x1[r][k][i][a];
 //   y2[r][ki,kj,ka][i][j][a][b] = scale * (P_ij P_ab Z)[ki,kj,ka][r][i][j][a][b] - omega_r * x2[r][...],
 // s1 and Z sums of arrays (NS of them in Z, or any number for NS = 0).  diag: the diagonal of
-// the one-body terms, (diag_a + diag_b - diag_i - diag_j) times x2_ijab (antisymmetric in both pairs), or with xs
-// a quarter of that times xs joins Z.  These are far the largest terms: they are added here, in double (in the ring
-// product with the other elements they double the rounding of a complex64 product's doubles, from 1.0e-7 to
-// 2.1e-7 at Nk=5, o=8, v=40), from x2 read for omega already (xs read besides, for the four rows: 8.8 against
-// 6.5 ms with 48 complex64 vectors of that size).  The workgroup of an orbit's first
+// the one-body terms joins Z, with xs as (diag_a + diag_b - diag_i - diag_j) / 4 times xs (antisymmetric in both
+// pairs), else as the products it stands for would form it from an x2 of any symmetry: 1/2 diag_b x_ijab in every
+// row, and - diag_j x_ijab on the unique pairs (ka, a) < (kb, b) alone.  These are far the largest terms: they are
+// added here, in double (in the products with the other elements they double the rounding of a
+// complex64 product's doubles, from 1.0e-7 to 2.1e-7 at Nk=5, o=8, v=40), from the elements of x2 that omega reads
+// again a moment later.  The workgroup of an orbit's first
 // row ((ki, i) <= (kj, j), ka <= kb) writes all of its distinct rows; the others return at once.
 template <typename T, int NS>
 __global__ void k_outputs(SlabList s1, SlabList zs, SlabList xs, const double2 *diag, const double2 *x1,
@@ -332,38 +337,36 @@ __global__ void k_outputs(SlabList s1, SlabList zs, SlabList xs, const double2 *
         const i64 yr[4] = {row * vv, yrow(kj, ki, ka, j, i), yrow(ki, kj, kb, i, j), yrow(kj, ki, kb, j, i)};
         const double w = omega ? omega[r] : 0.0;
         const double2 *const da = diag + ka * (o + v) + o, *const db = diag + kb * (o + v) + o;
-        double2 dij = make_double2(0, 0);
+        double2 di = make_double2(0, 0), dj = make_double2(0, 0);
         if (diag) {
-            const double2 di = diag[ki * (o + v) + i], dj = diag[kj * (o + v) + j];
-            dij = make_double2(di.x + dj.x, di.y + dj.y);
+            di = diag[ki * (o + v) + i];
+            dj = diag[kj * (o + v) + j];
         }
-        auto dpair = [&](int a, int b) {        // the same for the four rows
-            const double2 fa = da[a], fb = db[b];
-            return make_double2(fa.x + fb.x - dij.x, fa.y + fb.y - dij.y);
-        };
+        const double half = 0.5 / scale;
         orbit_rows(lds, v, pi != pj, ka != kb,
                    [&](int rw, int e, int a, int b) {
                        double2 z = slab_sum<T, NS>(zs, zr[rw] + e);
-                       if (xs.n) {
-                           const double2 x = slab_sum<T, 0>(xs, zr[rw] + e), d = dpair(a, b);
+                       if (diag && xs.n) {             // the same factor for the four rows
+                           const double2 x = slab_sum<T, 0>(xs, zr[rw] + e), fa = da[a], fb = db[b];
+                           const double2 d = make_double2(fa.x + fb.x - di.x - dj.x, fa.y + fb.y - di.y - dj.y);
                            z.x += 0.25 * (d.x * x.x - d.y * x.y);
                            z.y += 0.25 * (d.x * x.y + d.y * x.x);
+                       } else if (diag) {              // second virtual and second occupied index of the row
+                           const double2 x = x2[yr[rw] + e], fv = rw < 2 ? db[b] : da[a], fo = (rw & 1) ? di : dj;
+                           const double u = (rw < 2 ? ka < kb || a < b : ka == kb && b < a) ? 2 : 0;
+                           const double2 d = make_double2(half * (fv.x - u * fo.x), half * (fv.y - u * fo.y));
+                           z.x += d.x * x.x - d.y * x.y;
+                           z.y += d.x * x.y + d.y * x.x;
                        }
                        return z;
                    },
-                   [&](int rw, int e, int a, int b, double2 z) {
+                   [&](int rw, int e, int, int, double2 z) {
                        const i64 at = yr[rw] + e;
                        double2 out = make_double2(scale * z.x, scale * z.y);
-                       if (omega || (diag && !xs.n)) {
+                       if (omega) {
                            const double2 xv = x2[at];
-                           double2 d = make_double2(-w, 0);
-                           if (diag && !xs.n) {
-                               const double2 f = dpair(a, b);
-                               d.x += f.x;
-                               d.y = f.y;
-                           }
-                           out.x += d.x * xv.x - d.y * xv.y;
-                           out.y += d.x * xv.y + d.y * xv.x;
+                           out.x -= w * xv.x;
+                           out.y -= w * xv.y;
                        }
                        y2[at] = out;
                    });
@@ -568,7 +571,7 @@ __global__ void k_ring_matrix(const double2 *in, const double2 *fbe, const doubl
                 x.x += 0.5 * f.x;
                 x.y += 0.5 * f.y;
             }
-            if (b == e && m != j) {
+            if (fmj && b == e && m != j) {
                 const double2 f = fmj[((i64)kmm * o + m) * o + j];
                 x.x -= 0.5 * f.x;
                 x.y -= 0.5 * f.y;
@@ -597,6 +600,16 @@ hipError_t ring_matrix(const void *in, const void *fbe, const void *fmj, void *o
     const i64 n = (i64)nk * nk * nk * o * v * v * o;
     hipLaunchKernelGGL(k_ring_matrix, dim3(grid_for(n)), dim3(256), 0, s, (const double2 *)in, (const double2 *)fbe,
                        (const double2 *)fmj, (double2 *)out, km, o, v, transposed);
+    return hipGetLastError();
+}
+
+__global__ void k_off_diag(const double2 *in, double2 *out, int n, int m) {
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < n) out[t] = t % m == t / m % m ? make_double2(0, 0) : in[t];
+}
+hipError_t off_diag(const void *in, void *out, int nk, int m, hipStream_t s) {
+    const int n = nk * m * m;
+    hipLaunchKernelGGL(k_off_diag, dim3((n + 255) / 256), dim3(256), 0, s, (const double2 *)in, (double2 *)out, n, m);
     return hipGetLastError();
 }
 

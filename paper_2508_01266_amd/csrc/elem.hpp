@@ -13,8 +13,9 @@ hipError_t tau_like(const void *x1, const void *x2, const void *t1, void *out, K
 template <typename T>
 hipError_t inputs(const void *x1, const void *x2, const void *t1, void *o1, void *o2, void *dtau, KMesh km, int R,
                   int o, int v, double scale, hipStream_t s);
-// y1 = s1 - omega x1, y2 = scale P(ij)P(ab) Z + (D - omega) x2 (caller layout; omega may be null), D = diag_a + diag_b
-// - diag_i - diag_j (diag: complex128 [nk][o + v], null for D = 0); with X.n: D X / 4 added to Z instead
+// y1 = s1 - omega x1, y2 = scale P(ij)P(ab) (Z + D) - omega x2 (caller layout; omega may be null), D_ijab =
+// diag_b x_ijab / 2 - diag_j x_ijab (the second for (ka, a) < (kb, b) alone), x = x2 / scale, or with X.n
+// (diag_a + diag_b - diag_i - diag_j) / 4 X_ijab, X antisymmetric (diag: complex128 [nk][o + v], null for D = 0)
 template <typename T>
 hipError_t outputs(const SlabList &s1, const SlabList &Z, const SlabList &X, const void *diag, const void *x1,
                    const void *x2, void *y1, void *y2, const double *omega, KMesh km, int R, int o, int v,
@@ -38,11 +39,13 @@ hipError_t antisym(const void *y, void *out, int R, KMesh km, int o, int v, doub
 // four-index complex128 permutation, scaled: output dim d = input dim perm[d]; output momentum signs sg_out
 hipError_t permute4(const void *in, void *out, KMesh km, const int *ext_in, const int *perm, const int *sg_out,
                     double scale, hipStream_t s);
-// W-bar in the layouts of the ring products, with the off-diagonal one-body terms of x2: out[m][e][b][j]
+// W-bar in the layouts of the ring products, with off-diagonal one-body terms of x2: out[m][e][b][j]
 // (transposed: [m][e][j][b]) = in[m][b][e][j] + delta_mj fbe[b][e] / 2 (b != e) - delta_be fmj[m][j] / 2 (m != j)
-// (complex128; fbe, fmj k-diagonal)
+// (complex128; fbe, fmj k-diagonal; fmj may be null)
 hipError_t ring_matrix(const void *in, const void *fbe, const void *fmj, void *out, KMesh km, int o, int v,
                        int transposed, hipStream_t s);
+// out[k] = in[k] (complex128 [nk][m][m]) with a zero diagonal
+hipError_t off_diag(const void *in, void *out, int nk, int m, hipStream_t s);
 // diag[k] = the diagonals of fmj and fbe (complex128 [nk][o + v])
 hipError_t pair_diag(const void *fbe, const void *fmj, void *diag, int nk, int o, int v, hipStream_t s);
 template <typename T>

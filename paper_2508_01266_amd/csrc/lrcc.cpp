@@ -67,6 +67,7 @@ struct State {
     KT fov, t1, t2, tau;
     KT g_oovv, g_ooov, g_ovov, g_ovvv, g_ovoo;
     KT Fae, Fmi, Fme, Fbe, Fmj, Fg, Wp, Wbar, S, U, H;
+    KT Fmj0;                                // Fbar_mj without its diagonal
     KT WbarT;                               // W-bar with (b, j) as [j][b], for the transposed ring product
     void *La = nullptr, *Lb = nullptr;      // dressed virtual Cholesky slices (ladder)
     void *LaT = nullptr, *LbT = nullptr;    // pair-transposed copies (adjoint ladder)
@@ -530,6 +531,11 @@ void build_state(lrcc_ctx *c) {
     S.Fmj = alloc_kt<double>(c, m, "oo");
     kt_copy<double>(P, S.Fmj, S.Fmi);
     contract<double>(P, S.Fmj, "mj", t1, "je", S.Fme, "me", 0.5);
+    S.Fmj0 = alloc_kt<double>(c, m, "oo");
+    {
+        const void *src = S.Fmj.p;
+        writes(S.Fmj0.p, S.Fmj0.count(), {src}, [=](hipStream_t s, void *d) { return off_diag(src, d, nk, o, s); });
+    }
     // W'_mnij = <mn||ij> + P(ij) t_je <mn||ie> + 1/2 tau_ijef <mn||ef>
     S.Wp = alloc_kt<double>(c, m, "oooo");
     kt_copy<double>(P, S.Wp, oooo);
@@ -553,14 +559,17 @@ void build_state(lrcc_ctx *c) {
         // Ring layout [m][e][b][j]: the (b,j) columns of the ring product become contiguous.  The one-body
         // terms of x2, 1/2 x_ijae Fbar_be - 1/2 x_imab Fbar_mj, are the ring product of
         //   delta_mj Fbar_be / 2 - delta_be Fbar_mj / 2
-        // in the blocks k_m = k_j, so the layout step adds its off-diagonal elements (b != e, m != j) here, the
-        // diagonal is added to the outputs, and no passes over Z are made for them (Nk=5, o=8, v=40: 5.6 of 120 ms with 48 complex64 vectors, 3.3 of 79.7
-        // with 12 complex128 ones)
+        // in the blocks k_m = k_j, so the layout step adds off-diagonal elements (b != e, m != j) here, the
+        // diagonal is added to the outputs, and fewer passes over Z are made for them (Nk=5, o=8, v=40, both
+        // terms: 5.6 of 120 ms with 48 complex64 vectors, 3.3 of 79.7 with 12 complex128 ones).  Forward, the
+        // Fbar_mj term stays a product: it reads the unique (a, b) pairs of x2, which for an x2 that is not
+        // antisymmetric is not what the ring would read.  The transposed product acts on the antisymmetric part
+        // of z2, so its layout carries both.
         KT wr = alloc_kt<double>(c, m, "ovvo", 0, {1, -1, 1, -1});
         const void *src = S.Wbar.p, *fbe = S.Fbe.p, *fmj = S.Fmj.p;
         const KMesh km = c->km;
-        writes(wr.p, wr.count(), {src, fbe, fmj}, [=](hipStream_t s, void *d) {
-            return ring_matrix(src, fbe, fmj, d, km, o, v, 0, s);
+        writes(wr.p, wr.count(), {src, fbe}, [=](hipStream_t s, void *d) {
+            return ring_matrix(src, fbe, nullptr, d, km, o, v, 0, s);
         });
         // [m][e][j][b]: the transposed ring product sums over (j, b), contiguous in both operands with this
         // layout; from the other one each 16 bytes come from a 128-byte line of their own (Nk=5, o=8, v=40,
@@ -672,7 +681,7 @@ void build_state(lrcc_ctx *c) {
     cv(F.fov, S.fov); cv(F.t1, S.t1); cv(F.t2, S.t2); cv(F.tau, S.tau);
     cv(F.g_oovv, S.g_oovv); cv(F.g_ooov, S.g_ooov); cv(F.g_ovov, S.g_ovov); cv(F.g_ovvv, S.g_ovvv);
     cv(F.g_ovoo, S.g_ovoo);
-    cv(F.Fae, S.Fae); cv(F.Fmi, S.Fmi); cv(F.Fme, S.Fme);
+    cv(F.Fae, S.Fae); cv(F.Fmi, S.Fmi); cv(F.Fme, S.Fme); cv(F.Fmj0, S.Fmj0);
     cv(F.Fg, S.Fg); cv(F.Wp, S.Wp); cv(F.Wbar, S.Wbar); cv(F.WbarT, S.WbarT); cv(F.S, S.S);
     cv(F.H, S.H);
     F.dpair = F.mem.get((size_t)nk * n * 16);
@@ -851,6 +860,7 @@ struct SymOp {
     std::string tpack;  // the same for the transposed product of the active operand
     KT Bt;              // B in another layout, read by the transposed product of A (null: B itself)
     std::string btl;
+    bool fwd_only = false;   // transposed, part of another term
 };
 
 struct SigmaGraph {
@@ -961,10 +971,11 @@ SigmaGraph record_sigma(lrcc_ctx *c, State<T> &S, int R, DevMem &wm, bool full =
     // operands are antisymmetric in a summed pair, or whose output pair reaches sigma2 (or the
     // transposed output) only antisymmetrised, run on unique pairs (pack / transposed pack: see
     // contract); dtau_bar's (e, f) pair is read unsymmetrised and is never packed.
-    // (with the full operator, W-bar and the output step carry the one-body terms of x2: see W-bar's layout)
+    // (with the full operator, W-bar and the output step carry one-body terms of x2: see W-bar's layout)
     if (!full) con(Z, "Rijab", x2, "Rijae", S.Fbe, "be", 0.5, false);
     con(Z, "Rijab", t2, "ijae", dFbe, "Rbe", 0.5, !full);
-    if (!full) con(Z, "Rijab", x2, "Rimab", S.Fmj, "mj", -0.5, true, "ab", "", "ab");
+    con(Z, "Rijab", x2, "Rimab", full ? S.Fmj0 : S.Fmj, "mj", -0.5, true, "ab", "", "ab");
+    G.ops.back().fwd_only = full;
     con(Z, "Rijab", t2, "imab", dFmj, "Rmj", -0.5, true, "ab", "", "ab");
     if (!full) return G;  // one-body (perturbation) operator: no two-electron terms
     {
@@ -982,7 +993,7 @@ SigmaGraph record_sigma(lrcc_ctx *c, State<T> &S, int R, DevMem &wm, bool full =
     con(Zmn, "Rijmn", dtau, "Rijef", S.g_oovv, "mnef", 1.0, false, "ijmnef", "im", "ijmn");
     con(Z, "Rijab", Zmn, "Rijmn", t2, "mnab", 1.0 / 16, true, "ijabmn", "", "ab");
     con(Z, "Rijab", S.Wp, "mnij", dtau, "Rmnab", 1.0 / 8, true, "ijabmn", "", "mnij");
-    // ring terms (P(ij)P(ab)), with the one-body terms of x2
+    // ring terms (P(ij)P(ab)), with one-body terms of x2
     con(Z, "Rijab", x2, "Rimae", S.Wbar, "mebj", 1.0);
     G.ops.back().Bt = S.WbarT;
     G.ops.back().btl = "mejb";
@@ -1267,6 +1278,7 @@ void emit_reverse_sweep(lrcc_ctx *c, State<T> &S, int R, const SigmaGraph &G, Pr
         const SymOp &op = *it;
         switch (op.kind) {
         case SymOp::CON: {
+            if (op.fwd_only) break;
             const std::string tp = c->pack_pairs ? op.tpack : "";
             if (op.actA)
                 contract<T>(*P, op.A, op.al, op.C, op.cl, op.Bt.p ? op.Bt : op.B, op.Bt.p ? op.btl : op.bl, op.alpha,
@@ -2997,7 +3009,7 @@ const KT *bar_of(lrcc_ctx *c, const HamBar &B, const KT &t) {
     const State<double> &S = c->s64;
     const std::pair<const void *, const KT *> map[] = {
         {S.fov.p, &B.fov}, {S.Fae.p, &B.Fae}, {S.Fmi.p, &B.Fmi}, {S.Fme.p, &B.Fme}, {S.Fg.p, &B.Fg},
-        {S.Wp.p, &B.Wp}, {S.Wbar.p, &B.Wbar}, {S.S.p, &B.S},
+        {S.Fmj0.p, &B.Fmj}, {S.Wp.p, &B.Wp}, {S.Wbar.p, &B.Wbar}, {S.S.p, &B.S},
         {S.H.p, &B.H}, {c->g_oovv.p, &B.oovv}, {c->g_ooov.p, &B.ooov},
         {c->g_ovov.p, &B.ovov}, {c->g_ovvv.p, &B.ovvv}};
     for (const auto &m : map)
@@ -3103,9 +3115,8 @@ Program *build_param_vjp(lrcc_ctx *c, HamBar &B, DevMem &wm) {
             ladder_param_vjp(c, *P, f.A, a.C, f.alpha.real(), S.La, S.Lb, B.La, B.Lb, R);
         }
     }
-    // the one-body terms of x2, which W-bar carries in the product (B.Wbar is W-bar's without them)
+    // x2 Fbar_be, which W-bar carries in the product (B.Wbar is W-bar's without it)
     contract<double>(*P, B.Fbe, "be", Gf.x2, "Rijae", Ga.Z, "Rijab", 0.5, true);
-    contract<double>(*P, B.Fmj, "mj", Gf.x2, "Rimab", Ga.Z, "Rijab", -0.5, true);
     return P;
 }
 
