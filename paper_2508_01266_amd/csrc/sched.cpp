@@ -315,9 +315,11 @@ bool Program::make_grouped(size_t budget, bool keep) {
         }
     }
     // ---- storage.  A tensor read as an operand needs its slabs summed into its buffer unless it is one
-    // slab; the output steps read the slabs themselves.  The first slab lives in the tensor's buffer where
-    // no sum goes there, or where its writer stores every element again in each run and nobody else
-    // counts it on its own
+    // slab; the output steps read the slabs themselves.  The first slab lives in the tensor's buffer where its
+    // writer stores every element again in each run and no sum goes there that another tensor does not count;
+    // or, stored in part, where it is the tensor's only slab.  A run of the program op by op leaves the
+    // tensor's whole value in that buffer: beside other slabs, elements that no writer of this one stores
+    // would be counted twice by the next grouped run
     std::vector<std::vector<int>> parts(tens.size());
     for (size_t t = 0; t < tens.size(); ++t)
         for (int s : tens[t].parts) {
@@ -362,7 +364,7 @@ bool Program::make_grouped(size_t budget, bool keep) {
     for (size_t t = 0; t < tens.size(); ++t) {
         if (tens[t].own.empty()) continue;
         Slab &s0 = slabs[tens[t].own[0]];
-        if (!need_sum[t] || (s0.all && !exposed[t])) s0.p = tens[t].p;
+        if (s0.all ? !need_sum[t] || !exposed[t] : !need_sum[t] && parts[t].size() == 1) s0.p = tens[t].p;
     }
     for (Slab &s : slabs)
         if (!s.p) extra_bytes += (size_t)(tens[s.tensor].count * esz);

@@ -1,0 +1,129 @@
+// Small recorded programs for the grouped form (Program::group): their layout in a dry run, and on a device their
+// values when the same program runs grouped, op by op and grouped again.  grouped_programs NAME [run]
+#include <hip/hip_runtime.h>
+
+#include <complex>
+#include <cstdio>
+#include <cstring>
+#include <string>
+
+#include "elem.hpp"
+#include "plan.hpp"
+
+using namespace lrcc;
+typedef std::complex<double> cd;
+
+namespace {
+
+constexpr int kM = 8, kN = 8, kK = 8, kBlocks = 4;
+constexpr i64 kBlock = (i64)kM * kN;
+bool g_run = false;
+
+struct Array {
+    void *p = nullptr;
+    std::vector<cd> h;
+    explicit Array(i64 n, int seed = 0) : h(n) {
+        for (i64 i = 0; i < n; ++i) h[i] = seed ? cd((i * seed) % 7 - 3, (i * (seed + 4)) % 5 - 2) : cd(1e30, 1e30);
+        p = dev_alloc(n * 16);
+        if (g_run && hipMemcpy(p, h.data(), n * 16, hipMemcpyHostToDevice) != hipSuccess) std::exit(3);
+    }
+};
+
+std::vector<cd> read(const void *p, i64 n) {
+    std::vector<cd> v(n);
+    if (hipMemcpy(v.data(), p, n * 16, hipMemcpyDeviceToHost) != hipSuccess) std::exit(3);
+    return v;
+}
+
+void zero(Program &P, void *p, i64 n) {
+    P.ops.push_back([=](hipStream_t s) { return zero_fill<double>(p, n, s); });
+    P.node(Node::ZERO, {}, p, n);
+}
+
+// C += A B for the given blocks (A, B: one kM x kK and one kK x kN matrix, C: kBlocks blocks)
+void product(Program &P, const Array &A, const Array &B, void *C, std::vector<i64> blocks) {
+    GemmArgs g{};
+    g.shape = -1;
+    g.A = A.p; g.B = B.p; g.C = C;
+    g.M = kM; g.N = kN; g.K = kK;
+    g.sm = Split{1, kM}; g.sn = Split{1, kN}; g.sk = Split{1, kK};
+    g.Am = Strides{{0, 0, kK}}; g.Ak = Strides{{0, 0, 1}};
+    g.Bk = Strides{{0, 0, kN}}; g.Bn = Strides{{0, 0, 1}};
+    g.Cm = Strides{{0, 0, kN}}; g.Cn = Strides{{0, 0, 1}};
+    g.bNfast = 1;
+    g.alpha_re = 1;
+    g.beta = 1;
+    std::vector<i64> off, zeros(blocks.size(), 0);
+    std::vector<int> beg{0};
+    for (i64 b : blocks) { off.push_back(b * kBlock); beg.push_back((int)off.size()); }
+    raw_gemm<double>(P, g, off, beg, zeros, zeros, (i64)kM * kK, (i64)kK * kN, kBlocks * kBlock);
+}
+
+std::vector<SlabList> g_lists;       // what the output step of the last run read
+std::vector<cd> g_out;
+
+void output(Program &P, void *Z, i64 n) {
+    auto sum = [n](const SlabList &l) {
+        g_lists.push_back(l);
+        if (!g_run) return hipSuccess;
+        if (hipDeviceSynchronize() != hipSuccess) return hipErrorUnknown;
+        g_out.assign(n, cd(0, 0));
+        for (int q = 0; q < l.n; ++q) {
+            const std::vector<cd> v = read(l.p[q], n);
+            for (i64 i = 0; i < n; ++i) g_out[i] += v[i];
+        }
+        return hipSuccess;
+    };
+    P.ops.push_back([=](hipStream_t) { return sum(one_slab(Z)); });
+    P.node(Node::OUT, {Z}, nullptr, n).from = [=](hipStream_t, const std::vector<SlabList> &l) { return sum(l[0]); };
+}
+
+// Z from a product over half of its blocks and two over all: three arrays, the first stored in part
+int partial() {
+    const Array A(kM * kK, 3), B(kK * kN, 5), C(kM * kK, 2), Z(kBlocks * kBlock);
+    Program P;
+    zero(P, Z.p, kBlocks * kBlock);
+    product(P, A, B, Z.p, {0, 1});
+    product(P, C, B, Z.p, {0, 1, 2, 3});
+    product(P, A, B, Z.p, {0, 1, 2, 3});
+    output(P, Z.p, kBlocks * kBlock);
+    if (!P.group<double>((size_t)1 << 20)) { std::printf("not grouped\n"); return 1; }
+    g_lists.clear();
+    if (!g_run) {
+        (void)P.grouped.back().fn(nullptr);
+        const SlabList &l = g_lists.at(0);
+        std::printf("arrays %d\n", l.n);
+        for (int q = 0; q < l.n; ++q)
+            if (l.n > 1 && l.p[q] == Z.p) { std::printf("an array stored in part is the tensor's own buffer\n"); return 1; }
+        return 0;
+    }
+    std::vector<cd> ref(kBlocks * kBlock);
+    for (i64 b = 0; b < kBlocks; ++b)
+        for (int m = 0; m < kM; ++m)
+            for (int n = 0; n < kN; ++n) {
+                cd s = 0;
+                for (int k = 0; k < kK; ++k)
+                    s += (C.h[m * kK + k] + A.h[m * kK + k] * (b < 2 ? 2.0 : 1.0)) * B.h[k * kN + n];
+                ref[b * kBlock + m * kN + n] = s;
+            }
+    int bad = 0;
+    for (int form = 0; form < 4; ++form) {
+        P.use_grouped = form % 2 == 0;
+        if (P.run(nullptr, nullptr) != hipSuccess) return 3;
+        const bool same = g_out == ref;          // small whole numbers: every sum is exact
+        std::printf("%s: %s\n", P.use_grouped ? "grouped" : "op by op", same ? "ok" : "wrong");
+        bad += !same;
+    }
+    return bad ? 1 : 0;
+}
+
+}  // namespace
+
+int main(int argc, char **argv) {
+    if (argc < 2) return 2;
+    const std::string name = argv[1];
+    g_run = argc > 2 && !std::strcmp(argv[2], "run");
+    g_dry_run = !g_run;
+    if (name == "partial") return partial();
+    return 2;
+}

@@ -1,0 +1,9 @@
+"""Layout of the grouped form of small recorded programs (dry run, no device)."""
+from tests.grouped_cases import run
+
+
+def test_array_stored_in_part_is_not_the_tensors_buffer(tmp_path):
+    """The op-by-op form leaves the whole sum in the tensor's buffer, which a grouped run of the same program
+    would add again wherever the array there is not stored."""
+    rc, out = run(tmp_path, "partial")
+    assert rc == 0 and "arrays 3" in out, out
