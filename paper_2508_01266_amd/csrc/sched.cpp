@@ -357,6 +357,9 @@ bool Program::make_grouped(size_t budget, bool keep) {
             if (!need_sum[t] && out_list(t).size() > (size_t)kMaxSlabs) need_sum[t] = 1;
         }
     }
+    // a sum follows the level of its last writer: one of arrays that no op writes has none
+    for (size_t t = 0; t < tens.size(); ++t)
+        if (need_sum[t] && last_of(tens[t]) < 0) return false;
     for (size_t t = 0; t < tens.size(); ++t)
         if (need_sum[t])
             for (int s : parts[t])

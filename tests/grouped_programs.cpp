@@ -117,6 +117,32 @@ int partial() {
     return bad ? 1 : 0;
 }
 
+void copy(Program &P, void *d, const void *src, i64 n) {
+    P.ops.push_back([=](hipStream_t s) { return hipMemcpyAsync(d, src, n * 16, hipMemcpyDeviceToDevice, s); });
+    P.node(Node::COPY, {src}, d, n);
+}
+void add(Program &P, void *d, const void *src, i64 n) {
+    P.ops.push_back([=](hipStream_t s) { return add_inplace<double>(d, src, n, s); });
+    P.node(Node::ADD, {src}, d, n);
+}
+
+// T = C1 + C2, arrays that no op writes, read by a product
+int constants() {
+    const i64 n = kBlocks * kBlock;
+    const Array A(kM * kK, 3), C1(kK * kN, 2), C2(kK * kN, 5), T(kK * kN), Z(n);
+    Program P;
+    copy(P, T.p, C1.p, kK * kN);
+    add(P, T.p, C2.p, kK * kN);
+    zero(P, Z.p, n);
+    product(P, A, T, Z.p, {0, 1, 2, 3});
+    output(P, Z.p, n);
+    const bool made = P.group<double>((size_t)1 << 20);
+    bool sums = false;
+    for (const auto &l : P.grouped) sums = sums || l.name.find("sums") != std::string::npos;
+    std::printf("%s\n", !made ? "not grouped" : sums ? "summed" : "grouped, the operand is never formed");
+    return made && !sums ? 1 : 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -125,5 +151,6 @@ int main(int argc, char **argv) {
     g_run = argc > 2 && !std::strcmp(argv[2], "run");
     g_dry_run = !g_run;
     if (name == "partial") return partial();
+    if (name == "constants") return constants();
     return 2;
 }

@@ -7,3 +7,9 @@ def test_array_stored_in_part_is_not_the_tensors_buffer(tmp_path):
     would add again wherever the array there is not stored."""
     rc, out = run(tmp_path, "partial")
     assert rc == 0 and "arrays 3" in out, out
+
+
+def test_sum_of_constant_arrays_is_formed(tmp_path):
+    """A tensor of copies of arrays that no op writes, read as an operand."""
+    rc, out = run(tmp_path, "constants")
+    assert rc == 0, out
