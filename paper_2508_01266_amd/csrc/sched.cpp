@@ -260,6 +260,15 @@ bool Program::make_grouped(size_t budget, bool keep) {
             others.push_back({i, lvl, pick, beta != 0});
         }
     }
+    // a tensor that others read and that nothing is added to: cleared in every run
+    for (size_t t = 0; keep && t < tens.size(); ++t) {
+        if (!tens[t].parts.empty()) continue;
+        const int s = new_slab((int)t);
+        slabs[s].all = true;
+        slabs[s].last = 0;
+        tens[t].own = tens[t].parts = {s};
+        others.push_back({0, 0, s, false, true});
+    }
     int nlev = 0;
     for (const Prod &p : prods) nlev = std::max(nlev, p.level + 1);
     for (const Other &p : others) nlev = std::max(nlev, p.level + 1);

@@ -143,6 +143,21 @@ int constants() {
     return made && !sums ? 1 : 0;
 }
 
+// T is cleared and nothing is added to it (a product without jobs); other programs read it
+int cleared() {
+    const i64 n = kBlocks * kBlock;
+    const Array A(kM * kK, 3), B(kK * kN, 5), T(n), Z(n);
+    Program P;
+    zero(P, T.p, n);
+    zero(P, Z.p, n);
+    product(P, A, B, Z.p, {0, 1, 2, 3});
+    const bool made = P.group<double>((size_t)1 << 20, true);
+    bool clears = false;
+    for (const auto &l : P.grouped) clears = clears || l.name == "clear";
+    std::printf("%s\n", !made ? "not grouped" : clears ? "cleared" : "grouped, the tensor is never cleared");
+    return made && !clears ? 1 : 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -152,5 +167,6 @@ int main(int argc, char **argv) {
     g_dry_run = !g_run;
     if (name == "partial") return partial();
     if (name == "constants") return constants();
+    if (name == "cleared") return cleared();
     return 2;
 }

@@ -13,3 +13,9 @@ def test_sum_of_constant_arrays_is_formed(tmp_path):
     """A tensor of copies of arrays that no op writes, read as an operand."""
     rc, out = run(tmp_path, "constants")
     assert rc == 0, out
+
+
+def test_tensor_that_is_only_cleared(tmp_path):
+    """A tensor with a clear and no other writer, read by other programs."""
+    rc, out = run(tmp_path, "cleared")
+    assert rc == 0, out
