@@ -257,7 +257,8 @@ lrcc_status lrcc_measure_peaks(int hip_device, double *mfma_f32_tflops, double *
 /* Host-only validation of the launch plans for a problem size: records every
  * kernel of lrcc_set_hamiltonian, lrcc_set_amplitudes and lrcc_apply_sigma (FP64
  * and FP32, nrhs right-hand sides) without a device, checking that every
- * address each matrix-core GEMM can form lies inside its operands.  Needs no
+ * address each matrix-core GEMM can form lies inside its operands, and that the tensors
+ * of grouped programs fit their arrays.  Needs no
  * GPU and allocates no device memory.  On failure writes a message into msg
  * (msglen bytes, may be NULL) and returns LRCC_E_ARG (or LRCC_E_OOM). */
 lrcc_status lrcc_plan_check(int nk, int nocc, int nvir, int naux, int nrhs, char *msg, int msglen);

@@ -658,6 +658,7 @@ void build_state(lrcc_ctx *c) {
         auto diag = [&](const KT &t, void *out, int m) {
             void *src = t.p;
             writes(out, (i64)nk * m, {src}, [=](hipStream_t s, void *d) { return diag_real(src, (double *)d, nk, m, s); });
+            P.nodes.back().real = true;
         };
         diag(S.Fmi, S.d_o1, o);
         diag(S.Fae, S.d_v1, v);
@@ -4612,7 +4613,7 @@ lrcc_status lrcc_plan_check_mesh(int n0, int n1, int n2, int nocc, int nvir, int
         return LRCC_E_ARG;
     const int nk = n0 * n1 * n2;
     lrcc_status st = LRCC_OK;
-    g_dry_run = true;
+    dry_run(true);
     try {
         lrcc_ctx c;
         c.km = KMesh{n0, n1, n2};
@@ -4652,7 +4653,7 @@ lrcc_status lrcc_plan_check_mesh(int n0, int n1, int n2, int nocc, int nvir, int
         st = LRCC_E_ARG;
         if (msg && msglen > 0) snprintf(msg, msglen, "%s", e.what());
     }
-    g_dry_run = false;
+    dry_run(false);
     return st;
 }
 

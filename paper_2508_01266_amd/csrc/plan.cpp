@@ -22,6 +22,16 @@ bool g_dry_run = false;
 
 namespace {
 std::uintptr_t g_fake_next = 0x100000;
+std::map<const void *, size_t> g_fake_bytes;          // sizes of the placeholders of a dry run
+}
+
+void dry_run(bool on) {
+    g_dry_run = on;
+    g_fake_bytes.clear();
+}
+size_t dry_bytes(const void *p) {
+    auto it = g_fake_bytes.find(p);
+    return it == g_fake_bytes.end() ? SIZE_MAX : it->second;
 }
 
 namespace {
@@ -67,6 +77,7 @@ void *dev_alloc(size_t bytes) {
     }
     if (g_dry_run) {
         void *p = reinterpret_cast<void *>(g_fake_next);
+        g_fake_bytes[p] = bytes;
         g_fake_next += (bytes + 4095) / 4096 * 4096 + 4096;
         return p;
     }

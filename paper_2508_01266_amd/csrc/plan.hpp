@@ -78,6 +78,7 @@ struct Node {
     void *write = nullptr;            // tensor written (null for OUT)
     i64 count = 0;                    // its elements
     bool acc = false, full = true;
+    bool real = false;                // real numbers, half the size: one WRITE, in their own buffer only
     // WRITE: the op writing to dst, or adding to it.  OUT: the op reading, for each of its reads, the sum of
     // the arrays that make it up
     std::function<hipError_t(hipStream_t, void *dst, bool acc)> write_to;
@@ -201,5 +202,8 @@ void raw_gemm(Program &P, GemmArgs g, const std::vector<i64> &offC, const std::v
 // Placeholder-or-real device allocation honouring g_dry_run.
 void *dev_alloc(size_t bytes);
 void dev_free(void *p);
+// starts (ends) a dry run; bytes of the placeholder at p in it (SIZE_MAX: not the start of one)
+void dry_run(bool on);
+size_t dry_bytes(const void *p);
 
 }  // namespace lrcc

@@ -32,6 +32,7 @@ struct Tensor {
     std::vector<int> parts;              // own slabs and slabs taken over, in order
     bool read = false;                   // no contribution may follow
     bool fixed = false;                  // written in its own buffer only
+    bool real = false;                   // of real numbers: never summed or taken over
 };
 
 struct Prod {
@@ -158,6 +159,8 @@ bool Program::make_grouped(size_t budget, bool keep) {
             xt.parts = xt.own;
             tens.push_back(std::move(xt));
         }
+        if (g_dry_run && (size_t)nd.count * (nd.real ? esz / 2 : esz) > dry_bytes(nd.write))
+            throw LrccError(1, "a tensor of a grouped program is larger than its array");
         if (constants.count(nd.write)) return false;      // read before it is written
         auto ins = ids.emplace(nd.write, (int)tens.size());
         if (ins.second) {
@@ -169,7 +172,9 @@ bool Program::make_grouped(size_t budget, bool keep) {
         Tensor &t = tens[ti];
         const bool fresh = ins.second;
         if (t.count != nd.count || t.read || t.fixed) return false;
-        if (!nd.also.empty()) t.fixed = true;
+        if (!nd.also.empty() || nd.real) t.fixed = true;
+        t.real = nd.real;
+        if (nd.real && (nd.kind != Node::WRITE || nd.acc)) return false;
         if (nd.kind == Node::ZERO) {
             if (!t.parts.empty()) return false;
             continue;
@@ -194,7 +199,7 @@ bool Program::make_grouped(size_t budget, bool keep) {
             }
             Tensor &t = tens[ti];            // (tens may have moved)
             const std::vector<int> &sp = tens[src->second].parts;
-            if (sp.empty() || tens[src->second].count != t.count) return false;
+            if (sp.empty() || tens[src->second].count != t.count || tens[src->second].real) return false;
             t.parts.insert(t.parts.end(), sp.begin(), sp.end());
             continue;
         }

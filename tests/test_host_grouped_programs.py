@@ -1,4 +1,6 @@
 """Layout of the grouped form of small recorded programs (dry run, no device)."""
+import pytest
+
 from tests.grouped_cases import run
 
 
@@ -19,3 +21,11 @@ def test_tensor_that_is_only_cleared(tmp_path):
     """A tensor with a clear and no other writer, read by other programs."""
     rc, out = run(tmp_path, "cleared")
     assert rc == 0, out
+
+
+@pytest.mark.parametrize("nk,o,v,naux,nrhs", [(1, 1, 1, 1, 1), (1, 3, 5, 4, 2), (3, 5, 7, 9, 2)])
+def test_tensors_fit_their_arrays(nk, o, v, naux, nrhs):
+    """The dry run compares the extent that each op of a grouped program declares with the array it stores to
+    (the real diagonals of the preconditioner are half as large as complex ones)."""
+    from paper_2508_01266_amd import plan_check
+    plan_check(nk, o, v, naux, nrhs)
