@@ -133,7 +133,10 @@ lrcc_status lrcc_set_amplitudes(lrcc_ctx *ctx, const double *t1, const double *t
  * denominators): y_r = (A - omega_r) x_r with A the CCSD Jacobian dOmega/dT.
  * omega may be NULL (all zero).  x/y are HOST buffers in the layouts above.
  * precision LRCC_FP64 computes in complex128; LRCC_FP32 in complex64 on the
- * matrix cores (inputs and outputs stay complex128). */
+ * matrix cores (inputs and outputs stay complex128).  Large complex64 products
+ * are formed from three bf16 parts of every operand: elements below 8e-34 in
+ * magnitude then enter with an error of up to 5e-41 instead of their own
+ * rounding; larger ones, infinities and NaN as in the other products. */
 lrcc_status lrcc_apply_sigma(lrcc_ctx *ctx, int nrhs, const double *omega,
                              const double *x1, const double *x2, double *y1, double *y2,
                              int precision);

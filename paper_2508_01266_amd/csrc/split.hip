@@ -4,9 +4,12 @@
 // roundings of x and of what is left), and a product is formed from six bf16 products with fp32
 // accumulation, smallest first: h l + l h + m m + m h + h m + h h.  The terms left out (m l, l m, l l)
 // are below 2^-24 |a b|.  The matrix cores run bf16 16 times as fast as fp32, so six products leave a
-// factor of 2.7; a complex product takes 24 of them.  An infinite operand gives NaN (its remainder is
-// NaN), a finite one above the largest bf16 number, 3.39e38, too.
-#include "group.hpp"
+// factor of 2.7; a complex product takes 24 of them.  An operand that rounds to an infinite bf16 number (above
+// 3.396e38, or infinite) has no such parts and leaves NaN: a tile with a sum that is not finite is formed again
+// by tile_product, so that it holds what the fp32 matrix cores give (all NaN, Nk=2, o=8, v=40, 24 vectors: 5.4 ms
+// against 3.1 of ordinary numbers).  An operand below 2^-110 = 8e-34 loses the bits of its parts under the
+// smallest bf16 number, 2^-133.
+#include "tile.hpp"
 
 namespace lrcc {
 
@@ -51,9 +54,28 @@ constexpr int STM = 128, STN = 64, STK = 32, SKG = STK / 8;
 // the k groups of a row start 8 banks apart
 constexpr int SSA = STM + 2, SSB = STN + 2;
 struct SplitLds { u4 a[6 * SKG * SSA], b[6 * SKG * SSB]; };
+static_assert(sizeof(TileLds<float, 64, 64>) <= sizeof(SplitLds), "LDS of the tiles formed again");
+
+// The tile on the fp32 matrix cores.  A function of its own, never inlined: in the kernels' body it costs the
+// main loop its scalar registers (Nk=3, o=10, v=60, 6 vectors, transposed: 24.1 ms inlined, 22.2 so, 22.0 without
+// the check; Nk=5, o=8, v=40, 48 vectors: 112.6, 107.2 and 106.9).
+__device__ __attribute__((noinline)) void form_again(const GemmArgs *gp, SplitLds *lds, int m0, int n0, int sb, int tbeg,
+                                                     int tend, float js, int beta, void *Cblock, float2 *dense) {
+    const GemmArgs &g = *gp;
+    const int ksteps = (g.K + STK - 1) / STK, k16 = (g.K + kGroupTK - 1) / kGroupTK;
+    auto at = [&](int t) {                          // step t of 32 in steps of 16
+        const int s = t / (ksteps > 0 ? ksteps : 1), left = 2 * (t - s * ksteps);
+        return s * k16 + (left < k16 ? left : k16);
+    };
+    for (int h = 0; h < STM; h += 64) {
+        tile_product<float, 64, 64, 32, 32, true>(g, *reinterpret_cast<TileLds<float, 64, 64> *>(lds), m0 + h, n0, sb,
+                                                  at(tbeg), at(tend), js, beta, Cblock, dense);
+        __syncthreads();
+    }
+}
 
 template <bool RUN>
-__device__ __forceinline__ void split_tile(const GemmArgs &g, SplitLds &lds, int m0, int n0, int sb, int tbeg, int tend,
+__device__ __forceinline__ void split_tile(const GemmArgs &g, const GemmArgs *gp, SplitLds &lds, int m0, int n0, int sb, int tbeg, int tend,
                                            float js, int beta, void *Cblock, float2 *dense) {
     constexpr int TM = STM, TN = STN, TK = STK, KG = SKG, SA = SSA, SB = SSB;
     constexpr int FM = 4, FN = 2, UA = TM * KG / NT, UB = TN * KG / NT;
@@ -197,6 +219,23 @@ __device__ __forceinline__ void split_tile(const GemmArgs &g, SplitLds &lds, int
         }
         __syncthreads();
     }
+    // 0 unless some sum is not finite; the LDS is free (the loop ends with a barrier)
+    float nan = 0;
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) nan += accr[i][j][r] * 0.0f + acci[i][j][r] * 0.0f;
+    unsigned *const again = reinterpret_cast<unsigned *>(lds.a);
+    const bool any = __any(nan != 0.0f);            // (true for NaN)
+    if (lane == 0) again[wave] = any;
+    __syncthreads();
+    if (again[0] | again[1] | again[2] | again[3]) {
+        __syncthreads();
+        form_again(gp, &lds, m0, n0, sb, tbeg, tend, js, beta, Cblock, dense);
+        return;
+    }
     if (dense) {
 #pragma unroll
         for (int i = 0; i < FM; ++i)
@@ -265,7 +304,9 @@ __global__ void __launch_bounds__(NT, 2) gemm_split_kernel(GemmArgs g) {
     const int tbeg = (int)(nsteps * split / g.ksplit), tend = (int)(nsteps * (split + 1) / g.ksplit);
     float2 *dense = g.ksplit > 1 ? reinterpret_cast<float2 *>(g.part) +
                                        ((i64)split * g.njobs_all + g.job0 + job) * g.M * g.N : nullptr;
-    split_tile<RUN>(g, lds, m0, n0, sb, tbeg, tend,
+    // (the arguments where the launch put them: the address of g would be that of a copy)
+    const GemmArgs *const gp = (const GemmArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+    split_tile<RUN>(g, gp, lds, m0, n0, sb, tbeg, tend,
                     g.jscale ? g.jscale[g.job0 + job] : 1.0f, g.beta, reinterpret_cast<float2 *>(g.C) + g.offC[job], dense);
 }
 
@@ -277,8 +318,8 @@ __global__ void __launch_bounds__(NT, 2) gemm_split_group_kernel(const GemmArgs 
     __shared__ SplitLds lds;
     const GroupItem it = items[blockIdx.x];
     const GemmArgs &g = ops[it.op];
-    if (split_run(g)) split_tile<true>(g, lds, it.m0, it.n0, it.sb, it.t0, it.t1, it.js, it.beta, it.C, nullptr);
-    else split_tile<false>(g, lds, it.m0, it.n0, it.sb, it.t0, it.t1, it.js, it.beta, it.C, nullptr);
+    if (split_run(g)) split_tile<true>(g, &g, lds, it.m0, it.n0, it.sb, it.t0, it.t1, it.js, it.beta, it.C, nullptr);
+    else split_tile<false>(g, &g, lds, it.m0, it.n0, it.sb, it.t0, it.t1, it.js, it.beta, it.C, nullptr);
 }
 
 hipError_t launch_split_group(const GemmArgs *ops, const GroupItem *items, int n, hipStream_t s) {
