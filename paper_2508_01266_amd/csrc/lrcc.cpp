@@ -717,7 +717,7 @@ void upload_amplitudes(lrcc_ctx *c, const double *t1h, const double *t2h) {
     HIPCHK(hipMemcpy(S.t2.p, tmp.data(), tmp.size() * sizeof(double), hipMemcpyHostToDevice));
 }
 
-bool tune_lookup(const std::string &key, std::vector<int> &choice);
+bool tune_lookup(const std::string &key, size_t count, std::vector<int> &choice);
 void tune_store(const std::string &key, const std::vector<int> &choice);
 
 // With autotuning on, the first run of an amplitude-dependent program picks its GEMM tiles (the
@@ -728,7 +728,7 @@ static void tune_pre(lrcc_ctx *c, Program *p, const char *which, hipStream_t st)
     std::snprintf(b, sizeof b, "v10,%s,%d,%d,%d,%d,ladder%d,mesh%dx%dx%d", which, c->nk, c->no, c->nv, c->naux,
                   c->ladder_mode, c->km.n0, c->km.n1, c->km.n2);
     std::vector<int> choice;
-    if (tune_lookup(b, choice)) {
+    if (tune_lookup(b, p->choices(), choice)) {
         p->apply(choice);
         return;
     }
@@ -1375,7 +1375,9 @@ std::string tune_key(lrcc_ctx *c, int prec, int R, bool adj, int variant, int pa
     return b;
 }
 
-bool tune_lookup(const std::string &key, std::vector<int> &choice) {
+// The last line of `key` with `count` choices.  The launches of one key can differ: the momentum classes of a batch
+// and the grouped form depend on the free device memory; choices recorded for others would go to other products.
+bool tune_lookup(const std::string &key, size_t count, std::vector<int> &choice) {
     const char *path = std::getenv("LRCC_TUNE_CACHE");
     if (!path) return false;
     FILE *f = std::fopen(path, "r");
@@ -1386,13 +1388,15 @@ bool tune_lookup(const std::string &key, std::vector<int> &choice) {
         std::string l(line);
         if (l.compare(0, key.size() + 1, key + " ") != 0) continue;
         // the choices: whitespace-separated candidate indices after the key
-        choice.clear();
+        std::vector<int> c;
         const char *q = l.c_str() + key.size();
         char *end = nullptr;
         for (long x = std::strtol(q, &end, 10); end != q; x = std::strtol(q, &end, 10)) {
-            choice.push_back((int)x);
+            c.push_back((int)x);
             q = end;
         }
+        if (c.size() != count) continue;
+        choice = std::move(c);
         found = true;
     }
     std::fclose(f);
@@ -1416,7 +1420,7 @@ void tune_store(const std::string &key, const std::vector<int> &choice) {
 hipError_t run_sigma(lrcc_ctx *c, Program *p, hipStream_t st) {
     if (c->autotune && !p->tuned) {
         std::vector<int> choice;
-        if (tune_lookup(p->tune_key, choice)) {
+        if (tune_lookup(p->tune_key, p->choices(), choice)) {
             p->apply(choice);
         } else {
             hipError_t e = p->autotune(st, choice);

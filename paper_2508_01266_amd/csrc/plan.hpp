@@ -129,6 +129,8 @@ struct Program {
     template <typename T>
     bool make_grouped(size_t budget, bool keep);
     std::vector<Tunable> tunables;
+    // numbers of a tuning choice: one per tunable launch and, where there is a grouped form, 0 grouped or 1 op by op
+    size_t choices() const { return tunables.size() + (grouped.empty() ? 0 : 1); }
     bool tuned = false;
     std::string tune_key;
     // Time every tunable op under each candidate (full program runs, so the
