@@ -58,7 +58,8 @@ double Program::tag_mfma_flops(int t) const {
     double f = 0;
     for (const auto &kv : gemm_ops) {
         if (kv.first >= tags.size() || tags[kv.first] != t) continue;
-        const int sh = gemm_shape(*kv.second.args, kv.second.fp64);
+        const auto it = group_tiles.find(kv.first);
+        const int sh = runs_grouped() && it != group_tiles.end() ? it->second : gemm_shape(*kv.second.args, kv.second.fp64);
         f += (double)kv.second.flops * (!kv.second.fp64 && sh == kSplitTile ? 6.0 : 1.0);   // six bf16 products per fp32 one
     }
     return f;

@@ -107,6 +107,7 @@ struct Program {
         std::string name;
     };
     std::vector<Launch> grouped;
+    std::map<size_t, int> group_tiles;   // tiles of the products that share launches in it, by op
     bool use_grouped = true;             // run the grouped form where there is one
     bool runs_grouped() const { return use_grouped && !grouped.empty(); }
     // node of the op recorded last

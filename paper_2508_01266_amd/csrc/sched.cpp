@@ -106,6 +106,7 @@ bool Program::group(size_t budget, bool keep) {
 template <typename T>
 bool Program::make_grouped(size_t budget, bool keep) {
     grouped.clear();
+    group_tiles.clear();
     if (nodes.size() != ops.size()) return false;
     for (size_t i = 0; i < nodes.size(); ++i)
         if (nodes[i].op != i) return false;
@@ -302,6 +303,7 @@ bool Program::make_grouped(size_t budget, bool keep) {
                 p.alone = true;
                 continue;
             }
+            group_tiles[p.node] = p.tile;
             units[launch_of(p)] += (double)p.tiles * kGroupTiles[p.tile].frags * p.steps;
         }
         // a workgroup runs at most about half of its launch's average work per compute unit in one
