@@ -496,8 +496,7 @@ void raw_gemm(Program &P, GemmArgs g, const std::vector<i64> &offC, const std::v
     g.sk = split_magic(g.sk);
     // split-K when the job x tile grid cannot fill the chip but the jobs have long reductions
     {
-        const i64 tn = g.M <= 16 ? (g.N + 255) / 256 : (g.N + 63) / 64;
-        const i64 tiles = (i64)g.njobs * ((g.M + 63) / 64) * tn;
+        const i64 tiles = (i64)g.njobs * ((g.M + 63) / 64) * ((g.N + 63) / 64);
         const i64 steps = (i64)segA.size() * ((g.K + 15) / 16) / g.njobs;  // average per job
         i64 ks = 1;
         if (tiles < 1024 && steps >= 64) {
