@@ -28,7 +28,11 @@
  *       x1/y1 [nrhs][nk][nocc][nvir], x2/y2 [nrhs][nk][nk][nk][o][o][v][v]
  *   - ownership: the caller owns every buffer it passes; the library copies
  *     inputs during the call and writes outputs only on success.  A context
- *     owns its device memory; lrcc_destroy frees it.  A context is not
+ *     owns its device memory; lrcc_destroy frees it.  It keeps the work tensors of
+ *     every product used (one program per direction, precision and nrhs), with
+ *     extra arrays for grouped launches of at most 1 GiB and an eighth of the
+ *     memory that is free at its first use, until amplitudes or Hamiltonian are
+ *     replaced; without them it runs op by op.  A context is not
  *     thread-safe; distinct contexts are independent.
  *   - errors: every call returns an lrcc_status; nothing unwinds across the
  *     ABI; lrcc_last_error() describes the last failure of that context.

@@ -451,9 +451,12 @@ void convert_kt(Program &P, State<float> &dst_state, KT &dst, const KT &src, lrc
 }
 
 // ---------------------------------------------------------------- precompute
-// most device memory of the extra arrays of a program's grouped form (six doubles arrays of 64 MB, the
-// largest that are split over several, with room for the smaller tensors)
-constexpr size_t kGroupBudget = (size_t)1 << 30;
+// Most device memory for the extra arrays of a program's grouped form made now.
+size_t group_budget() {
+    size_t fr = SIZE_MAX, tot = 0;
+    if (!g_dry_run && hipMemGetInfo(&fr, &tot) != hipSuccess) return 0;
+    return group_budget_of(fr);
+}
 // Allocate the amplitude-dependent state and record the programs that compute it
 // from the device amplitudes (run again whenever the amplitudes change).
 void build_state(lrcc_ctx *c) {
@@ -670,7 +673,7 @@ void build_state(lrcc_ctx *c) {
         const void *fbe = S.Fbe.p, *fmj = S.Fmj.p;
         writes(S.dpair, (i64)nk * n, {fbe, fmj}, [=](hipStream_t s, void *d) { return pair_diag(fbe, fmj, d, nk, o, v, s); });
     }
-    (void)P.group<double>(kGroupBudget, true);
+    (void)P.group<double>(group_budget(), true);
     c->pre64 = std::move(Pp);
     S.ready = true;
 
@@ -782,7 +785,7 @@ Program *lean_program(lrcc_ctx *c, bool lin) {
         auto g = P.gemm_ops.find(i);
         if (g != P.gemm_ops.end()) L.gemm_ops[L.ops.size() - 1] = g->second;
     }
-    return L.group<double>(kGroupBudget, true) ? slot.get() : nullptr;
+    return L.group<double>(group_budget(), true) ? slot.get() : nullptr;
 }
 
 // Recompute every amplitude-dependent block from the device amplitudes.
@@ -1464,8 +1467,8 @@ Program *sigma_program(lrcc_ctx *c, int prec, int R, bool adjoint = false, int v
     p->tune_key = tune_key(c, prec, R, adjoint, variant, p->ladder_path);
     c->progs[key].reset(p);
     c->progmem[key] = std::move(mem);
-    if (prec == LRCC_FP64) (void)p->group<double>(kGroupBudget);
-    else (void)p->group<float>(kGroupBudget);
+    if (prec == LRCC_FP64) (void)p->group<double>(group_budget());
+    else (void)p->group<float>(group_budget());
     return p;
 }
 

@@ -87,6 +87,13 @@ struct Node {
     std::vector<std::pair<void *, i64>> also;
 };
 
+// Most bytes of the extra arrays of one grouped form, by the free device memory: 1 GiB (six doubles arrays of
+// 64 MB, the largest that are split over several, with room for the smaller tensors), and an eighth of what is
+// free, as for the ladder's scratch arrays, so that programs never take the last of it.
+constexpr size_t group_budget_of(size_t free_bytes) {
+    return free_bytes / 8 < ((size_t)1 << 30) ? free_bytes / 8 : (size_t)1 << 30;
+}
+
 // A recorded sequence of device launches plus the device memory it owns.
 struct Program {
     std::vector<std::function<hipError_t(hipStream_t)>> ops;

@@ -158,6 +158,24 @@ int cleared() {
     return made && !clears ? 1 : 0;
 }
 
+// the extra arrays take at most 1 GiB and an eighth of the free memory: a program that needs more runs op by op
+int budget() {
+    const size_t gib = (size_t)1 << 30;
+    if (group_budget_of(288 * gib) != gib || group_budget_of(8 * gib) != gib || group_budget_of(4 * gib) != gib / 2 ||
+        group_budget_of(0) != 0) { std::printf("budget\n"); return 1; }
+    const i64 n = kBlocks * kBlock;
+    const Array A(kM * kK, 3), B(kK * kN, 5), Z(n);
+    Program P;
+    zero(P, Z.p, n);
+    product(P, A, B, Z.p, {0, 1});
+    product(P, A, B, Z.p, {0, 1, 2, 3});
+    output(P, Z.p, n);
+    const size_t need = 2 * n * 16;
+    const bool less = P.group<double>(group_budget_of(8 * need - 8)), enough = P.group<double>(group_budget_of(8 * need));
+    std::printf("%d %d\n", less, enough);
+    return !less && enough ? 0 : 1;
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -167,6 +185,7 @@ int main(int argc, char **argv) {
     g_dry_run = !g_run;
     if (name == "partial") return partial();
     if (name == "constants") return constants();
+    if (name == "budget") return budget();
     if (name == "cleared") return cleared();
     return 2;
 }

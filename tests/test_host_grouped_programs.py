@@ -29,3 +29,8 @@ def test_tensors_fit_their_arrays(nk, o, v, naux, nrhs):
     (the real diagonals of the preconditioner are half as large as complex ones)."""
     from paper_2508_01266_amd import plan_check
     plan_check(nk, o, v, naux, nrhs)
+
+
+def test_extra_arrays_leave_free_memory(tmp_path):
+    rc, out = run(tmp_path, "budget")
+    assert rc == 0, out
