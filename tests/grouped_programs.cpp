@@ -1,5 +1,6 @@
 // Small recorded programs for the grouped form (Program::group): their layout in a dry run, and on a device their
-// values when the same program runs grouped, op by op and grouped again.  grouped_programs NAME [run]
+// values when the same program runs grouped, op by op and grouped again; and single products with long reductions.
+// grouped_programs NAME [run]
 #include <hip/hip_runtime.h>
 
 #include <complex>
@@ -176,6 +177,63 @@ int budget() {
     return !less && enough ? 0 : 1;
 }
 
+// Relative error of one complex64 product of kM x n and n x kN random matrices on the fp32 (64x64) and bf16 tiles
+// in one piece each, against 64 bits
+int reduction(int n) {
+    constexpr int M = 64, N = 32;
+    typedef std::complex<float> cf;
+    unsigned long long state = 12345;
+    auto rnd = [&] {                     // uniform in [-1, 1), mean zero
+        state = state * 6364136223846793005ull + 1442695040888963407ull;
+        return (float)((double)(state >> 40) / (1 << 23) - 1.0);
+    };
+    std::vector<cf> A((size_t)M * n), B((size_t)n * N), C(M * N);
+    for (cf &x : A) x = cf(rnd(), rnd());
+    for (cf &x : B) x = cf(rnd(), rnd());
+    std::vector<cd> ref(M * N, 0);
+    for (int k = 0; k < n; ++k)
+        for (int m = 0; m < M; ++m) {
+            const cd a = A[(size_t)m * n + k];
+            for (int j = 0; j < N; ++j) {
+                const cd b = B[(size_t)k * N + j];
+                ref[m * N + j] += cd(a.real() * b.real() - a.imag() * b.imag(), a.real() * b.imag() + a.imag() * b.real());
+            }
+        }
+    auto up = [](const void *p, size_t bytes) {
+        void *d = nullptr;
+        if (hipMalloc(&d, bytes) != hipSuccess || hipMemcpy(d, p, bytes, hipMemcpyHostToDevice) != hipSuccess) std::exit(3);
+        return d;
+    };
+    const i64 zero64 = 0;
+    const int beg[2] = {0, 1};
+    GemmArgs g{};
+    g.A = up(A.data(), A.size() * sizeof(cf));
+    g.B = up(B.data(), B.size() * sizeof(cf));
+    g.C = up(C.data(), C.size() * sizeof(cf));
+    g.M = M; g.N = N; g.K = n;
+    g.sm = split_magic(Split{1, M}); g.sn = split_magic(Split{1, N}); g.sk = split_magic(Split{1, n});
+    g.Am = Strides{{0, 0, n}}; g.Ak = Strides{{0, 0, 1}};
+    g.Bk = Strides{{0, 0, N}}; g.Bn = Strides{{0, 0, 1}};
+    g.Cm = Strides{{0, 0, N}}; g.Cn = Strides{{0, 0, 1}};
+    g.bNfast = 1;
+    g.alpha_re = 1;
+    g.offC = g.segA = g.segB = (const i64 *)up(&zero64, sizeof zero64);
+    g.segBeg = (const int *)up(beg, sizeof beg);
+    g.njobs = g.njobs_all = g.ksplit = 1;
+    double err[2], norm = 0;
+    for (const cd &r : ref) norm += std::norm(r);
+    for (int q = 0; q < 2; ++q) {
+        g.shape = q ? kSplitTile : 1;
+        if (launch_gemm<float>(g, nullptr) != hipSuccess || hipDeviceSynchronize() != hipSuccess ||
+            hipMemcpy(C.data(), g.C, C.size() * sizeof(cf), hipMemcpyDeviceToHost) != hipSuccess) return 3;
+        double e = 0;
+        for (int i = 0; i < M * N; ++i) e += std::norm(cd(C[i]) - ref[i]);
+        err[q] = std::sqrt(e / norm);
+    }
+    std::printf("%d %.3e %.3e\n", n, err[0], err[1]);
+    return 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -184,6 +242,11 @@ int main(int argc, char **argv) {
     g_run = argc > 2 && !std::strcmp(argv[2], "run");
     g_dry_run = !g_run;
     if (name == "partial") return partial();
+    if (name == "reduction") {
+        for (int n : {40, 320, 1600, 12800, 98304})
+            if (reduction(n)) return 3;
+        return 0;
+    }
     if (name == "constants") return constants();
     if (name == "budget") return budget();
     if (name == "cleared") return cleared();
