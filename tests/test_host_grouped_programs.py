@@ -34,3 +34,14 @@ def test_tensors_fit_their_arrays(nk, o, v, naux, nrhs):
 def test_extra_arrays_leave_free_memory(tmp_path):
     rc, out = run(tmp_path, "budget")
     assert rc == 0, out
+
+
+@pytest.mark.parametrize("nk,o,v,naux,nrhs", [(1, 4, 12, 48, 9), (3, 4, 20, 72, 12), ((2, 2, 2), 1, 3, 4, 2)])
+def test_recorded_programs_run_grouped(monkeypatch, capfd, nk, o, v, naux, nrhs):
+    """The programs of the plan check: the blocks of the amplitudes, products and transposes in both precisions, lean
+    and perturbation forms."""
+    from paper_2508_01266_amd import plan_check
+    monkeypatch.setenv("LRCC_PLAN_DUMP", "1")
+    plan_check(nk, o, v, naux, nrhs)
+    forms = [ln for ln in capfd.readouterr().err.splitlines() if ln.startswith("grouped: ")]
+    assert len(forms) == 20, forms
