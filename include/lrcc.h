@@ -167,8 +167,9 @@ lrcc_status lrcc_apply_sigma_dev(lrcc_ctx *ctx, int nrhs, const double *omega,
  * 3 nrhs nk^3 o^2 v^2 complex elements of the precision, plus tables); other
  * errors as for lrcc_apply_sigma_dev.  In the automatic ladder mode the call
  * takes the integrals-rebuilt-in-LDS path (mode 1; mode 3 would put a momentum
- * class of integral blocks in the array too).  Results equal
- * lrcc_apply_sigma_dev's with the same ladder path and launch variants. */
+ * class of integral blocks in the array too).  The program runs op by op; results
+ * equal lrcc_apply_sigma_dev's with the same ladder path and launch variants, up to
+ * the order of sums where that call runs grouped. */
 lrcc_status lrcc_apply_sigma_dev_noalloc(lrcc_ctx *ctx, int nrhs, const double *omega, const void *x1,
                                          const void *x2, void *y1, void *y2, int precision, void *stream);
 
@@ -209,19 +210,21 @@ lrcc_status lrcc_set_ladder_mode(lrcc_ctx *ctx, int mode);
 
 /* Autotuning of launch variants: when enabled, the first application of each
  * sigma program (per problem size, nrhs, precision and direction) is run once
- * per candidate configuration (matrix-core GEMM tiles 64x64 or large; ladder
+ * per candidate configuration (matrix-core GEMM tiles; ladder
  * antisymmetry-packed or full-range), every tunable launch is timed with HIP
- * events and the fastest candidate is kept per launch.  If the environment
- * variable LRCC_TUNE_CACHE names a file, choices are read from and appended to
- * it (one line per program).  Results do not depend on the choice. */
+ * events and the fastest candidate is kept per launch; then the grouped form of
+ * the program, where there is one, against the tuned launches one by one.  If
+ * the environment variable LRCC_TUNE_CACHE names a file, choices are read from
+ * and appended to it (one line per program).  Results do not depend on the
+ * choice, up to the order of sums. */
 lrcc_status lrcc_set_autotune(lrcc_ctx *ctx, int enable);
 
 /* HIP-graph replay of the sigma (and transpose) applications: when enabled,
  * each application on a non-null stream that runs op by op is captured once per
  * set of buffer addresses and replayed as one graph launch (the solver uses a
- * stream of its own); programs that run grouped launch their few kernels directly,
- * which is faster than a graph of as many nodes.  Profiling events are not recorded inside graphs.  Disabling frees the
- * captured graphs. */
+ * stream of its own); programs that run grouped launch their few kernels
+ * directly, which is faster than a graph of as many nodes.  Profiling events are
+ * not recorded inside graphs.  Disabling frees the captured graphs. */
 lrcc_status lrcc_set_graphs(lrcc_ctx *ctx, int enable);
 
 /* Real floating-point operations executed by one sigma application for nrhs
@@ -264,10 +267,10 @@ lrcc_status lrcc_measure_peaks(int hip_device, double *mfma_f32_tflops, double *
 /* Host-only validation of the launch plans for a problem size: records every
  * kernel of lrcc_set_hamiltonian, lrcc_set_amplitudes and lrcc_apply_sigma (FP64
  * and FP32, nrhs right-hand sides) without a device, checking that every
- * address each matrix-core GEMM can form lies inside its operands, and that the tensors
- * of grouped programs fit their arrays.  Needs no
- * GPU and allocates no device memory.  On failure writes a message into msg
- * (msglen bytes, may be NULL) and returns LRCC_E_ARG (or LRCC_E_OOM). */
+ * address each matrix-core GEMM can form lies inside its operands, and that the
+ * tensors of grouped programs fit their arrays.  Needs no GPU and allocates no
+ * device memory.  On failure writes a message into msg (msglen bytes, may be
+ * NULL) and returns LRCC_E_ARG (or LRCC_E_OOM). */
 lrcc_status lrcc_plan_check(int nk, int nocc, int nvir, int naux, int nrhs, char *msg, int msglen);
 /* The same on an n0 x n1 x n2 k mesh (lrcc_set_kmesh); lrcc_plan_check is the
  * 1D chain (nk, 1, 1). */

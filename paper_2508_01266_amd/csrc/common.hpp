@@ -159,9 +159,7 @@ struct GemmArgs {
     int ksplit;
     void *part;
     const float *jscale; // per-job multiplier of alpha (full job list), or null
-    int kind;            // 0 generic, 1 ladder over integral blocks (a separate kernel symbol for
-                         // profiling); the launcher takes instances 2 (generic) and 3 (ladder) when
-                         // sk is a triangle split
+    int kind;            // 0 generic, 1 ladder over integral blocks (a separate kernel symbol for profiling)
 };
 
 // Tile of workgroup x of a job: workgroups x, x + 8, ... run on one die and its L2, and take a contiguous run of

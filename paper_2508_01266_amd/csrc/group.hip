@@ -5,8 +5,8 @@
 // What bounds it: at these sizes a product alone has a few workgroups and waits on launch, address
 // table and operand latency; side by side the products of a level fill the chip.  The molecular-limit
 // sigma (o=4, v=12, 9 right-hand sides, complex128) went from 0.65 ms in 53 launches to 0.09 ms in 11 by
-// this (0.062 now), the three-k chain (o=4, v=20, 12 right-hand sides) from 3.53 to 0.87 ms (0.58 now), Nk=4,
-// o=6, v=26 (6 right-hand sides, forward and backward) from 17.0 to 9.6 ms (7.3 now).
+// this (0.064 now), the three-k chain (o=4, v=20, 12 right-hand sides) from 3.53 to 0.87 ms (0.61 now), Nk=4,
+// o=6, v=26 (6 right-hand sides, forward and backward) from 17.0 to 9.6 ms (7.4 now).
 #include "tile.hpp"
 
 namespace lrcc {

@@ -11,7 +11,7 @@ hipError_t batched_dot(const void *u, const void *v, int R, i64 n, double scale,
 hipError_t batched_axpby(void *y, const void *x, const void *alpha, double beta, int R, i64 n, hipStream_t s);
 // Krylov vectors (and the vectors orthogonalised against them) are stored in complex128, or in
 // complex64 with f32 = 1 (the complex64 inner solves); arithmetic is complex128 in both.
-// y = beta y + alpha_r x on that storage
+// (vs, vd)_r *= alpha_r: singles and doubles on that storage
 hipError_t basis_scale(void *vs, void *vd, const void *alpha, int R, i64 n1, i64 n2, int f32, hipStream_t s);
 // singles divided by (ev - eo - w), doubles by (ev2 + ev2 - eo2 - eo2 - w)
 hipError_t precond(void *o1, void *o2, const void *i1, const void *i2, const double *eo, const double *ev,
