@@ -31,7 +31,7 @@
  *     owns its device memory; lrcc_destroy frees it.  It keeps the work tensors of
  *     every product used (one program per direction, precision and nrhs), with
  *     extra arrays for grouped launches of at most 1 GiB and an eighth of the
- *     memory that is free at its first use, until amplitudes or Hamiltonian are
+ *     memory that is free at its first use, until the Hamiltonian is
  *     replaced; without them it runs op by op.  A context is not
  *     thread-safe; distinct contexts are independent.
  *   - errors: every call returns an lrcc_status; nothing unwinds across the
