@@ -290,7 +290,8 @@ __device__ __forceinline__ double2 slab_sum(const SlabList &l, i64 at) {
 // row, and - diag_j x_ijab on the unique pairs (ka, a) < (kb, b) alone.  These are far the largest terms: they are
 // added here, in double (in the products with the other elements they double the rounding of a
 // complex64 product's doubles, from 1.0e-7 to 2.1e-7 at Nk=5, o=8, v=40), from the elements of x2 that omega reads
-// again a moment later.  The workgroup of an orbit's first
+// again a moment later (48 complex64 vectors of that size: 7.2 ms for 41 GB; 6.5 with one read of x2, as an x2 that
+// is antisymmetric would allow).  The workgroup of an orbit's first
 // row ((ki, i) <= (kj, j), ka <= kb) writes all of its distinct rows; the others return at once.
 template <typename T, int NS>
 __global__ void k_outputs(SlabList s1, SlabList zs, SlabList xs, const double2 *diag, const double2 *x1,
